@@ -171,6 +171,16 @@ def _static_inputs(c, seed):
     return x, sent
 
 
+_made = []
+
+
+def _streams():
+    """The program's two streams: one that trains and one for the All-Reduce, whatever contexts it holds."""
+    if not _made:
+        _made.extend(torch.cuda.Stream(device=DEV) for _ in range(2))
+    return _made
+
+
 class _State:
     pass
 
@@ -205,13 +215,14 @@ def prepare(case, seed):
         st.opt = LASGD(nets, lr=st.lr, momentum=MU, nesterov=True, weight_decay=WD, m=c["m"])
         st.opt.step()                                                      # first update, send, first All-Reduce
         return st
-    st.main = torch.cuda.Stream(device=DEV)
-    st.side = torch.cuda.Stream(device=DEV) if c["streams"] == 2 else st.main
+    main, side = _streams()
+    if c["streams"] == 1:
+        side = main
     bf16 = c["storage"] == "bf16"
     esize = 2 if bf16 else 4
     torch.cuda.synchronize()
     st.ctx = B.Context(K, numels, storage=B.BF16 if bf16 else B.F32, momentum=MU, nesterov=c.get("nesterov", True),
-                       wd_scalar=WD, main_stream=st.main.cuda_stream, side_stream=st.side.cuda_stream)
+                       wd_scalar=WD, main_stream=main.cuda_stream, side_stream=side.cuda_stream)
     for k in range(K):
         st.ctx.bind(k, [st.x[k].data_ptr() + o * esize for o in off[:-1]], [st.g[k].data_ptr() + o * esize for o in off[:-1]])
     if bf16:
