@@ -16,7 +16,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -953,35 +952,26 @@ void lasgd_destroy(lasgd_ctx *c)
 } // extern "C"
 
 // ---- the allocation-free entry point ---------------------------------------
-// z of lasgd_global_update_static lives in this file-scope device array instead
-// of an allocation.  Every GPU that loads the library holds its own copy (128 MiB)
-// until the process ends.  In host code the array's name is only a stand-in for
-// the symbol; its device address is looked up once per device and that pointer
-// is what kernels and copies receive.
 constexpr int64_t kStaticMaxN = LASGD_STATIC_MAX_N;
-static __device__ __align__(256) float scratch[kStaticMaxN];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-float *g_scratch_ptr[kMaxDevices] = {};
-
-// Device address of `scratch` on the current device (looked up on first use).
-lasgd_status scratch_for_current_device(float **out)
+template <int NT> hipError_t launch_flat_update(const FlatArgs &a, uint32_t blocks, hipStream_t st)
 {
-    int dev = -1;
-    LASGD_HIP(nullptr, hipGetDevice(&dev));
-    if (dev < 0 || dev >= kMaxDevices) return fail(nullptr, LASGD_ERR_UNSUPPORTED, "device ordinal %d outside 0..%d", dev, kMaxDevices - 1);
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        float *p = nullptr;
-        LASGD_HIP(nullptr, hipGetSymbolAddress((void **)&p, HIP_SYMBOL(scratch)));
-        if (!p) return fail(nullptr, LASGD_ERR_HIP, "hipGetSymbolAddress returned a NULL address");
-        g_scratch_ptr[dev] = p;
-    }
-    *out = g_scratch_ptr[dev];
-    return LASGD_OK;
+    // One wave per replica while a workgroup can hold that many (16), then two or four replicas a wave.  Measured with
+    // 1, 2, 4 replicas a wave at n = 12e6: K = 4 125, 129, 131 us, K = 8 258, 269, 273, K = 16 546, 562, 565.  Two replicas
+    // a wave win for K = 4..8 where the vectors stay in the memory-side cache and the waves are more than the chip holds
+    // at once (8192): K = 8, n = 2^19 13.8 us against 16.1, n = 600,000 13.5 against 13.9, K = 4, n = 2^20 12.4 against 14.0;
+    // below that the extra wave is free and shortens the call (K = 4, n = 300,000 4.5 against 4.9), and from K = 12 on one
+    // a wave is ahead again (n = 1,000,003 31.6 against 34.2).
+    uint32_t R = a.K <= kGroupWaves ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
+    if (NT == 0 && a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > 8192u) R = 2u;
+    const dim3 bs(64u * ((a.K + R - 1u) / R));
+    const size_t lds = (size_t)a.K * 256u * sizeof(float);
+    if (R == 1u) hipLaunchKernelGGL((flat_update_kernel<1, NT>), dim3(blocks), bs, lds, st, a);
+    else if (R == 2u) hipLaunchKernelGGL((flat_update_kernel<2, NT>), dim3(blocks), bs, lds, st, a);
+    else hipLaunchKernelGGL((flat_update_kernel<4, NT>), dim3(blocks), bs, lds, st, a);
+    return hipGetLastError();
 }
 
 } // namespace
@@ -1015,27 +1005,16 @@ extern "C" lasgd_status lasgd_global_update_static(int32_t K, int64_t n, float *
                     return fail(nullptr, LASGD_ERR_INVALID, "%s of replica %d overlaps %s of replica %d",
                                 i < K ? "x" : "sent", i < K ? i : i - K, j < K ? "x" : "sent", j < K ? j : j - K);
             }
-        float *z = nullptr;
-        lasgd_status st = scratch_for_current_device(&z);
-        if (st != LASGD_OK) return st;
-        a.z = z;
         a.n = (uint64_t)n;
-        a.nvec = (uint64_t)n / 4u;
         a.K = (uint32_t)K;
         a.use_mul = is_pow2((uint32_t)K) ? 1 : 0;
         a.inv_k = 1.0 / (double)K;
         a.k_as_double = (double)K;
         a.resnap = resnapshot ? 1 : 0;
-        hipStream_t hs = (hipStream_t)stream;
-        // one thread per 128-bit vector, at least enough threads for the scalar tail
-        uint64_t blocks = (a.nvec + 255u) / 256u;
-        if (blocks < 1) blocks = 1;
-        if (blocks > 65535u * 16u) blocks = 65535u * 16u;
-        hipLaunchKernelGGL(flat_mean_kernel, dim3((uint32_t)blocks), dim3(256), 0, hs, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return fail(nullptr, LASGD_ERR_HIP, "mean launch failed: %s", hipGetErrorString(e));
-        hipLaunchKernelGGL(flat_merge_kernel, dim3((uint32_t)blocks, (uint32_t)K), dim3(256), 0, hs, a);
-        e = hipGetLastError();
+        // the streaming hint from the size on at which the vectors no longer fit the 256 MB memory-side cache
+        const bool hint = (uint64_t)K * (uint64_t)n * sizeof(float) >= (128ull << 20);
+        const uint32_t blocks = (uint32_t)(((uint64_t)n + 255u) / 256u);
+        const hipError_t e = hint ? launch_flat_update<3>(a, blocks, (hipStream_t)stream) : launch_flat_update<0>(a, blocks, (hipStream_t)stream);
         if (e != hipSuccess) return fail(nullptr, LASGD_ERR_HIP, "global-update launch failed: %s", hipGetErrorString(e));
         return LASGD_OK;
     } catch (...) {

@@ -120,3 +120,34 @@ def test_static_global_update_refuses_bad_arguments():
     assert e.value.status == B.ERR_INVALID
     torch.cuda.synchronize()
     assert float(t.abs().sum()) == 0.0 and float(u.abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("K", [1, 2, 5, 8, 9, 16, 17, 31, 32, 33, 64])
+def test_static_global_update_every_group_shape(K):
+    """Every shape of the one-pass kernel (one, two or four replicas a wave; the sum in every wave up to K = 8 and
+    shared beyond) at sizes around a workgroup's 256 elements and a lane's four, bit for bit against the oracle;
+    the elements behind each vector's end stay untouched."""
+    # K = 5 at 500,001 elements: more waves than the chip holds at once, two replicas a wave with one slot empty
+    for n in (1, 3, 4, 255, 256, 257, 1030) + ((500_001,) if K == 5 else ()):
+        for resnapshot in (True, False):
+            rng = np.random.default_rng(1000 * K + n)
+            hx = rng.standard_normal((K, n + 8), dtype=np.float32)
+            hs = rng.standard_normal((K, n + 8), dtype=np.float32)
+            pad = (n + 8 + 3) // 4 * 4                       # rows start on 16 bytes and no wider boundary
+            x, s = torch.zeros(K, pad, device="cuda:0"), torch.zeros(K, pad, device="cuda:0")
+            x[:, :n + 8], s[:, :n + 8] = torch.from_numpy(hx).cuda(), torch.from_numpy(hs).cuda()
+            torch.cuda.synchronize()
+            say(f"[no-alloc] K={K} n={n} resnapshot={resnapshot}")
+            B.global_update_static([t.data_ptr() for t in x], [t.data_ptr() for t in s], n, resnapshot)
+            torch.cuda.synchronize()
+            orc = O32.Oracle(K, [n], 0.9, True, [0.0], threads=1)
+            for k in range(K):
+                orc.x[k][:], orc.s[k][:] = hx[k, :n], hs[k, :n]
+            orc.average()
+            orc.merge(resnapshot=resnapshot)
+            gx, gs = x.cpu().numpy(), s.cpu().numpy()
+            for k in range(K):
+                np.testing.assert_array_equal(_bits(gx[k, :n]), _bits(orc.x[k]), err_msg=f"x replica {k}")
+                np.testing.assert_array_equal(_bits(gs[k, :n]), _bits(orc.s[k]), err_msg=f"sent replica {k}")
+            np.testing.assert_array_equal(_bits(gx[:, n:n + 8]), _bits(hx[:, n:]))
+            np.testing.assert_array_equal(_bits(gs[:, n:n + 8]), _bits(hs[:, n:]))
