@@ -64,3 +64,27 @@ def test_k_models_with_autograd_gradients(m):
         assert 0 < np.abs(a - b).max() < 0.5
     finally:
         opt.close()
+
+
+def test_zero_grad_clears_every_gradient_in_place():
+    """All buffers, also one that the caller replaced, at unchanged addresses; saved-tensor checks still see the write;
+    a dropped gradient is refused as before."""
+    from paper_2203_13085_amd.torch_api import LASGD
+    dev = torch.device("cuda:0")
+    replicas = [torch.nn.ParameterList([torch.nn.Parameter(torch.ones(n, device=dev)) for n in (5, 1, 4097)]) for _ in range(3)]
+    opt = LASGD(replicas, lr=0.1)
+    try:
+        ps = [p for r in replicas for p in r]
+        ps[2].grad = torch.ones(4097, device=dev)
+        for p in ps:
+            p.grad.fill_(2.0)
+        at = [(p.grad.data_ptr(), p.grad._version) for p in ps]
+        opt.zero_grad()
+        torch.cuda.synchronize()
+        for p, (ptr, version) in zip(ps, at):
+            assert p.grad.data_ptr() == ptr and p.grad._version > version and not p.grad.any()
+        ps[1].grad = None
+        with pytest.raises(AttributeError):
+            opt.zero_grad()
+    finally:
+        opt.close()
