@@ -50,14 +50,17 @@ struct lasgd_ctx {
     // device memory (one allocation, carved up)
     char *arena = nullptr;
     float *v = nullptr, *s = nullptr, *z = nullptr, *x32 = nullptr;
-    Tile *tiles = nullptr;           // the table for the current tile size (one of tiles_by_vec)
-    uint32_t ntiles = 0;
-    // one table per tile size ever used (vec = 1, 2, 4), kept until destroy: a graph captured
-    // under one tile size still points at its table after the tile size has been changed
-    Tile *tiles_by_vec[3] = {nullptr, nullptr, nullptr};
-    uint32_t ntiles_by_vec[3] = {0, 0, 0};
-    void **xptr = nullptr, **gptr = nullptr;     // device tables [K*n_tensors]
-    std::vector<void *> h_xptr, h_gptr;
+    // one set of lookup tables per tile size ever used (vec = 1, 2, 4), kept until destroy: a graph captured
+    // under one tile size still points at its tables after the tile size has been changed
+    struct Tables {
+        uint32_t *mem = nullptr;                 // the two arrays, one behind the other
+        const uint32_t *blocks = nullptr, *tile0 = nullptr;
+        uint32_t ntiles = 0;
+    };
+    Tables tables_by_vec[3];
+    const Tables *tables = nullptr;              // those of the current tile size
+    Record *records = nullptr;                   // device table [K*n_tensors]
+    std::vector<void *> h_xptr;
     std::vector<char> bound;
     int32_t n_bound = 0;
 
@@ -107,45 +110,54 @@ uint64_t round_up(uint64_t a, uint64_t b) { return (a + b - 1) / b * b; }
 
 bool is_pow2(uint32_t k) { return k && !(k & (k - 1)); }
 
-// Build (on the host) the tile list for 256*vec-element tiles.
-std::vector<Tile> build_tiles(const lasgd_ctx &c, int vec)
+// What fast_div expects for a divisor d in 1 .. 2^31.
+FastDiv make_div(uint32_t d)
 {
-    std::vector<Tile> t;
-    const uint64_t T = 256ull * vec;
-    for (int32_t i = 0; i < c.n_tensors; ++i) {
-        const uint64_t n = (uint64_t)c.numel[i];
-        for (uint64_t o = 0; o < n; o += T) {
-            Tile d{};
-            d.toff = o;
-            d.aoff = c.aoff[i] + o;
-            d.tensor = (uint32_t)i;
-            d.count = (uint32_t)((n - o < T) ? n - o : T);
-            d.wd = c.wd[i];
-            t.push_back(d);
-        }
-    }
-    return t;
+    const uint32_t l = d > 1u ? 32u - (uint32_t)__builtin_clz(d - 1u) : 0u;          // ceil(log2 d)
+    FastDiv f;
+    f.shift = 31u + l;
+    f.m = (uint32_t)(is_pow2(d) ? 1ull << 31 : (1ull << f.shift) / d + 1ull);
+    return f;
 }
 
-lasgd_status upload_tiles(lasgd_ctx *c, int vec)
+// Build (on the host) the lookup tables for 256*vec-element tiles and copy them to the device.
+lasgd_status upload_tables(lasgd_ctx *c, int vec)
 {
-    const int slot = vec == 1 ? 0 : vec == 2 ? 1 : 2;
-    if (!c->tiles_by_vec[slot]) {
-        std::vector<Tile> t = build_tiles(*c, vec);
-        if (t.size() > 0x7fffffffull / kMaxK) return fail(c, LASGD_ERR_UNSUPPORTED, "too many tiles (%zu)", t.size());
-        Tile *d = nullptr;
-        LASGD_HIP(c, hipMalloc(&d, t.size() * sizeof(Tile)));
-        hipError_t e = hipMemcpy(d, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice);
+    lasgd_ctx::Tables &t = c->tables_by_vec[vec == 1 ? 0 : vec == 2 ? 1 : 2];
+    if (!t.mem) {
+        const uint64_t T = 256ull * vec;
+        std::vector<uint32_t> tile0((size_t)c->n_tensors);
+        uint64_t tiles = 0;
+        for (size_t i = 0; i < tile0.size(); ++i) {
+            tile0[i] = (uint32_t)tiles;
+            tiles += ((uint64_t)c->numel[i] + T - 1) / T;
+            if (tiles > 0x7fffffffull / kMaxK) return fail(c, LASGD_ERR_UNSUPPORTED, "too many tiles (more than %llu)", 0x7fffffffull / kMaxK);
+        }
+        std::vector<uint32_t> host;              // blocks, then tile0
+        const size_t nblocks = (size_t)((tiles + (1u << kBlockShift) - 1) >> kBlockShift);
+        size_t t0 = 0;
+        for (size_t b = 0; b < nblocks; ++b) {
+            const uint32_t first = (uint32_t)(b << kBlockShift), next = first + (1u << kBlockShift);
+            while (t0 + 1 < tile0.size() && tile0[t0 + 1] <= first) ++t0;
+            host.push_back((uint32_t)t0 | (t0 + 1 < tile0.size() && tile0[t0 + 1] < next ? kMoreInBlock : 0u));
+        }
+        host.insert(host.end(), tile0.begin(), tile0.end());
+        host.insert(host.end(), kProbe, 0xffffffffu);
+        const size_t bytes = host.size() * sizeof(uint32_t);
+        uint32_t *d = nullptr;
+        LASGD_HIP(c, hipMalloc((void **)&d, bytes));
+        hipError_t e = hipMemcpy(d, host.data(), bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(d);
             (void)hipGetLastError();
-            return fail(c, LASGD_ERR_HIP, "tile table upload failed: %s", hipGetErrorString(e));
+            return fail(c, LASGD_ERR_HIP, "table upload failed: %s", hipGetErrorString(e));
         }
-        c->tiles_by_vec[slot] = d;
-        c->ntiles_by_vec[slot] = (uint32_t)t.size();
+        t.mem = d;
+        t.blocks = d;
+        t.tile0 = d + nblocks;
+        t.ntiles = (uint32_t)tiles;
     }
-    c->tiles = c->tiles_by_vec[slot];
-    c->ntiles = c->ntiles_by_vec[slot];
+    c->tables = &t;
     return LASGD_OK;
 }
 
@@ -179,19 +191,45 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     return t;
 }
 
+// How many waves a CU may hold at once in the streaming kernels, set through the LDS a workgroup asks for (and does
+// not use): 160 KiB in granules of 1280 bytes.  The memory system is fastest with about 60 KiB of loads in flight per
+// CU; with all 32 waves a CU the kernels reach it through L2 misses that evict each other.  us at 0 (32 waves), 5 (25),
+// 6 (21), 7 (18), 8 (16), 10 (12) granules a wave:
+//   local step (3 KiB of loads a wave)     ResNet-50 K = 8       642  636  629  619  633    -     bf16 663  647  631  616  626  (9: 646)
+//   update and step (4 KiB, and z)         ResNet-50 K = 8 *    1078 1074 1061 1040 1034 1022     * with the mean, 150
+//   global update (2 KiB, and z)           ResNet-50 K = 8 *     667  657  647  654  678  743
+//   snapshot (1 KiB)                       ResNet-50 K = 8       252  276  285  308  336  393
+// Where the state stays in the memory-side cache (no streaming hint) nothing is gained: MobileNetV2 K = 6 60 us at any of
+// these counts.
+constexpr uint32_t kLdsGranule = 1280;
+uint32_t pace_lds(int op, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
+{
+    if (!(nt & 3)) return 0;
+    uint32_t granules = op == OP_STEP ? 7u : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? 10u : 0u;
+    if (xa && op == OP_STEP_MERGE) {         // replicas that only step or only merge load less: the mean over the waves
+        const uint32_t both = (uint32_t)__builtin_popcountll(xa->step_mask & xa->merge_mask);
+        const uint32_t step = (uint32_t)__builtin_popcountll(xa->step_mask & ~xa->merge_mask);
+        const uint32_t merge = (uint32_t)__builtin_popcountll(xa->merge_mask & ~xa->step_mask);
+        granules = (10u * both + 7u * step + 6u * merge) / (both + step + merge);
+    }
+    const uint32_t bytes = granules * kLdsGranule * vec * waves_per_block;
+    return bytes < 65536u ? bytes : 65536u;
+}
+
 template <int VEC, int OP, bool BF16>
 hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, hipStream_t st, int nt)
 {
+    const uint32_t lds = pace_lds(OP, xa, nt, VEC, bs.x / 64u);
     if (xa) {      // extended variants: hints all on or all off
-        if (nt & 3) hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 3>), grid, bs, 0, st, a, *xa);
-        else hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 0>), grid, bs, 0, st, a, *xa);
+        if (nt & 3) hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 3>), grid, bs, lds, st, a, *xa);
+        else hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 0>), grid, bs, lds, st, a, *xa);
         return hipGetLastError();
     }
     switch (nt & 3) {
-    case 0: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 0>), grid, bs, 0, st, a); break;
-    case 1: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 1>), grid, bs, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 2>), grid, bs, 0, st, a); break;
-    default: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 3>), grid, bs, 0, st, a); break;
+    case 0: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 0>), grid, bs, lds, st, a); break;
+    case 1: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 1>), grid, bs, lds, st, a); break;
+    case 2: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 2>), grid, bs, lds, st, a); break;
+    default: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 3>), grid, bs, lds, st, a); break;
     }
     return hipGetLastError();
 }
@@ -214,15 +252,16 @@ hipError_t launch_op(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, 
 
 void fill_common(const lasgd_ctx *c, ApplyArgs &a)
 {
-    a.tiles = c->tiles;
-    a.xptr = c->xptr;
-    a.gptr = c->gptr;
+    a.blocks = c->tables->blocks;
+    a.tile0 = c->tables->tile0;
+    a.records = c->records;
+    a.tile_elems = 256u * (uint32_t)c->tune.vec;
     a.x32 = c->x32;
     a.v = c->v;
     a.s = c->s;
     a.z = c->z;
     a.npad = c->npad;
-    a.ntiles = c->ntiles;
+    a.ntiles = c->tables->ntiles;
     a.K = (uint32_t)c->K;
     a.n_tensors = (uint32_t)c->n_tensors;
     a.mu = c->mu;
@@ -250,10 +289,12 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     ApplyArgs &a = p.a;
     fill_common(c, a);
     int kper = (op == OP_MERGE || op == OP_STEP_MERGE) ? c->tune.kper_merge : c->tune.kper_step;
+    const int taking = xa ? __builtin_popcountll(xa->step_mask | xa->merge_mask) : c->K;
     if (kper < 1) kper = 1;
-    if (kper > c->K) kper = c->K;
+    if (kper > taking) kper = taking;
+    a.kcount = (uint32_t)taking;
     a.kper = (uint32_t)kper;
-    a.kgroups = (uint32_t)((c->K + kper - 1) / kper);
+    a.kgroups = (uint32_t)((taking + kper - 1) / kper);
     a.neg_lr = -lr;
     a.resnap = resnap;
     const bool merging = op == OP_MERGE || op == OP_STEP_MERGE;
@@ -271,9 +312,14 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     const uint64_t nitems = (uint64_t)a.full_items + (tail ? (uint64_t)a.tail_stride * a.kgroups : 0u);
     if (nitems == 0 || nitems > 0x7fffffffull) return fail(c, LASGD_ERR_UNSUPPORTED, "work-item count %llu out of range", (unsigned long long)nitems);
     a.nitems = (uint32_t)nitems;
+    a.by_per = make_div(a.chunk * a.kgroups);
+    a.by_chunk = make_div(a.chunk);
+    a.by_stride = make_div(a.tail_stride);
     const uint32_t wpb = (uint32_t)c->tune.waves_per_block;
     uint64_t blocks = (nitems + wpb - 1) / wpb;
     if (c->tune.max_blocks > 0 && blocks > (uint64_t)c->tune.max_blocks) blocks = (uint64_t)c->tune.max_blocks;
+    a.wpb = wpb;
+    a.nwaves = (uint32_t)blocks * wpb;
     p.op = op;
     p.grid = dim3((uint32_t)blocks);
     p.bs = dim3(64u * wpb);
@@ -310,29 +356,46 @@ lasgd_status enqueue_apply(lasgd_ctx *c, int op, float lr, int resnap, const Ext
 // The replica-group kernels: one workgroup per tile, W waves, R replicas per wave.
 struct GroupShape {
     uint32_t R, W, passes;
+    uint32_t delay;      // sleeps of 512 clocks before a wave's first load
     dim3 grid, bs;
     size_t lds;
 };
 
+// kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
 GroupShape group_shape(const lasgd_ctx *c, int kind)
 {
     GroupShape g{};
     const uint32_t K = (uint32_t)c->K;
-    // replicas a wave takes at a time (measured on MI355X).  Every wave of the SGD-AR kernel
-    // repeats the fp64 sum, so it prefers fewer, fatter waves sooner than the fused update,
-    // whose sum is shared out; beyond 16 replicas both do best with 8-wave workgroups.
-    if (kind == 0) g.R = K < 4u ? 1u : K <= 16u ? 2u : 4u;
-    else g.R = K <= kGroupWaves ? 1u : 4u;
+    const bool streaming = (c->tune.nontemporal & 3) != 0, bf16 = c->storage == LASGD_BF16;
+    // Replicas a wave takes at a time.  A wave with one replica has the fewest loads to wait for, but a workgroup of
+    // more than eight waves leaves slots empty until a whole workgroup's worth is free on one CU.  us on MI355X, R = 1
+    // against 2 (SGD-AR): ResNet-50 list K = 8 664, 688; ResNet-18 K = 12 460, 477; MobileNetV2 K = 13 196, 160; bf16 with
+    // its three more streams changes over earlier, ResNet-18 K = 10 467, 377.  R = 2 against 4: MobileNetV2 K = 24 308, 312,
+    // K = 32 433, 411.  In the memory-side cache two a wave from K = 9 on: MobileNetV2's first 60 tensors K = 16 8.0, 7.0.
+    // Fused update (its sum is the last thing a workgroup does): ResNet-50 K = 8 988, 1011; ResNet-18 bf16 K = 11 639, 642;
+    // K = 12 see below.
+    if (kind == 0) g.R = K <= (streaming && !bf16 ? 12u : 8u) ? 1u : K <= (streaming ? 24u : 32u) ? 2u : 4u;
+    else g.R = K <= kGroupWaves && !(streaming && K == 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     if (c->tune.group_r > 0) g.R = (uint32_t)c->tune.group_r;
     if (g.R > K) g.R = K >= 4 ? 4 : K >= 2 ? 2 : 1;
     g.W = (K + g.R - 1) / g.R;
     if (g.W > kGroupWaves) g.W = kGroupWaves;
     g.passes = (K + g.W * g.R - 1) / (g.W * g.R);
-    uint64_t blocks = c->ntiles;
+    uint64_t blocks = c->tables->ntiles;
     if (c->tune.max_blocks > 0 && blocks > (uint64_t)c->tune.max_blocks) blocks = (uint64_t)c->tune.max_blocks;
     g.grid = dim3((uint32_t)blocks);
     g.bs = dim3(64u * g.W);
     g.lds = (size_t)K * 256u * sizeof(float);
+    if (streaming && kind == 1 && K <= 12u && K != 11u && c->tune.group_r <= 0) {
+        // Paced like the other kernels (pace_lds): 16 to 21 waves a CU.  Without / with: ResNet-18 K = 4 224 / 222 us,
+        // ResNet-50 K = 8 1003 / 988; at K = 11 only one workgroup would fit (635 / 655).  At K = 12 two workgroups a CU (six waves of two replicas) are a little too much and
+        // one too little; there every wave starts about 0.6 us late: ResNet-18 696 -> 677 us, bf16 716 -> 697 (one replica
+        // a wave: 708 and 714, one workgroup a CU 688 and 709).  The SGD-AR kernel waits for its gradients in the middle,
+        // and holding waves back costs it (K = 8 664 / 688).
+        const size_t pace = (size_t)(g.R == 1u ? 6u : 8u) * kLdsGranule * g.W;
+        if (pace > g.lds) g.lds = pace;
+        if (K == 12u) g.delay = 3u;
+    }
     return g;
 }
 
@@ -352,9 +415,12 @@ hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t s
 }
 
 // kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
-hipError_t launch_group(int kind, const ApplyArgs &a, const GroupShape &g, hipStream_t st, bool bf16, int nt)
+hipError_t launch_group(int kind, ApplyArgs &a, const GroupShape &g, hipStream_t st, bool bf16, int nt)
 {
     const bool hint = (nt & 3) != 0;
+    a.wpb = g.W;
+    a.nwaves = g.grid.x;
+    a.delay = g.delay;
     if (kind == 0) {
         if (bf16) return hint ? launch_group_r<0, true, 3>(a, g, st) : launch_group_r<0, true, 0>(a, g, st);
         return hint ? launch_group_r<0, false, 3>(a, g, st) : launch_group_r<0, false, 0>(a, g, st);
@@ -379,8 +445,8 @@ hipError_t launch_average(const AvgArgs &a, dim3 grid, hipStream_t st, int split
     return hipGetLastError();
 }
 
-// Enqueue the mean of the replicas in `mask` on the side stream.
-lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic)
+// Enqueue the mean of the replicas in `mask` on `stream`.
+lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic, hipStream_t stream, int split)
 {
     AvgArgs a{};
     a.s = c->s;
@@ -397,7 +463,6 @@ lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic)
     a.elastic = elastic ? 1 : 0;
     a.beta = (double)c->beta;
     a.one_minus_beta = 1.0 - (double)c->beta;
-    const int split = c->tune.avg_split;
     const uint32_t bs1 = 64u * (uint32_t)c->tune.waves_per_block;           // block size of the unsplit kernel
     const uint64_t cols = split == 1 ? bs1 : 256u / (uint32_t)split;
     uint64_t blocks = (a.nvec + cols - 1) / cols;
@@ -406,7 +471,7 @@ lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic)
     const dim3 grid((uint32_t)blocks);
     const bool nt = (c->tune.nontemporal & 1) != 0;
     const bool ext = elastic || mask != c->all;
-    hipError_t e = ext ? launch_average<true>(a, grid, c->side, split, nt, bs1) : launch_average<false>(a, grid, c->side, split, nt, bs1);
+    hipError_t e = ext ? launch_average<true>(a, grid, stream, split, nt, bs1) : launch_average<false>(a, grid, stream, split, nt, bs1);
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "average launch failed: %s", hipGetErrorString(e));
     return LASGD_OK;
 }
@@ -423,9 +488,9 @@ lasgd_status check_ready_to_step(lasgd_ctx *c, float lr)
 void release(lasgd_ctx *c)
 {
     if (c->arena) (void)hipFree(c->arena);
-    for (Tile *t : c->tiles_by_vec)
-        if (t) (void)hipFree(t);
-    if (c->xptr) (void)hipFree(c->xptr);
+    for (const lasgd_ctx::Tables &t : c->tables_by_vec)
+        if (t.mem) (void)hipFree(t.mem);
+    if (c->records) (void)hipFree(c->records);
     if (c->evA) (void)hipEventDestroy(c->evA);
     if (c->evZ) (void)hipEventDestroy(c->evZ);
     delete c;
@@ -469,7 +534,6 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     c->ntotal = total;
     c->bound.assign((size_t)c->K, 0);
     c->h_xptr.assign((size_t)c->K * c->n_tensors, nullptr);
-    c->h_gptr.assign((size_t)c->K * c->n_tensors, nullptr);
     c->tune = default_tuning(*c);
 
 #define CREATE_HIP(call)                                                                       \
@@ -494,13 +558,12 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     c->s = c->v + (uint64_t)c->K * c->npad;
     c->z = c->s + (uint64_t)c->K * c->npad;
     c->x32 = bf16 ? c->z + c->npad : nullptr;
-    const size_t tab = (size_t)c->K * c->n_tensors * sizeof(void *);
-    CREATE_HIP(hipMalloc((void **)&c->xptr, 2 * tab));
-    c->gptr = c->xptr + (size_t)c->K * c->n_tensors;
-    CREATE_HIP(hipMemset(c->xptr, 0, 2 * tab));
+    const size_t tab = (size_t)c->K * c->n_tensors * sizeof(Record);
+    CREATE_HIP(hipMalloc((void **)&c->records, tab));
+    CREATE_HIP(hipMemset(c->records, 0, tab));
     CREATE_HIP(hipEventCreateWithFlags(&c->evA, hipEventDisableTiming));
     CREATE_HIP(hipEventCreateWithFlags(&c->evZ, hipEventDisableTiming));
-    lasgd_status st = upload_tiles(c, c->tune.vec);
+    lasgd_status st = upload_tables(c, c->tune.vec);
     if (st != LASGD_OK) {
         g_create_error = c->err;
         release(c);
@@ -536,12 +599,19 @@ lasgd_status lasgd_bind(lasgd_ctx *c, int32_t k, void *const *params, void *cons
         if (((uintptr_t)params[t] | (uintptr_t)grads[t]) & 15u)
             return fail(c, LASGD_ERR_INVALID, "buffer of tensor %d is not 16-byte aligned", t);
     }
+    std::vector<Record> recs;
+    try {
+        recs.resize((size_t)c->n_tensors);
+    } catch (...) {
+        return fail(c, LASGD_ERR_ALLOC, "out of host memory");
+    }
     LASGD_HIP(c, hipStreamSynchronize(c->main));
-    const size_t base = (size_t)k * c->n_tensors, bytes = (size_t)c->n_tensors * sizeof(void *);
-    LASGD_HIP(c, hipMemcpy(c->xptr + base, params, bytes, hipMemcpyHostToDevice));
-    LASGD_HIP(c, hipMemcpy(c->gptr + base, grads, bytes, hipMemcpyHostToDevice));
-    memcpy(&c->h_xptr[base], params, bytes);
-    memcpy(&c->h_gptr[base], grads, bytes);
+    const size_t base = (size_t)k * c->n_tensors;
+    for (size_t t = 0; t < recs.size(); ++t)
+        recs[t] = Record{(uint64_t)(uintptr_t)params[t], (uint64_t)(uintptr_t)grads[t], (uint32_t)(c->aoff[t] / kArenaAlign),
+                         (uint32_t)c->numel[t], c->wd[t], 0u};
+    LASGD_HIP(c, hipMemcpy(c->records + base, recs.data(), recs.size() * sizeof(Record), hipMemcpyHostToDevice));
+    memcpy(&c->h_xptr[base], params, recs.size() * sizeof(void *));
     if (!c->bound[(size_t)k]) {
         c->bound[(size_t)k] = 1;
         ++c->n_bound;
@@ -586,11 +656,14 @@ static bool fill_ext(const lasgd_ctx *c, ExtArgs &x, const float *lr, uint64_t s
     x.step_mask = step_mask;
     x.merge_mask = merge_mask;
     x.alpha = c->alpha;
+    uint32_t n = 0;
+    for (uint64_t rest = step_mask | merge_mask; rest; rest &= rest - 1ull, ++n)
+        x.who[n >> 2] |= (uint32_t)__builtin_ctzll(rest) << ((n & 3u) * 8u);
     bool uniform = true;
     float first = 0.f;
     bool have = false;
-    for (int k = 0; k < 64; ++k) {
-        const bool in = k < c->K && ((step_mask >> k) & 1ull) && lr;
+    for (int k = 0; k < c->K; ++k) {        // the entries beyond K stay zero, as the caller made them
+        const bool in = ((step_mask >> k) & 1ull) && lr;
         x.neg_lr_k[k] = in ? -lr[k] : 0.f;
         if (in) {
             if (!have) { first = lr[k]; have = true; }
@@ -663,7 +736,7 @@ static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "poison launch failed: %s", hipGetErrorString(e));
     }
-    st = enqueue_average(c, mask, elastic);
+    st = enqueue_average(c, mask, elastic, c->side, c->tune.avg_split);
     if (st != LASGD_OK) return st;
     // from here on the side stream reads s and writes z: the state says so even if the event below fails
     c->pending_mask = mask;
@@ -817,15 +890,28 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         return fail(c, LASGD_ERR_STATE, "the pending average is partial or partly merged: use lasgd_step_merge_ex and lasgd_average_ex");
     if (c->alpha != 1.f || c->beta != 1.f)
         return fail(c, LASGD_ERR_STATE, "elastic coefficients are set: use lasgd_step_merge and lasgd_average");
-    ApplyArgs a{};
-    fill_common(c, a);
-    a.neg_lr = -lr;
-    a.resnap = 1;
-    const GroupShape g = group_shape(c, 1);
     const bool captured = is_capturing(c->main);
-    if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
-    hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, c->tune.nontemporal);
-    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    if (c->K > 12 && (c->tune.nontemporal & 3) && c->tune.group_r <= 0) {
+        // Streaming from 13 replicas on, workgroups that hold all replicas of a tile lose more to their shape than the
+        // second pass over s costs: update, then the in-order mean.  us, one kernel / two: MobileNetV2 K = 14 248 / 247,
+        // K = 16 295 / 281, K = 24 452 / 415; ResNet-18 bf16 K = 24 1453 / 1404; but K = 12 686 / 705.
+        ApplyPlan p;
+        if ((st = plan_apply(c, p, OP_STEP_MERGE, lr, 1)) != LASGD_OK) return st;
+        if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
+        if ((st = launch_apply(c, p)) != LASGD_OK) return st;
+        c->snap_mask = c->all;
+        c->pending_mask = 0;
+        if ((st = enqueue_average(c, c->all, false, c->main, 1)) != LASGD_OK) return st;
+    } else {
+        ApplyArgs a{};
+        fill_common(c, a);
+        a.neg_lr = -lr;
+        a.resnap = 1;
+        const GroupShape g = group_shape(c, 1);
+        if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
+        hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, c->tune.nontemporal);
+        if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    }
     // every replica has merged and re-sent, and the mean of the sent models is (being) written to z
     // on the main stream: the same state as after lasgd_step_merge(lr, 1) + lasgd_average
     c->snap_mask = c->all;
@@ -913,7 +999,7 @@ static lasgd_status set_tuning_impl(lasgd_ctx *c, const lasgd_tuning *t)
     lasgd_status st = lasgd_sync(c);
     if (st != LASGD_OK) return st;
     if (n.vec != c->tune.vec) {
-        st = upload_tiles(c, n.vec);
+        st = upload_tables(c, n.vec);
         if (st != LASGD_OK) return st;
     }
     c->tune = n;
@@ -956,7 +1042,7 @@ constexpr int64_t kStaticMaxN = LASGD_STATIC_MAX_N;
 
 namespace {
 
-template <int NT> hipError_t launch_flat_update(const FlatArgs &a, uint32_t blocks, hipStream_t st)
+template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hipStream_t st)
 {
     // One wave per replica while a workgroup can hold that many (16), then two or four replicas a wave.  Measured with
     // 1, 2, 4 replicas a wave at n = 12e6: K = 4 125, 129, 131 us, K = 8 258, 269, 273, K = 16 546, 562, 565.  Two replicas
@@ -966,7 +1052,8 @@ template <int NT> hipError_t launch_flat_update(const FlatArgs &a, uint32_t bloc
     // a wave is ahead again (n = 1,000,003 31.6 against 34.2).
     uint32_t R = a.K <= kGroupWaves ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
     if (NT == 0 && a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > 8192u) R = 2u;
-    const dim3 bs(64u * ((a.K + R - 1u) / R));
+    a.W = (a.K + R - 1u) / R;
+    const dim3 bs(64u * a.W);
     const size_t lds = (size_t)a.K * 256u * sizeof(float);
     if (R == 1u) hipLaunchKernelGGL((flat_update_kernel<1, NT>), dim3(blocks), bs, lds, st, a);
     else if (R == 2u) hipLaunchKernelGGL((flat_update_kernel<2, NT>), dim3(blocks), bs, lds, st, a);

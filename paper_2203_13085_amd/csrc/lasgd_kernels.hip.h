@@ -21,47 +21,77 @@ namespace lasgd {
 struct Tile {
     uint64_t toff;     // first element, relative to the tensor's start
     uint64_t aoff;     // first element, relative to a replica's start in the library arenas
-    uint32_t tensor;   // index into the pointer tables
     uint32_t count;    // elements in this tile (<= 256*VEC; smaller only at a tensor's end)
     float wd;          // the tensor's weight decay
+};
+
+// What the kernels look up: one 16-byte record per tensor and one pointer pair per
+// (replica, tensor).  A tile's tensor is named by its block of 64 tiles; the top bit
+// says that more tensors start inside the block, and then the tile is compared with
+// the following tensors' first tiles, sixteen at a time.
+//
+// The tables are read through the scalar cache.  They are per block and per tensor
+// and not per tile (161 tensors, 10^5 tiles: 6 KB of blocks, 2.5 KB each of records
+// and pointers of one replica), so a few hundred waves in a row find them there, and
+// a scalar hit does not queue behind the streaming loads of other waves as a vector
+// load does.  A record per tile, read through the vector path, made every wave wait twice
+// for the loaded memory system before its first data load: at 24 waves a CU that cost
+// 13 % of a local step, and kernels in the memory-side cache 4 % (flat list of 2^20
+// elements, K = 4, update cycle 42.0 -> 40.5 us).  With the short wait fewer waves do,
+// and then the kernels can be paced (pace_lds in the host code).
+constexpr uint32_t kBlockShift = 6;
+constexpr uint32_t kMoreInBlock = 0x80000000u;
+constexpr uint32_t kProbe = 16;
+struct Record {        // one per (replica, tensor): everything a wave needs, in one load
+    uint64_t x, g;     // device addresses of the caller's parameters and gradient
+    uint32_t arow;     // arena offset in units of 256 elements
+    uint32_t numel;
+    float wd;
     uint32_t pad_;
 };
-static_assert(sizeof(Tile) == 32, "tile descriptors are two 16-byte loads");
-
-// The descriptor and pointer tables are read with wave-uniform indices.  The
-// compiler fetches them through the vector memory path (all lanes, one
-// address).  Forcing scalar loads instead (constant address space) was
-// measured 4.5 % slower on MI355X: every descriptor is used once, so each
-// scalar load misses the small scalar cache, while the vector L1 keeps more
-// of these misses in flight.
-__device__ __forceinline__ Tile load_tile(const Tile *p) { return *p; }
-__device__ __forceinline__ char *load_ptr(void *const *table, size_t i) { return static_cast<char *>(table[i]); }
+static_assert(sizeof(Record) == 32, "one 32-byte scalar load");
 
 enum Op : int { OP_STEP = 0, OP_MERGE = 1, OP_STEP_MERGE = 2, OP_SNAPSHOT = 3, OP_INIT = 4 };
 
+// n / d for n < 2^31 by a multiplication (Granlund and Montgomery, "Division by invariant integers using
+// multiplication", 1994): with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1 (2^31 for a power of two),
+// floor(n * m / 2^(31+l)) is exact, and m fits 32 bits.
+struct FastDiv {
+    uint32_t m, shift;
+};
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv d)
+{
+    return (uint32_t)(((uint64_t)n * d.m) >> d.shift);
+}
+
 struct ApplyArgs {
-    const Tile *tiles;
-    void *const *xptr;      // [K * n_tensors] caller's parameters (fp32 or bf16)
-    void *const *gptr;      // [K * n_tensors] caller's gradients  (fp32 or bf16)
+    const uint32_t *blocks; // [ceil(ntiles / 64)] tensor of each block's first tile, kMoreInBlock if others follow in it
+    const uint32_t *tile0;  // [n_tensors + 16] the tensors' first tiles, then 0xffffffff, which no tile reaches
+    const Record *records;  // [K * n_tensors]
     float *x32;             // bf16 storage only: fp32 master, [K][npad]
     float *v;               // momentum,     [K][npad]
     float *s;               // sent models,  [K][npad]
     float *z;               // mean,         [npad] (written only by the fused step+update+mean kernel)
     uint64_t npad;          // elements per replica in the arenas
     uint32_t ntiles, K, n_tensors;
+    uint32_t kcount;        // replicas that take part (K, or fewer in the extended calls)
     uint32_t kper;          // replicas a wave handles back to back
-    uint32_t kgroups;       // ceil(K / kper)
+    uint32_t kgroups;       // ceil(kcount / kper)
     uint32_t nitems;        // ntiles * kgroups
     float neg_lr, mu;
     int32_t nesterov, resnap;
+    uint32_t tile_elems;    // 256 * VEC
+    uint32_t wpb, nwaves;   // waves per workgroup, and in the grid (the replica-group kernels: workgroups in the grid)
     uint32_t chunk;         // item order, see apply_kernel
     uint32_t full_items;    // (ntiles / chunk) * chunk * kgroups
     uint32_t tail_first;    // first tile of the last, shorter chunk
     uint32_t tail_chunk;    // its length (>= 1 even when unused)
     uint32_t tail_stride;   // items per replica group in the last chunk: tail_chunk rounded up so that every
                             // group's pass starts on the same XCD; the items in between do nothing
+    FastDiv by_per, by_chunk, by_stride;   // division by chunk * kgroups, chunk, tail_stride
     // the replica-group kernels finish a mean over all K replicas themselves
     int32_t use_mul;        // K is a power of two: multiply by the exact reciprocal
+    uint32_t delay;         // sleeps of 512 clocks before a wave's first load
     double inv_k, k_as_double;
 };
 
@@ -73,6 +103,8 @@ struct ExtArgs {
     uint64_t merge_mask;    // bit k: replica k takes the global update
     float alpha;            // 1 = step 9a of Algorithm 1 exactly
     float neg_lr_k[64];     // -eta per replica
+    uint32_t who[16];       // the replicas of either mask, ascending, four to a word: only they get work items (a replica
+                            // that sits the call out used to get waves that looked it up and left)
 };
 
 // ---- 128-bit / 64-bit accesses, optionally with the streaming hint --------
@@ -90,6 +122,60 @@ template <class T> __device__ __forceinline__ const LASGD_GLOBAL_AS T *as_global
 template <class T> __device__ __forceinline__ LASGD_GLOBAL_AS T *as_global(void *p)
 {
     return reinterpret_cast<LASGD_GLOBAL_AS T *>(reinterpret_cast<uintptr_t>(p));
+}
+
+#define LASGD_CONST_AS __attribute__((address_space(4)))
+template <class T> __device__ __forceinline__ const LASGD_CONST_AS T *as_const(const T *p)
+{
+    return reinterpret_cast<const LASGD_CONST_AS T *>(reinterpret_cast<uintptr_t>(p));
+}
+
+typedef uint32_t u32x16_t __attribute__((ext_vector_type(16), aligned(4)));
+
+// The tensor that tile `tile` (wave-uniform) belongs to.
+__device__ __forceinline__ uint32_t tensor_of(const ApplyArgs &a, uint32_t tile)
+{
+    uint32_t t = 0;
+    if (a.n_tensors > 1u) {
+        t = as_const(a.blocks)[tile >> kBlockShift];
+        if (t & kMoreInBlock) {
+            t &= ~kMoreInBlock;
+            uint32_t below;              // how many of the next sixteen tensors start at or before the tile
+            do {
+                const u32x16_t n = *reinterpret_cast<const LASGD_CONST_AS u32x16_t *>(as_const(a.tile0) + t + 1u);
+                below = 0;
+#define LASGD_BELOW(n) "s_cmp_le_u32 %" #n ", %1\n\ts_addc_u32 %0, %0, 0\n\t"
+                asm(LASGD_BELOW(2) LASGD_BELOW(3) LASGD_BELOW(4) LASGD_BELOW(5) LASGD_BELOW(6) LASGD_BELOW(7)
+                    LASGD_BELOW(8) LASGD_BELOW(9) LASGD_BELOW(10) LASGD_BELOW(11) LASGD_BELOW(12) LASGD_BELOW(13)
+                    LASGD_BELOW(14) LASGD_BELOW(15) LASGD_BELOW(16) LASGD_BELOW(17)
+                    : "+&s"(below)
+                    : "s"(tile), "s"(n[0]), "s"(n[1]), "s"(n[2]), "s"(n[3]), "s"(n[4]), "s"(n[5]), "s"(n[6]), "s"(n[7]),
+                      "s"(n[8]), "s"(n[9]), "s"(n[10]), "s"(n[11]), "s"(n[12]), "s"(n[13]), "s"(n[14]), "s"(n[15])
+                    : "scc");
+#undef LASGD_BELOW
+                t += below;
+            } while (below == kProbe);
+        }
+    }
+    return t;
+}
+__device__ __forceinline__ Record load_record(const ApplyArgs &a, uint32_t k, uint32_t tensor)
+{
+    const LASGD_CONST_AS Record *r = as_const(a.records) + ((size_t)k * a.n_tensors + tensor);
+    return Record{r->x, r->g, r->arow, r->numel, r->wd, 0u};
+}
+// Where the tile lies in its tensor and in the arenas.  Tiles of 256 elements are the arenas' rows.
+__device__ __forceinline__ Tile locate(const ApplyArgs &a, const Record &rec, uint32_t tile, uint32_t tensor, uint32_t tile_elems)
+{
+    const uint32_t first = tile_elems == 256u ? rec.arow : as_const(a.tile0)[tensor];
+    const uint32_t off = (tile - first) * tile_elems;
+    const uint32_t left = rec.numel - off;
+    Tile r;
+    r.toff = off;
+    r.aoff = (uint64_t)rec.arow * 256u + off;
+    r.count = left < tile_elems ? left : tile_elems;
+    r.wd = rec.wd;
+    return r;
 }
 
 template <int NT> __device__ __forceinline__ float4 ld4(const float *p)
@@ -185,10 +271,22 @@ __device__ __forceinline__ float compv(const float4 &a, int c)
     return c == 0 ? a.x : c == 1 ? a.y : c == 2 ? a.z : a.w;
 }
 
-// Apply one operation to VEC rows of one replica's tile.  `rows` is the number
-// of full 256-element rows (VEC on the fast path); `count` bounds the ragged
+// How many of the four elements from e0 on a tile of `count` elements has.
+template <bool FULL> __device__ __forceinline__ uint32_t lane_elems(uint32_t e0, uint32_t count)
+{
+    return FULL ? 4u : e0 >= count ? 0u : count - e0 < 4u ? count - e0 : 4u;
+}
+
+// Apply one operation to VEC rows of one replica's tile.  `count` bounds the ragged
 // path.  x/g point at the tile's first element in the caller's buffers
 // (storage dtype), xm/v/s at the tile's first element in the arenas.
+//
+// A ragged tile (the last of a tensor) takes the same 128-bit accesses in the lanes
+// that have all four elements, and only the one lane that a tensor's odd end leaves
+// with one to three goes element by element: all its loads before its first store,
+// as everywhere, so that the wave waits once for memory.
+// Small ragged list, K = 3: snapshot 4.0 -> 3.1 us,
+// local step 3.4 -> 3.2.
 template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT>
 __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const void *gu, float *xm,
                                            float *v, float *s, const float4 (&zt)[VEC], float wd,
@@ -206,31 +304,62 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     const uint16_t *g16 = static_cast<const uint16_t *>(gu);
     const bool write_s = (OP == OP_SNAPSHOT) || (NEED_S && a.resnap);
 
-    if constexpr (FULL) {
-        float4 x[VEC], vv[VEC], g[VEC], ss[VEC];
-        // all loads first: up to 4*VEC independent 128-bit loads in flight per lane
+    if constexpr (OP == OP_SNAPSHOT && !FULL) {          // a copy
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            const uint32_t e = j * 256u + lane * 4u;
+            const uint32_t e = j * 256u + lane * 4u, n = lane_elems<FULL>(e, count);
+            if (n == 4u) st4<NT>(s + e, ld4<NT>(xf + e));
+            else
+                for (uint32_t i = 0; i < n; ++i) *as_global<float>(s + e + i) = *as_global<float>(xf + e + i);
+        }
+        return;
+    }
+    float4 x[VEC], vv[VEC], g[VEC], ss[VEC];
+    if constexpr (!FULL) {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) x[j] = vv[j] = g[j] = ss[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    // all loads first: up to 4*VEC independent 128-bit loads in flight per lane
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        const uint32_t e = j * 256u + lane * 4u;
+        if (FULL || lane_elems<FULL>(e, count) == 4u) {
             if constexpr (NEED_G) g[j] = BF16 ? widen4(ld2<NT>(g16 + e)) : ld4<NT>(gf + e);
             if constexpr (NEED_X) x[j] = ld4<NT>(xf + e);
             if constexpr (OP == OP_INIT) x[j] = widen4(ld2<NT>(x16 + e));
             if constexpr (NEED_V) vv[j] = ld4<NT>(v + e);
             if constexpr (NEED_S) ss[j] = ld4<NT>(s + e);
         }
+    }
+    if constexpr (!FULL) {
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            const uint32_t e = j * 256u + lane * 4u;
-            if constexpr (NEED_G)
-                LASGD_FOR4(step_elem(comp(x[j], c), comp(vv[j], c), compv(g[j], c), wd, a.mu,
-                                     neg_lr, a.nesterov);)
-            if constexpr (NEED_S) {
-                if constexpr (EXT)
-                    LASGD_FOR4(comp(x[j], c) = merge_elem_elastic(compv(x[j], c), compv(ss[j], c), compv(zt[j], c), alpha);)
-                else
-                    LASGD_FOR4(comp(x[j], c) = merge_elem(compv(x[j], c), compv(ss[j], c), compv(zt[j], c));)
+            const uint32_t e = j * 256u + lane * 4u, n = lane_elems<FULL>(e, count);
+            if (n - 1u < 3u) {
+                LASGD_FOR4(if (c < 3 && (uint32_t)c < n) {
+                    if constexpr (NEED_G) comp(g[j], c) = BF16 ? bf16_widen(*as_global<uint16_t>(g16 + e + c)) : *as_global<float>(gf + e + c);
+                    if constexpr (NEED_X) comp(x[j], c) = *as_global<float>(xf + e + c);
+                    if constexpr (OP == OP_INIT) comp(x[j], c) = bf16_widen(*as_global<uint16_t>(x16 + e + c));
+                    if constexpr (NEED_V) comp(vv[j], c) = *as_global<float>(v + e + c);
+                    if constexpr (NEED_S) comp(ss[j], c) = *as_global<float>(s + e + c);
+                })
             }
-            if constexpr (OP == OP_INIT) vv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        const uint32_t e = j * 256u + lane * 4u, n = lane_elems<FULL>(e, count);
+        if constexpr (NEED_G)
+            LASGD_FOR4(step_elem(comp(x[j], c), comp(vv[j], c), compv(g[j], c), wd, a.mu,
+                                 neg_lr, a.nesterov);)
+        if constexpr (NEED_S) {
+            if constexpr (EXT)
+                LASGD_FOR4(comp(x[j], c) = merge_elem_elastic(compv(x[j], c), compv(ss[j], c), compv(zt[j], c), alpha);)
+            else
+                LASGD_FOR4(comp(x[j], c) = merge_elem(compv(x[j], c), compv(ss[j], c), compv(zt[j], c));)
+        }
+        if constexpr (OP == OP_INIT) vv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (FULL || n == 4u) {
             if constexpr (WRITE_V) st4<NT>(v + e, vv[j]);
             if constexpr (WRITE_X) {
                 st4<NT>(xf + e, x[j]);
@@ -238,35 +367,28 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
             }
             if (write_s) st4<NT>(s + e, x[j]);
         }
-    } else {
-        // ragged tile: same arithmetic, element by element where a 128-bit
-        // access would cross the end of the tensor
-        // (fully unrolled over j so that the z registers are never indexed at run time)
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            const uint32_t e0 = j * 256u + lane * 4u;
-            const uint32_t n = (e0 >= count) ? 0u : (count - e0 < 4u) ? count - e0 : 4u;
-            for (uint32_t i = 0; i < n; ++i) {
-                const uint32_t e = e0 + i;
-                float xe = 0.f, ve = 0.f, ge = 0.f, se = 0.f;
-                if constexpr (NEED_G) ge = BF16 ? bf16_widen(g16[e]) : gf[e];
-                if constexpr (NEED_X) xe = xf[e];
-                if constexpr (OP == OP_INIT) xe = bf16_widen(x16[e]);
-                if constexpr (NEED_V) ve = v[e];
-                if constexpr (NEED_S) se = s[e];
-                if constexpr (NEED_G) step_elem(xe, ve, ge, wd, a.mu, neg_lr, a.nesterov);
-                if constexpr (NEED_S)
-                    xe = EXT ? merge_elem_elastic(xe, se, compv(zt[j], (int)i), alpha)
-                             : merge_elem(xe, se, compv(zt[j], (int)i));
-                if constexpr (WRITE_V) v[e] = ve;
-                if constexpr (WRITE_X) {
-                    xf[e] = xe;
-                    if constexpr (BF16 && OP != OP_INIT) x16[e] = (uint16_t)bf16_round(xe);
-                }
-                if (write_s) s[e] = xe;
+        if constexpr (!FULL) {
+            if (n - 1u < 3u) {
+                LASGD_FOR4(if (c < 3 && (uint32_t)c < n) {
+                    if constexpr (WRITE_V) *as_global<float>(v + e + c) = compv(vv[j], c);
+                    if constexpr (WRITE_X) {
+                        *as_global<float>(xf + e + c) = compv(x[j], c);
+                        if constexpr (BF16 && OP != OP_INIT) *as_global<uint16_t>(x16 + e + c) = (uint16_t)bf16_round(compv(x[j], c));
+                    }
+                    if (write_s) *as_global<float>(s + e + c) = compv(x[j], c);
+                })
             }
         }
     }
+}
+
+// The j-th replica that takes part; when all do, without the look into the list.
+template <bool EXT> __device__ __forceinline__ uint32_t replica_at(const ApplyArgs &a, const ExtArgs *xa, uint32_t j)
+{
+    if constexpr (EXT) {
+        if (a.kcount != a.K) return (xa->who[j >> 2] >> ((j & 3u) * 8u)) & 0xffu;
+    }
+    return j;
 }
 
 // Multi-tensor apply.  Work item = (tile, group of kper replicas); one wave
@@ -278,10 +400,9 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
 {
     constexpr bool NEED_Z = (OP == OP_MERGE || OP == OP_STEP_MERGE);
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wpb = blockDim.x >> 6;                  // independent waves per workgroup
-    const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + (threadIdx.x >> 6));
-    const uint32_t nwaves = gridDim.x * wpb;
-    for (uint32_t item = wave0; item < a.nitems; item += nwaves) {
+    // the shape travels in the arguments: reading it from the dispatch would be a vector load before everything else
+    const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.wpb + (threadIdx.x >> 6));
+    for (uint32_t item = wave0; item < a.nitems; item += a.nwaves) {
         // Item order: tiles are taken in chunks of a.chunk; inside a chunk the items run
         // replica group by replica group, so that each replica's arrays are swept in
         // contiguous runs of a.chunk tiles while the chunk's z tiles are reused K times
@@ -293,51 +414,46 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
         // padded with idle items to such a multiple for the same reason.
         uint32_t tile, kg;
         if (item < a.full_items) {
-            const uint32_t per = a.chunk * a.kgroups;
-            const uint32_t ch = item / per;
-            const uint32_t r = item - ch * per;
-            kg = r / a.chunk;
+            const uint32_t ch = fast_div(item, a.by_per);
+            const uint32_t r = item - ch * (a.chunk * a.kgroups);
+            kg = fast_div(r, a.by_chunk);
             tile = ch * a.chunk + (r - kg * a.chunk);
         } else {
             const uint32_t r = item - a.full_items;
-            kg = r / a.tail_stride;
+            kg = fast_div(r, a.by_stride);
             const uint32_t i = r - kg * a.tail_stride;
             if (i >= a.tail_chunk) continue;                    // padding item
             tile = a.tail_first + i;
         }
-        const Tile t = load_tile(a.tiles + tile);
+        const uint32_t k0 = kg * a.kper;
+        const uint32_t k1 = (k0 + a.kper < a.kcount) ? k0 + a.kper : a.kcount;
+        const uint32_t tensor = tensor_of(a, tile);
+        Record rec = load_record(a, replica_at<EXT>(a, xa, k0), tensor);
+        const Tile t = locate(a, rec, tile, tensor, 256u * VEC);
         const bool full = (t.count == 256u * VEC);
         float4 zt[VEC];
         if constexpr (NEED_Z) {
+            // the arenas are padded to whole rows: a full row of z is there even where the tensor ends inside it
             const float *zp = a.z + t.aoff;
-            if (full) {
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) zt[j] = *reinterpret_cast<const float4 *>(zp + j * 256u + lane * 4u);
-            } else {
-#pragma unroll
-                for (int j = 0; j < VEC; ++j) {
-                    const uint32_t e0 = j * 256u + lane * 4u;
-                    zt[j].x = (e0 + 0u < t.count) ? zp[e0 + 0u] : 0.f;
-                    zt[j].y = (e0 + 1u < t.count) ? zp[e0 + 1u] : 0.f;
-                    zt[j].z = (e0 + 2u < t.count) ? zp[e0 + 2u] : 0.f;
-                    zt[j].w = (e0 + 3u < t.count) ? zp[e0 + 3u] : 0.f;
-                }
+            for (int j = 0; j < VEC; ++j) {
+                const uint32_t e = j * 256u + lane * 4u;
+                zt[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j == 0 || j * 256u < t.count) zt[j] = ld4<0>(zp + e);
             }
         }
-        const uint32_t k0 = kg * a.kper;
-        const uint32_t k1 = (k0 + a.kper < a.K) ? k0 + a.kper : a.K;
-        for (uint32_t k = k0; k < k1; ++k) {
-            const size_t pi = (size_t)k * a.n_tensors + t.tensor;
+        for (uint32_t j = k0;;) {
+            const uint32_t k = replica_at<EXT>(a, xa, j);
             const size_t esz = BF16 ? 2 : 4;
-            char *xu = load_ptr(a.xptr, pi) + t.toff * esz;
+            char *xu = reinterpret_cast<char *>(rec.x) + t.toff * esz;
             const char *gu = nullptr;
             if constexpr (OP == OP_STEP || OP == OP_STEP_MERGE)
-                gu = load_ptr(a.gptr, pi) + t.toff * esz;
+                gu = reinterpret_cast<const char *>(rec.g) + t.toff * esz;
             const size_t ao = (size_t)k * a.npad + t.aoff;
             float *xm = BF16 ? a.x32 + ao : nullptr;
 #define LASGD_TILE(OPX, NLR, AL)                                                                             \
     do {                                                                                                     \
-        if (full) apply_tile<VEC, OPX, BF16, NT, true, EXT>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
+        if (__builtin_expect(full, 1)) apply_tile<VEC, OPX, BF16, NT, true, EXT>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
         else apply_tile<VEC, OPX, BF16, NT, false, EXT>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL);     \
     } while (0)
             if constexpr (!EXT) {
@@ -358,6 +474,8 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
                 }
             }
 #undef LASGD_TILE
+            if (++j == k1) break;
+            rec = load_record(a, replica_at<EXT>(a, xa, j), tensor);
         }
     }
 }
@@ -561,6 +679,33 @@ template <int NT, bool FULL> __device__ __forceinline__ void row_st16(uint16_t *
     if (n > 2u) p[e0 + 2u] = (uint16_t)bf16_round(a.z);
 }
 
+// The mean of one row over its K values per element, which lie in lds[K][256]; every wave gets its lanes' columns.
+// Up to K = 8 every wave sums them itself, which saves a barrier; beyond, up to four waves finish one column per
+// thread and turn: only that thread reads the column, so the mean may replace replica 0's value in it.  SGD-AR mix,
+// bare probe, every wave / shared: K = 4 6.12 / 6.01 TB/s, K = 8 6.08 / 6.01, K = 12 6.02 / 6.09, K = 16 5.51 / 5.89.
+template <class MEAN>
+__device__ __forceinline__ float4 row_mean(float *lds, uint32_t K, uint32_t W, uint32_t lane, MEAN mean_of)
+{
+    if (K <= 8u) {
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+        for (uint32_t k = 0; k < K; ++k) {
+            const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + lane * 4u);
+            LASGD_ACC4(q);
+        }
+        return make_float4(mean_of(a0), mean_of(a1), mean_of(a2), mean_of(a3));
+    }
+    const uint32_t fin = (W < 4u ? W : 4u) * 64u;
+    if (threadIdx.x < fin) {
+        for (uint32_t c = threadIdx.x; c < 256u; c += fin) {
+            double acc = 0.0;
+            for (uint32_t k = 0; k < K; ++k) acc += (double)lds[(size_t)k * 256u + c];
+            lds[c] = mean_of(acc);
+        }
+    }
+    __syncthreads();
+    return *reinterpret_cast<const float4 *>(lds + lane * 4u);
+}
+
 __device__ __forceinline__ float group_mean_of(double acc, const ApplyArgs &a)
 {
     return (float)(a.use_mul ? acc * a.inv_k : acc / a.k_as_double);
@@ -574,19 +719,23 @@ template <bool BF16> struct ReplicaTile {
     const void *g;
 };
 template <bool BF16>
-__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, uint32_t k)
+__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, const Record &rec, uint32_t k)
 {
     constexpr size_t ESZ = BF16 ? 2 : 4;
-    const size_t pi = (size_t)k * a.n_tensors + t.tensor;
     const size_t ao = (size_t)k * a.npad + t.aoff;
-    char *xu = load_ptr(a.xptr, pi) + t.toff * ESZ;
+    char *xu = reinterpret_cast<char *>(rec.x) + t.toff * ESZ;
     ReplicaTile<BF16> r;
     r.xf = BF16 ? a.x32 + ao : reinterpret_cast<float *>(xu);
     r.x16 = reinterpret_cast<uint16_t *>(xu);
     r.v = a.v + ao;
     r.s = a.s + ao;
-    r.g = load_ptr(a.gptr, pi) + t.toff * ESZ;
+    r.g = reinterpret_cast<const char *>(rec.g) + t.toff * ESZ;
     return r;
+}
+template <bool BF16>
+__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, uint32_t k, uint32_t tensor)
+{
+    return replica_tile<BF16>(a, t, load_record(a, k, tensor), k);
 }
 template <bool BF16, int NT, bool FULL>
 __device__ __forceinline__ float4 row_ld_grad(const void *g, uint32_t e0, uint32_t n)
@@ -604,7 +753,7 @@ __device__ __forceinline__ float4 row_ld_grad(const void *g, uint32_t e0, uint32
 // every replica takes the local update with that mean gradient.  Same 20 bytes
 // per replica-parameter as a local step.
 template <int R, bool BF16, int NT, bool FULL>
-__device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, float *lds, uint32_t row,
+__device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
                                            uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
@@ -619,7 +768,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, fl
         for (int r = 0; r < R; ++r) {
             const uint32_t kw = w + (uint32_t)r * W;
             mine[r] = kw < a.K;
-            rt[r] = replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u);
+            rt[r] = r == 0 ? replica_tile<BF16>(a, t, rec0, kw) : replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u, tensor);
             g[r] = row_ld_grad<BF16, NT, FULL>(rt[r].g, e0, n);
             x[r] = row_ld<NT, FULL>(rt[r].xf, e0, n);
             v[r] = row_ld<NT, FULL>(rt[r].v, e0, n);
@@ -634,7 +783,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, fl
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
-            const ReplicaTile<BF16> q = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u);
+            const ReplicaTile<BF16> q = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
             g[r] = row_ld_grad<BF16, NT, FULL>(q.g, e0, n);
         }
 #pragma unroll
@@ -642,14 +791,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, fl
             if (kw[r] < a.K) *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = g[r];
     }
     __syncthreads();
-    // every wave sums the row itself: handing the sum to a few waves and passing the result
-    // round through LDS costs a second barrier and measured slower than the repeated fp64 adds
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    for (uint32_t k = 0; k < a.K; ++k) {
-        const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + lane * 4u);
-        LASGD_ACC4(q);
-    }
-    const float4 gbar = make_float4(group_mean_of(a0, a), group_mean_of(a1, a), group_mean_of(a2, a), group_mean_of(a3, a));
+    const float4 gbar = row_mean(lds, a.K, W, lane, [&a](double acc) { return group_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(step_elem(comp(x[r], c), comp(v[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
@@ -667,7 +809,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, fl
         for (int r = 0; r < R; ++r) {
             const uint32_t kw = w + (p * R + (uint32_t)r) * W;
             ok[r] = kw < a.K;
-            q[r] = replica_tile<BF16>(a, t, ok[r] ? kw : a.K - 1u);
+            q[r] = replica_tile<BF16>(a, t, ok[r] ? kw : a.K - 1u, tensor);
             xx[r] = row_ld<NT, FULL>(q[r].xf, e0, n);
             vv[r] = row_ld<NT, FULL>(q[r].v, e0, n);
         }
@@ -681,7 +823,6 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, fl
             }
         }
     }
-    __syncthreads();                 // the next row reuses the LDS buffer
 }
 
 template <int R, bool BF16, int NT>
@@ -690,13 +831,18 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
     extern __shared__ float lds[];                        // [K][256]
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t W = blockDim.x >> 6;
-    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
-        const Tile t = load_tile(a.tiles + tile);
+    const uint32_t W = a.wpb;
+    bool again = false;
+    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
+        const uint32_t tensor = tensor_of(a, tile);
+        const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
+        const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
         const uint32_t rows = (t.count + 255u) >> 8;
         for (uint32_t row = 0; row < rows; ++row) {
-            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true>(a, t, lds, row, w, W, passes, lane);
-            else sgd_ar_row<R, BF16, NT, false>(a, t, lds, row, w, W, passes, lane);
+            if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
+            again = true;
+            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            else sgd_ar_row<R, BF16, NT, false>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
     }
 }
@@ -708,7 +854,7 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
 // tile's z, and all its waves have used the old values before the barrier.
 // Same roundings as step_merge followed by the in-order mean.
 template <int R, bool BF16, int NT, bool FULL>
-__device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Tile &t, float *lds, uint32_t row,
+__device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
                                                     uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
@@ -721,7 +867,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
-            q[r] = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u);
+            q[r] = r == 0 && p == 0u ? replica_tile<BF16>(a, t, rec0, kw[r]) : replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
             g[r] = row_ld_grad<BF16, NT, FULL>(q[r].g, e0, n);
             x[r] = row_ld<NT, FULL>(q[r].xf, e0, n);
             v[r] = row_ld<NT, FULL>(q[r].v, e0, n);
@@ -753,7 +899,6 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
             }
         }
     }
-    __syncthreads();
 }
 
 template <int R, bool BF16, int NT>
@@ -762,13 +907,19 @@ __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a
     extern __shared__ float lds[];                        // [K][256]
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t W = blockDim.x >> 6;
-    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
-        const Tile t = load_tile(a.tiles + tile);
+    const uint32_t W = a.wpb;
+    for (uint32_t i = 0; i < a.delay; ++i) __builtin_amdgcn_s_sleep(8);
+    bool again = false;
+    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
+        const uint32_t tensor = tensor_of(a, tile);
+        const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
+        const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
         const uint32_t rows = (t.count + 255u) >> 8;
         for (uint32_t row = 0; row < rows; ++row) {
-            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true>(a, t, lds, row, w, W, passes, lane);
-            else step_merge_mean_row<R, BF16, NT, false>(a, t, lds, row, w, W, passes, lane);
+            if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
+            again = true;
+            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            else step_merge_mean_row<R, BF16, NT, false>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
     }
 }
@@ -797,7 +948,7 @@ struct FlatArgs {
     float *x[64];       // local models, n elements each
     float *s[64];       // sent models
     uint64_t n;
-    uint32_t K;
+    uint32_t K, W;      // replicas; waves per workgroup
     int32_t use_mul;    // K is a power of two: multiply by the exact reciprocal
     double inv_k, k_as_double;
     int32_t resnap;
@@ -830,29 +981,7 @@ __device__ __forceinline__ void flat_update_row(const FlatArgs &a, float *lds, u
     for (int r = 0; r < R; ++r)
         if (mine[r]) *reinterpret_cast<float4 *>(lds + (size_t)(w + (uint32_t)r * W) * 256u + e0) = ss[r];
     __syncthreads();
-    float4 z;
-    if (a.K <= 8u) {
-        // few terms: every wave sums its columns itself, which saves the second barrier
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (uint32_t k = 0; k < a.K; ++k) {
-            const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + e0);
-            LASGD_ACC4(q);
-        }
-        z = make_float4(flat_mean_of(a0, a), flat_mean_of(a1, a), flat_mean_of(a2, a), flat_mean_of(a3, a));
-    } else {
-        // up to four waves finish one column per thread and turn; only that thread reads the column, so
-        // the mean may replace replica 0's value in it
-        const uint32_t fin = (W < 4u ? W : 4u) * 64u;
-        if (threadIdx.x < fin) {
-            for (uint32_t c = threadIdx.x; c < 256u; c += fin) {
-                double acc = 0.0;
-                for (uint32_t k = 0; k < a.K; ++k) acc += (double)lds[(size_t)k * 256u + c];
-                lds[c] = flat_mean_of(acc, a);
-            }
-        }
-        __syncthreads();
-        z = *reinterpret_cast<const float4 *>(lds + e0);
-    }
+    const float4 z = row_mean(lds, a.K, W, lane, [&a](double acc) { return flat_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(comp(x[r], c) = merge_elem(compv(x[r], c), compv(ss[r], c), compv(z, c));)
@@ -869,7 +998,7 @@ __global__ __launch_bounds__(1024) void flat_update_kernel(const FlatArgs a)
     extern __shared__ float lds[];                        // [K][256]
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t W = blockDim.x >> 6;
+    const uint32_t W = a.W;
     const uint64_t first = (uint64_t)blockIdx.x * 256u;
     if (a.n - first >= 256u) flat_update_row<R, NT, true>(a, lds, first, 256u, w, W, lane);
     else flat_update_row<R, NT, false>(a, lds, first, (uint32_t)(a.n - first), w, W, lane);

@@ -321,3 +321,41 @@ def test_random_legal_call_sequences(seed):
             compare_state(dev, orc, step, z_exact=False)
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("hint", [3, 4])
+@pytest.mark.parametrize("K,step_mask,merge_mask", [(5, 0b10010, 0b01100), (5, 0b11111, 0b00001), (6, 0b000001, 0b100000),
+                                                    (33, (1 << 32) | 0b1010, (1 << 31) | 0b11), (64, 1 << 63, (1 << 63) | 1)])
+def test_only_the_named_replicas_are_touched(K, step_mask, merge_mask, hint):
+    """Masked calls hand work to the named replicas only: with gaps, at both ends of the mask, with one replica in both
+    masks, with several replicas a wave, with and without the streaming hint, against the oracle's masked calls."""
+    from oracle import lasgd_oracle as O32
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    w = W.small(K=K, numels=(700, 3, 256))
+    wd = [w.weight_decay] * 3
+    x0, grads = packed_inputs(w)
+    lrs = [0.01 * (1 + k % 3) for k in range(K)]
+    for kper in (1, 2):
+        orc = O32.Oracle(K, w.numels, w.momentum, w.nesterov, wd)
+        dev = DeviceReplicas(w, weight_decay=wd)
+        try:
+            dev.ctx.set_tuning(nontemporal=hint, kper_step=kper, kper_merge=kper)
+            g = grads(0)
+            orc.set_model(x0); dev.load_model(x0); dev.load_grads(g)
+            orc.prologue(g, w.lr); dev.prologue(w.lr)
+            sel = [k for k in range(K) if (step_mask >> k) & 1]
+            before = [(dev.ctx.read_state(B.STATE_X, k), dev.ctx.read_state(B.STATE_S, k)) for k in range(K)]
+            dev.ctx.step_merge_ex(lrs, step_mask, merge_mask, True)
+            for k in range(K):
+                x, v, s = before[k][0].copy(), orc.v[k].copy(), before[k][1]
+                one = O32.Oracle(1, w.numels, w.momentum, w.nesterov, wd, threads=1)
+                one.x[0][:], one.v[0][:], one.s[0][:], one.z[:] = x, v, s, dev.ctx.read_state(B.STATE_Z)
+                if k in sel:
+                    one.local_step([g[k]], float(np.float32(lrs[k])))
+                if (merge_mask >> k) & 1:
+                    one.merge(resnapshot=True)
+                assert_close(dev.ctx.read_state(B.STATE_X, k), one.x[0], f"x replica {k}")
+                assert_close(dev.ctx.read_state(B.STATE_V, k), one.v[0], f"v replica {k}")
+                assert_close(dev.ctx.read_state(B.STATE_S, k), one.s[0], f"s replica {k}")
+        finally:
+            dev.close()

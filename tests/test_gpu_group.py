@@ -180,3 +180,31 @@ def test_sgd_ar_every_group_shape(storage, K):
                     np.testing.assert_array_equal(dev.params(k), orc.x16[k])
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("K", [4, 9, 11, 12, 13, 25])
+def test_streaming_shapes_of_the_group_calls(K, storage):
+    """The shapes taken once the state no longer fits the memory-side cache (here asked for by the streaming hint):
+    one or two replicas a wave, paced workgroups, and from K = 13 on update + in-order mean.  z stays bit-exact."""
+    w = W.small(K=K, numels=(1030, 1, 4, 257, 768, 2051), storage=storage, m=1, T=4)
+    assert run_parity(w, tuning=dict(nontemporal=3), fused_mean=True) == 0
+    from oracle import lasgd_oracle as O32
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    x0, grads = packed_inputs(w)
+    wd = [w.weight_decay] * len(w.numels)
+    orc = O32.Oracle(K, w.numels, w.momentum, w.nesterov, wd, storage=storage)
+    dev = DeviceReplicas(w, weight_decay=wd)
+    try:
+        dev.ctx.set_tuning(nontemporal=3)
+        orc.set_model(x0); dev.load_model(x0)
+        for i in range(2):
+            g = grads(i)
+            dev.load_grads(g)
+            orc.sgd_ar_step(g, w.lr)
+            dev.ctx.sgd_ar_step(w.lr)
+        for k in range(K):
+            assert_close(dev.ctx.read_state(B.STATE_X, k), orc.x[k], f"x replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
+    finally:
+        dev.close()

@@ -507,3 +507,13 @@ def test_create_destroy_returns_all_device_memory():
     torch.cuda.synchronize()
     free1, _ = torch.cuda.mem_get_info()
     assert abs(free0 - free1) <= 8 << 20, (free0, free1)
+
+
+@pytest.mark.parametrize("vec", [1, 2, 4])
+@pytest.mark.parametrize("tensors", [1, 2, 17, 64, 65, 300])
+def test_tensor_lookup_at_block_edges(tensors, vec):
+    """Which tensor a tile belongs to: tensors that end on and one element beyond a tile, blocks of 64 tiles that hold
+    one tensor, two, or more of them than one probe of sixteen covers; the last tensor spans several blocks."""
+    numels = [(256 * vec, 1, 256 * vec + 1, 3)[i % 4] for i in range(tensors - 1)] + [256 * vec * 130 + 5]
+    w = W.small(K=2, numels=numels, m=1, T=2)
+    run_parity(w, weight_decay=[1e-4 * (i % 7) for i in range(tensors)], tuning=dict(vec=vec))
