@@ -170,9 +170,10 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // (the longest contiguous runs); merges take the tiles in chunks of 8192 (8 MB
 // of z per chunk, 1 MB per XCD) so that the chunk's z is still in L2 when the
 // next replica needs it.  The split mean (256-thread workgroups with LDS) wins
-// from K = 8 upwards; next to one-wave workgroups of a local step it is
-// dispatched sparingly, which keeps the step fast, and split 2 still ends well
-// before the next global update at m = 4 (split 4 trickles until just before it).
+// from K = 8 upwards, with two groups of waves up to K = 11 and four beyond: merge + mean,
+// us at split 1 / 2 / 4: ResNet-18 K = 8 303 / 306 / 301, ResNet-50 K = 8 654 / 648 / 649,
+// step + update + mean ResNet-18 K = 10 598 / 595 / 599, K = 12 705 / 706 / 701,
+// MobileNetV2 K = 16 281 / 287 / 280, K = 24 415 / 422 / 414.
 lasgd_tuning default_tuning(const lasgd_ctx &c)
 {
     lasgd_tuning t{};
@@ -180,7 +181,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.kper_step = 1;
     t.kper_merge = 1;
     t.max_blocks = -1;
-    t.avg_split = c.K >= 8 ? 2 : 1;
+    t.avg_split = c.K >= 12 ? 4 : c.K >= 8 ? 2 : 1;
     t.avg_max_blocks = -1;
     t.nontemporal = ((uint64_t)c.K * c.npad * sizeof(float) >= (128ull << 20)) ? 3 : 0;
     t.waves_per_block = 1;
@@ -468,6 +469,8 @@ lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic, hipStrea
     uint64_t blocks = (a.nvec + cols - 1) / cols;
     if (c->tune.avg_max_blocks > 0 && blocks > (uint64_t)c->tune.avg_max_blocks) blocks = (uint64_t)c->tune.avg_max_blocks;
     if (blocks > 0x7fffffffull) blocks = 0x7fffffffull;
+    a.blocks = (uint32_t)blocks;
+    a.threads = split == 1 ? bs1 : 256u;
     const dim3 grid((uint32_t)blocks);
     const bool nt = (c->tune.nontemporal & 1) != 0;
     const bool ext = elastic || mask != c->all;

@@ -508,6 +508,7 @@ struct AvgArgs {
     double inv_k, k_as_double;
     int32_t elastic;    // EXT: blend with the previous centre
     double beta, one_minus_beta;
+    uint32_t blocks, threads; // the grid: reading it from the dispatch would be a vector load before everything else
     uint8_t idx[64];    // EXT: the participants, ascending
 };
 
@@ -538,8 +539,8 @@ template <bool EXT> __device__ __forceinline__ float finish_mean(double acc, flo
 template <int NT, bool EXT>
 __global__ __launch_bounds__(256) void average_kernel(const AvgArgs a)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.nvec; i += stride) {
+    const uint64_t stride = (uint64_t)a.blocks * a.threads;
+    for (uint64_t i = (uint64_t)blockIdx.x * a.threads + threadIdx.x; i < a.nvec; i += stride) {
         const float *p = a.s + i * 4u;
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
         uint32_t k = 0;
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(256) void average_split_kernel(const AvgArgs a)
     const uint32_t kb = (uint32_t)(((uint64_t)a.K * g) / SPLIT);
     const uint32_t ke = (uint32_t)(((uint64_t)a.K * (g + 1u)) / SPLIT);
     const uint64_t ntile = (a.nvec + COLS - 1u) / COLS;
-    for (uint64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    for (uint64_t tile = blockIdx.x; tile < ntile; tile += a.blocks) {
         const uint64_t i = tile * COLS + c;
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
         if (i < a.nvec) {
