@@ -30,7 +30,7 @@
  *   aligned, fp32 or bf16 according to `storage`), and both streams.
  * Memory owned by the library:  momentum v[k], sent models s[k], the mean z,
  *   the fp32 master copy of the parameters when storage is bf16, and the
- *   descriptor tables.
+ *   lookup tables.
  *
  * Paper <-> calls.  Prologue (steps 1-5): lasgd_local_step(eta_0),
  *   lasgd_snapshot, lasgd_average.  Loop iteration without global update
@@ -105,7 +105,8 @@ typedef struct {
                               as NaN in the parameters.  Results are unchanged when the ordering holds.  */
     int32_t group_r;       /* replicas one wave takes at a time in the one-workgroup-per-tile kernels
                               (lasgd_step_merge_average, lasgd_sgd_ar_step): 1, 2 or 4; the workgroup has
-                              ceil(K / group_r) waves, at most 16.  <0 = default (chosen from K)            */
+                              ceil(K / group_r) waves, at most 16; a value > 0 also keeps
+                              lasgd_step_merge_average in one kernel.  <0 = default (chosen from K)         */
 } lasgd_tuning;
 
 /*
@@ -195,7 +196,8 @@ lasgd_status lasgd_step_merge(lasgd_ctx *ctx, float lr, int32_t resnapshot);
  * (Algorithm 1 steps 7 and 9a-c, then Sec. 3 Eq. 8 on the models just re-sent):
  * exactly lasgd_step_merge(lr, 1) followed by lasgd_average, same roundings, but
  * the K replicas of each tile meet in on-chip memory, so the sent models are not
- * read back for the mean.  Everything runs on the main stream (after the pending
+ * read back for the mean (more than 12 replicas of a model beyond the memory-side
+ * cache take two kernels, which is faster there).  Everything runs on the main stream (after the pending
  * average), nothing on the side stream; afterwards the new mean counts as
  * launched, exactly as after lasgd_average.  Meant for cadences with nothing to
  * overlap the All-Reduce with (a global update every step, tau_max = 1 in Sec. 5.2).
@@ -300,8 +302,8 @@ lasgd_status lasgd_global_update_static(int32_t K, int64_t n, float *const *x, f
 lasgd_status lasgd_sync(lasgd_ctx *ctx);
 
 /* Change launch-shape knobs (waits for enqueued work first).  A graph captured
- * earlier keeps the shape it was recorded with and stays valid (the tile table
- * of every tile size used is kept until lasgd_destroy).
+ * earlier keeps the shape it was recorded with and stays valid (the lookup tables
+ * of every tile size used are kept until lasgd_destroy).
  * Errors: INVALID (NULL, a field outside its documented values), HIP, ALLOC. */
 lasgd_status lasgd_set_tuning(lasgd_ctx *ctx, const lasgd_tuning *t);
 

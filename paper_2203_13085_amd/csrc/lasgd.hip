@@ -1,5 +1,5 @@
 // Host side of the LASGD update library: context, validation, state machine,
-// descriptor tables, launches.  The C ABI is declared in include/lasgd.h.
+// lookup tables, launches.  The C ABI is declared in include/lasgd.h.
 //
 // Stream protocol (single-GPU image of "the All-Reduce runs while the node
 // keeps computing", Sec. 4):
