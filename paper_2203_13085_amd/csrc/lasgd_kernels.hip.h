@@ -137,7 +137,8 @@ __device__ __forceinline__ uint32_t tensor_of(const ApplyArgs &a, uint32_t tile)
 {
     uint32_t t = 0;
     if (a.n_tensors > 1u) {
-        t = as_const(a.blocks)[tile >> kBlockShift];
+        // one probe holds the whole list when no more than sixteen tensors follow the first
+        t = a.n_tensors > kProbe + 1u ? as_const(a.blocks)[tile >> kBlockShift] : kMoreInBlock;
         if (t & kMoreInBlock) {
             t &= ~kMoreInBlock;
             uint32_t below;              // how many of the next sixteen tensors start at or before the tile

@@ -517,3 +517,10 @@ def test_tensor_lookup_at_block_edges(tensors, vec):
     numels = [(256 * vec, 1, 256 * vec + 1, 3)[i % 4] for i in range(tensors - 1)] + [256 * vec * 130 + 5]
     w = W.small(K=2, numels=numels, m=1, T=2)
     run_parity(w, weight_decay=[1e-4 * (i % 7) for i in range(tensors)], tuning=dict(vec=vec))
+
+
+@pytest.mark.parametrize("tensors", [16, 18, 33, 34])
+def test_tensor_lookup_at_probe_edges(tensors):
+    """Lists that one probe of sixteen holds whole, and the first that it does not; all in the first block of tiles."""
+    w = W.small(K=2, numels=[(256, 1, 3)[i % 3] for i in range(tensors)], m=1, T=2)
+    run_parity(w, weight_decay=[1e-4 * (i % 7) for i in range(tensors)])
