@@ -659,9 +659,6 @@ static bool fill_ext(const lasgd_ctx *c, ExtArgs &x, const float *lr, uint64_t s
     x.step_mask = step_mask;
     x.merge_mask = merge_mask;
     x.alpha = c->alpha;
-    uint32_t n = 0;
-    for (uint64_t rest = step_mask | merge_mask; rest; rest &= rest - 1ull, ++n)
-        x.who[n >> 2] |= (uint32_t)__builtin_ctzll(rest) << ((n & 3u) * 8u);
     bool uniform = true;
     float first = 0.f;
     bool have = false;

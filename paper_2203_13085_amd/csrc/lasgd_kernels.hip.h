@@ -103,8 +103,6 @@ struct ExtArgs {
     uint64_t merge_mask;    // bit k: replica k takes the global update
     float alpha;            // 1 = step 9a of Algorithm 1 exactly
     float neg_lr_k[64];     // -eta per replica
-    uint32_t who[16];       // the replicas of either mask, ascending, four to a word: only they get work items (a replica
-                            // that sits the call out used to get waves that looked it up and left)
 };
 
 // ---- 128-bit / 64-bit accesses, optionally with the streaming hint --------
@@ -383,11 +381,28 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     }
 }
 
-// The j-th replica that takes part; when all do, without the look into the list.
+// Position of the n-th set bit (n = 0: the lowest) of a word that has more than n: halve the word six times.
+__device__ __forceinline__ uint32_t nth_bit(uint64_t word, uint32_t n)
+{
+    uint32_t pos = 0;
+#pragma unroll
+    for (uint32_t width = 32u; width; width >>= 1) {
+        const uint32_t below = (uint32_t)__popcll(word & ((1ull << width) - 1ull));
+        const bool above = n >= below;
+        n -= above ? below : 0u;
+        pos += above ? width : 0u;
+        word >>= above ? width : 0u;
+    }
+    return pos;
+}
+
+// The j-th replica that takes part: only those of either mask get work items (a replica that sits the call out used to
+// get waves that looked it up and left).  Found in the masks, which are in registers, not in a list in the arguments:
+// that would be one more load in front of all others and 64 bytes more for the host to hand over with each launch.
 template <bool EXT> __device__ __forceinline__ uint32_t replica_at(const ApplyArgs &a, const ExtArgs *xa, uint32_t j)
 {
     if constexpr (EXT) {
-        if (a.kcount != a.K) return (xa->who[j >> 2] >> ((j & 3u) * 8u)) & 0xffu;
+        if (a.kcount != a.K) return nth_bit(xa->step_mask | xa->merge_mask, j);
     }
     return j;
 }
