@@ -203,10 +203,10 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 // Where the state stays in the memory-side cache (no streaming hint) nothing is gained: MobileNetV2 K = 6 60 us at any of
 // these counts.
 constexpr uint32_t kLdsGranule = 1280;
-uint32_t pace_lds(int op, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
+uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
 {
     if (!(nt & 3)) return 0;
-    uint32_t granules = op == OP_STEP ? 7u : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? 10u : 0u;
+    uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? 10u : 0u;
     if (xa && op == OP_STEP_MERGE) {         // replicas that only step or only merge load less: the mean over the waves
         const uint32_t both = (uint32_t)__builtin_popcountll(xa->step_mask & xa->merge_mask);
         const uint32_t step = (uint32_t)__builtin_popcountll(xa->step_mask & ~xa->merge_mask);
@@ -220,7 +220,7 @@ uint32_t pace_lds(int op, const ExtArgs *xa, int nt, uint32_t vec, uint32_t wave
 template <int VEC, int OP, bool BF16>
 hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, hipStream_t st, int nt)
 {
-    const uint32_t lds = pace_lds(OP, xa, nt, VEC, bs.x / 64u);
+    const uint32_t lds = pace_lds(OP, BF16, xa, nt, VEC, bs.x / 64u);
     if (xa) {      // extended variants: hints all on or all off
         if (nt & 3) hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 3>), grid, bs, lds, st, a, *xa);
         else hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 0>), grid, bs, lds, st, a, *xa);

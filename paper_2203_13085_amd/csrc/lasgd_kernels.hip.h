@@ -204,6 +204,13 @@ template <int NT> __device__ __forceinline__ void st2(uint16_t *p, uint2 a)
     else *as_global<u32x2_t>(p) = r;
 }
 
+// How long the word at p takes to come says how busy the memory is.
+__device__ __forceinline__ void wait_for_word(const float *p)
+{
+    const uint32_t word = *as_global<uint32_t>(p);
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(word) : "memory");
+}
+
 // ---- bf16 <-> fp32 ----------------------------------------------------------
 __device__ __forceinline__ float bf16_widen(uint32_t h) { return __uint_as_float(h << 16); }
 
@@ -285,8 +292,8 @@ template <bool FULL> __device__ __forceinline__ uint32_t lane_elems(uint32_t e0,
 // with one to three goes element by element: all its loads before its first store,
 // as everywhere, so that the wave waits once for memory.
 // Small ragged list, K = 3: snapshot 4.0 -> 3.1 us,
-// local step 3.4 -> 3.2.
-template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT>
+// local step 3.4 -> 3.2.  ALONE: the operation is the whole kernel's, not one of several in a masked call.
+template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT, bool ALONE>
 __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const void *gu, float *xm,
                                            float *v, float *s, const float4 (&zt)[VEC], float wd,
                                            uint32_t count, uint32_t lane, float neg_lr, float alpha)
@@ -318,6 +325,12 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
 #pragma unroll
         for (int j = 0; j < VEC; ++j) x[j] = vv[j] = g[j] = ss[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
+    // An fp32 local step that streams from HBM asks for one word of its model first and issues its loads when that has
+    // come: the busier the memory, the later.  us, with 18 waves a CU (pace_lds) / with 21 and this word: ResNet-18 list
+    // K = 8 283 / 273, ResNet-50 K = 8 621 / 594, K = 24 1901 / 1863, K = 32 2495 / 2493, MobileNetV2 K = 16 172 / 165.
+    // bf16 gains below 3e8 replica-parameters (ResNet-50 K = 8 622 / 607) and loses beyond (ResNet-18 K = 32 1140 / 1156,
+    // ResNet-50 K = 32 2478 / 2492), so it goes without; so do the steps inside a masked step_merge.
+    if constexpr (ALONE && OP == OP_STEP && !BF16 && FULL && (NT & 3) != 0) wait_for_word(xf);
     // all loads first: up to 4*VEC independent 128-bit loads in flight per lane
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
@@ -469,8 +482,8 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
             float *xm = BF16 ? a.x32 + ao : nullptr;
 #define LASGD_TILE(OPX, NLR, AL)                                                                             \
     do {                                                                                                     \
-        if (__builtin_expect(full, 1)) apply_tile<VEC, OPX, BF16, NT, true, EXT>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
-        else apply_tile<VEC, OPX, BF16, NT, false, EXT>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL);     \
+        if (__builtin_expect(full, 1)) apply_tile<VEC, OPX, BF16, NT, true, EXT, OPX == OP>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
+        else apply_tile<VEC, OPX, BF16, NT, false, EXT, OPX == OP>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL);     \
     } while (0)
             if constexpr (!EXT) {
                 LASGD_TILE(OP, a.neg_lr, 1.0f);

@@ -76,3 +76,12 @@ def test_arguments_of_the_masked_kernels_stay_small(asm):
     assert len(sizes) >= 4
     for size, name in sizes:
         assert int(size) <= 512, (name, size)
+
+
+def test_streaming_fp32_local_step_asks_for_one_word_first(asm):
+    """The word that paces a wave has to be there before the wave's loads go out, in the fp32 form only."""
+    paced = r"global_load_dword v\d+,[^\n]*(?:(?!global_load_dwordx4)[^\n]*\n)*?\s*s_waitcnt vmcnt\(0\)(?:[^\n]*\n)*?[^\n]*global_load_dwordx4 [^\n]* nt"
+    f32 = _fast_path(_kernel(asm, "_ZN5lasgd12apply_kernelILi1ELi0ELb0ELi3EEEvNS_9ApplyArgsE"))
+    bf16 = _fast_path(_kernel(asm, "_ZN5lasgd12apply_kernelILi1ELi0ELb1ELi3EEEvNS_9ApplyArgsE"))
+    assert re.search(paced, f32)
+    assert not re.search(r"global_load_dword v", bf16)
