@@ -685,15 +685,6 @@ template <int NT, bool FULL> __device__ __forceinline__ float4 row_ld(const floa
     if (n > 2u) r.z = p[e0 + 2u];
     return r;
 }
-template <int NT, bool FULL> __device__ __forceinline__ float4 row_ld16(const uint16_t *p, uint32_t e0, uint32_t n)
-{
-    if (FULL || n == 4u) return widen4(ld2<NT>(p + e0));
-    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n > 0u) r.x = bf16_widen(p[e0]);
-    if (n > 1u) r.y = bf16_widen(p[e0 + 1u]);
-    if (n > 2u) r.z = bf16_widen(p[e0 + 2u]);
-    return r;
-}
 template <int NT, bool FULL> __device__ __forceinline__ void row_st(float *p, uint32_t e0, uint32_t n, float4 a)
 {
     if (FULL || n == 4u) { st4<NT>(p + e0, a); return; }
@@ -767,11 +758,43 @@ __device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, co
 {
     return replica_tile<BF16>(a, t, load_record(a, k, tensor), k);
 }
-template <bool BF16, int NT, bool FULL>
-__device__ __forceinline__ float4 row_ld_grad(const void *g, uint32_t e0, uint32_t n)
+// The loads of R replicas' gradients (G) and models (X) from the caller's buffers.  The last row of a tensor takes the
+// same 128-bit accesses in the lanes that have four elements; only the one lane with one to three goes element by
+// element.  All replicas' loads are issued before anything waits: array by array, every one of them waited for the last
+// (flat list of 1000 elements, K = 64: fused update 16.3 -> 12.9 us, SGD-AR 10.2 -> 8.1).  The library's own arrays need none of this: they are
+// padded to whole rows.
+template <int R, bool BF16, int NT, bool FULL, bool G, bool X>
+__device__ __forceinline__ void ld_caller(const ReplicaTile<BF16> (&q)[R], uint32_t e0, uint32_t n, float4 (&g)[R], float4 (&x)[R])
 {
-    if constexpr (BF16) return row_ld16<NT, FULL>(static_cast<const uint16_t *>(g), e0, n);
-    else return row_ld<NT, FULL>(static_cast<const float *>(g), e0, n);
+    if constexpr (!FULL) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (G) g[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (X && !BF16) x[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+    if constexpr (X && BF16) {             // the master copy: whole rows
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = ld4<NT>(q[r].xf + e0);
+    }
+    if (FULL || n == 4u) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (G) g[r] = BF16 ? widen4(ld2<NT>(static_cast<const uint16_t *>(q[r].g) + e0)) : ld4<NT>(static_cast<const float *>(q[r].g) + e0);
+            if constexpr (X && !BF16) x[r] = ld4<NT>(q[r].xf + e0);
+        }
+    }
+    if constexpr (!FULL) {
+        if (n - 1u < 3u) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                LASGD_FOR4(if (c < 3 && (uint32_t)c < n) {
+                    if constexpr (G) comp(g[r], c) = BF16 ? bf16_widen(*as_global<uint16_t>(static_cast<const uint16_t *>(q[r].g) + e0 + c))
+                                                          : *as_global<float>(static_cast<const float *>(q[r].g) + e0 + c);
+                    if constexpr (X && !BF16) comp(x[r], c) = *as_global<float>(q[r].xf + e0 + c);
+                })
+        }
+    }
 }
 
 // A wave owns replicas w + q*W, q = 0, 1, ...; it takes them R at a time ("pass").
@@ -799,23 +822,24 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             const uint32_t kw = w + (uint32_t)r * W;
             mine[r] = kw < a.K;
             rt[r] = r == 0 ? replica_tile<BF16>(a, t, rec0, kw) : replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u, tensor);
-            g[r] = row_ld_grad<BF16, NT, FULL>(rt[r].g, e0, n);
-            x[r] = row_ld<NT, FULL>(rt[r].xf, e0, n);
-            v[r] = row_ld<NT, FULL>(rt[r].v, e0, n);
         }
+        ld_caller<R, BF16, NT, FULL, true, true>(rt, e0, n, g, x);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = ld4<NT>(rt[r].v + e0);
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if (mine[r]) *reinterpret_cast<float4 *>(lds + (size_t)(w + (uint32_t)r * W) * 256u + lane * 4u) = g[r];
     }
     for (uint32_t p = 1; p < passes; ++p) {
+        ReplicaTile<BF16> q[R];
         float4 g[R];
         uint32_t kw[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
-            const ReplicaTile<BF16> q = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
-            g[r] = row_ld_grad<BF16, NT, FULL>(q.g, e0, n);
+            q[r] = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
         }
+        ld_caller<R, BF16, NT, FULL, true, false>(q, e0, n, g, g);
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if (kw[r] < a.K) *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = g[r];
@@ -840,9 +864,10 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             const uint32_t kw = w + (p * R + (uint32_t)r) * W;
             ok[r] = kw < a.K;
             q[r] = replica_tile<BF16>(a, t, ok[r] ? kw : a.K - 1u, tensor);
-            xx[r] = row_ld<NT, FULL>(q[r].xf, e0, n);
-            vv[r] = row_ld<NT, FULL>(q[r].v, e0, n);
         }
+        ld_caller<R, BF16, NT, FULL, false, true>(q, e0, n, xx, xx);
+#pragma unroll
+        for (int r = 0; r < R; ++r) vv[r] = ld4<NT>(q[r].v + e0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             LASGD_FOR4(step_elem(comp(xx[r], c), comp(vv[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
@@ -889,7 +914,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
 {
     const uint32_t e0 = row * 256u + lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= t.count) ? 0u : (t.count - e0 < 4u) ? t.count - e0 : 4u;
-    const float4 z = row_ld<0, FULL>(a.z + t.aoff, e0, n);         // shared by the K waves: cacheable
+    const float4 z = ld4<0>(a.z + t.aoff + e0);                    // shared by the K waves: cacheable
     for (uint32_t p = 0; p < passes; ++p) {
         ReplicaTile<BF16> q[R];
         float4 x[R], v[R], g[R], ss[R];
@@ -898,10 +923,12 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
             q[r] = r == 0 && p == 0u ? replica_tile<BF16>(a, t, rec0, kw[r]) : replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
-            g[r] = row_ld_grad<BF16, NT, FULL>(q[r].g, e0, n);
-            x[r] = row_ld<NT, FULL>(q[r].xf, e0, n);
-            v[r] = row_ld<NT, FULL>(q[r].v, e0, n);
-            ss[r] = row_ld<NT, FULL>(q[r].s, e0, n);
+        }
+        ld_caller<R, BF16, NT, FULL, true, true>(q, e0, n, g, x);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v[r] = ld4<NT>(q[r].v + e0);
+            ss[r] = ld4<NT>(q[r].s + e0);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {

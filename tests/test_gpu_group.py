@@ -208,3 +208,32 @@ def test_streaming_shapes_of_the_group_calls(K, storage):
             assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("storage,K,R,hint", [("bf16", 40, 1, 3), ("f32", 40, 2, 3), ("bf16", 33, 1, 4), ("f32", 64, 2, 4),
+                                              ("f32", 17, 4, 3), ("f32", 12, 1, 3)])
+def test_replicas_a_wave_as_asked_for(storage, K, R, hint):
+    """group_r: one kernel whatever K, and a second and third pass of a wave where K exceeds 16 R."""
+    w = W.small(K=K, numels=(2048, 12, 999, 1, 514), storage=storage, m=2, T=4, nesterov=False)
+    assert run_parity(w, fused_mean=True, tuning=dict(nontemporal=hint, group_r=R)) == 0
+    from oracle import lasgd_oracle as O32
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    x0, grads = packed_inputs(w)
+    wd = [w.weight_decay] * len(w.numels)
+    orc = O32.Oracle(K, w.numels, w.momentum, w.nesterov, wd, storage=storage)
+    dev = DeviceReplicas(w, weight_decay=wd)
+    try:
+        dev.ctx.set_tuning(nontemporal=hint, group_r=R)
+        orc.set_model(x0); dev.load_model(x0)
+        for i in range(3):
+            g = grads(i)
+            dev.load_grads(g)
+            orc.sgd_ar_step(g, w.lr)
+            dev.ctx.sgd_ar_step(w.lr)
+        for k in range(K):
+            assert_close(dev.ctx.read_state(B.STATE_X, k), orc.x[k], f"x replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
+            if storage == "bf16":
+                np.testing.assert_array_equal(dev.params(k), orc.x16[k])
+    finally:
+        dev.close()
