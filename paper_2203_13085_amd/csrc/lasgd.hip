@@ -203,6 +203,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 // Where the state stays in the memory-side cache (no streaming hint) nothing is gained: MobileNetV2 K = 6 60 us at any of
 // these counts.
 constexpr uint32_t kLdsGranule = 1280;
+constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
 uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
 {
     if (!(nt & 3)) return 0;
@@ -214,7 +215,7 @@ uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, ui
         granules = (10u * both + 7u * step + 6u * merge) / (both + step + merge);
     }
     const uint32_t bytes = granules * kLdsGranule * vec * waves_per_block;
-    return bytes < 65536u ? bytes : 65536u;
+    return bytes < kMaxLds ? bytes : (uint32_t)kMaxLds;
 }
 
 template <int VEC, int OP, bool BF16>
@@ -354,10 +355,13 @@ lasgd_status enqueue_apply(lasgd_ctx *c, int op, float lr, int resnap, const Ext
     return launch_apply(c, p);
 }
 
+// Streaming, lasgd_step_merge_average holds up to this many replicas in one workgroup; beyond, it takes two kernels.
+constexpr uint32_t kOneKernelMaxK = 12;
+
 // The replica-group kernels: one workgroup per tile, W waves, R replicas per wave.
 struct GroupShape {
     uint32_t R, W, passes;
-    uint32_t delay;      // sleeps of 512 clocks before a wave's first load
+    bool staged;         // a wave's loads in two groups, the second when the first has arrived
     dim3 grid, bs;
     size_t lds;
 };
@@ -373,10 +377,11 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     // against 2 (SGD-AR): ResNet-50 list K = 8 664, 688; ResNet-18 K = 12 460, 477; MobileNetV2 K = 13 196, 160; bf16 with
     // its three more streams changes over earlier, ResNet-18 K = 10 467, 377.  R = 2 against 4: MobileNetV2 K = 24 308, 312,
     // K = 32 433, 411.  In the memory-side cache two a wave from K = 9 on: MobileNetV2's first 60 tensors K = 16 8.0, 7.0.
-    // Fused update (its sum is the last thing a workgroup does): ResNet-50 K = 8 988, 1011; ResNet-18 bf16 K = 11 639, 642;
-    // K = 12 see below.
+    // Fused update (its sum is the last thing a workgroup does): one a wave up to K = 9, streaming see below; in the
+    // memory-side cache one / two at 2^20 elements K = 8 44.1 / 43.3, K = 16 100 / 92; 300,000 elements K = 16 27.1 / 25.6.
+    const bool paced = streaming && kind == 1 && K <= kOneKernelMaxK && c->tune.group_r <= 0;
     if (kind == 0) g.R = K <= (streaming && !bf16 ? 12u : 8u) ? 1u : K <= (streaming ? 24u : 32u) ? 2u : 4u;
-    else g.R = K <= kGroupWaves && !(streaming && K == 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
+    else g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     if (c->tune.group_r > 0) g.R = (uint32_t)c->tune.group_r;
     if (g.R > K) g.R = K >= 4 ? 4 : K >= 2 ? 2 : 1;
     g.W = (K + g.R - 1) / g.R;
@@ -387,26 +392,30 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     g.grid = dim3((uint32_t)blocks);
     g.bs = dim3(64u * g.W);
     g.lds = (size_t)K * 256u * sizeof(float);
-    if (streaming && kind == 1 && K <= 12u && K != 11u && c->tune.group_r <= 0) {
-        // Paced like the other kernels (pace_lds): 16 to 21 waves a CU.  Without / with: ResNet-18 K = 4 224 / 222 us,
-        // ResNet-50 K = 8 1003 / 988; at K = 11 only one workgroup would fit (635 / 655).  At K = 12 two workgroups a CU (six waves of two replicas) are a little too much and
-        // one too little; there every wave starts about 0.6 us late: ResNet-18 696 -> 677 us, bf16 716 -> 697 (one replica
-        // a wave: 708 and 714, one workgroup a CU 688 and 709).  The SGD-AR kernel waits for its gradients in the middle,
-        // and holding waves back costs it (K = 8 664 / 688).
-        const size_t pace = (size_t)(g.R == 1u ? 6u : 8u) * kLdsGranule * g.W;
-        if (pace > g.lds) g.lds = pace;
-        if (K == 12u) g.delay = 3u;
+    if (paced) {
+        // Paced like the other kernels (pace_lds): about 60 KiB of loads in flight per CU, in whole workgroups.  Up to
+        // K = 9 a wave issues all the loads of its replica, 4 KiB, and the LDS a workgroup asks for leaves room for 16 to
+        // 21 waves.  From K = 10 on one workgroup a CU is too few and two are too many (70 to 96 KiB), so a wave asks for
+        // the gradients when the rest is there: two workgroups then start with 3 KiB a replica, 60 to 72 KiB.  Two
+        // replicas a wave, unless two workgroups of one-replica waves fill three quarters of the CU's 32 slots (K = 12).  us, means
+        // over eight placements in memory, one replica and everything at once / one, staged / two, staged: ResNet-18 list bf16
+        // K = 9 527 / 555 / 528, 10 586 / 607 / 579, 11 643 / 657 / 638, 12 717 / 687 / 699, fp32 K = 12 710 / 688 / 688;
+        // ResNet-50 bf16 K = 12 1540 / 1520 / 1530; MobileNetV2 bf16 K = 12 218 / 214 / 219.  The SGD-AR kernel waits for
+        // its gradients in the middle, and holding its waves back costs it.
+        g.staged = K > 9u;
+        const size_t pace = g.staged ? 43u * kLdsGranule : (size_t)6u * kLdsGranule * g.W;      // 43 granules: two a CU
+        g.lds = pace > g.lds ? (pace < kMaxLds ? pace : kMaxLds) : g.lds;
     }
     return g;
 }
 
-template <int KIND, bool BF16, int NT>
+template <int KIND, bool BF16, int NT, bool ST>
 hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t st)
 {
 #define LASGD_GROUP(RR)                                                                                  \
     do {                                                                                                 \
         if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT>), g.grid, g.bs, g.lds, st, a, g.passes); \
-        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT>), g.grid, g.bs, g.lds, st, a, g.passes);         \
+        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes);         \
     } while (0)
     if (g.R == 1) LASGD_GROUP(1);
     else if (g.R == 2) LASGD_GROUP(2);
@@ -421,13 +430,12 @@ hipError_t launch_group(int kind, ApplyArgs &a, const GroupShape &g, hipStream_t
     const bool hint = (nt & 3) != 0;
     a.wpb = g.W;
     a.nwaves = g.grid.x;
-    a.delay = g.delay;
-    if (kind == 0) {
-        if (bf16) return hint ? launch_group_r<0, true, 3>(a, g, st) : launch_group_r<0, true, 0>(a, g, st);
-        return hint ? launch_group_r<0, false, 3>(a, g, st) : launch_group_r<0, false, 0>(a, g, st);
-    }
-    if (bf16) return hint ? launch_group_r<1, true, 3>(a, g, st) : launch_group_r<1, true, 0>(a, g, st);
-    return hint ? launch_group_r<1, false, 3>(a, g, st) : launch_group_r<1, false, 0>(a, g, st);
+#define LASGD_KIND(KIND, BF)                                                                              \
+    (!hint ? launch_group_r<KIND, BF, 0, false>(a, g, st)                                                 \
+           : g.staged ? launch_group_r<KIND, BF, 3, true>(a, g, st) : launch_group_r<KIND, BF, 3, false>(a, g, st))
+    if (kind == 0) return bf16 ? LASGD_KIND(0, true) : LASGD_KIND(0, false);
+    return bf16 ? LASGD_KIND(1, true) : LASGD_KIND(1, false);
+#undef LASGD_KIND
 }
 
 template <bool EXT>
@@ -891,10 +899,11 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
     if (c->alpha != 1.f || c->beta != 1.f)
         return fail(c, LASGD_ERR_STATE, "elastic coefficients are set: use lasgd_step_merge and lasgd_average");
     const bool captured = is_capturing(c->main);
-    if (c->K > 12 && (c->tune.nontemporal & 3) && c->tune.group_r <= 0) {
+    if (c->K > (int32_t)kOneKernelMaxK && (c->tune.nontemporal & 3) && c->tune.group_r <= 0) {
         // Streaming from 13 replicas on, workgroups that hold all replicas of a tile lose more to their shape than the
-        // second pass over s costs: update, then the in-order mean.  us, one kernel / two: MobileNetV2 K = 14 248 / 247,
-        // K = 16 295 / 281, K = 24 452 / 415; ResNet-18 bf16 K = 24 1453 / 1404; but K = 12 686 / 705.
+        // second pass over s costs: update, then the in-order mean.  us, one kernel / two: K = 12 ResNet-18
+        // 667 / 706, bf16 697 / 716, ResNet-50 bf16 1542 / 1563, MobileNetV2 bf16 217 / 216; K = 13 737 / 765, 768 / 776,
+        // 1709 / 1700, 236 / 233; K = 16 MobileNetV2 286 / 282, bf16 293 / 285, ResNet-50 bf16 2102 / 2077.
         ApplyPlan p;
         if ((st = plan_apply(c, p, OP_STEP_MERGE, lr, 1)) != LASGD_OK) return st;
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));

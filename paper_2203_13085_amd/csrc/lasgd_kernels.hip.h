@@ -91,7 +91,6 @@ struct ApplyArgs {
     FastDiv by_per, by_chunk, by_stride;   // division by chunk * kgroups, chunk, tail_stride
     // the replica-group kernels finish a mean over all K replicas themselves
     int32_t use_mul;        // K is a power of two: multiply by the exact reciprocal
-    uint32_t delay;         // sleeps of 512 clocks before a wave's first load
     double inv_k, k_as_double;
 };
 
@@ -203,6 +202,9 @@ template <int NT> __device__ __forceinline__ void st2(uint16_t *p, uint2 a)
     if constexpr (NT & 2) __builtin_nontemporal_store(r, as_global<u32x2_t>(p));
     else *as_global<u32x2_t>(p) = r;
 }
+
+// Every load written before it has arrived, none written after it is issued yet.
+__device__ __forceinline__ void wait_for_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // How long the word at p takes to come says how busy the memory is.
 __device__ __forceinline__ void wait_for_word(const float *p)
@@ -908,13 +910,16 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
 // just sent -- is written over the old one.  Only this workgroup touches the
 // tile's z, and all its waves have used the old values before the barrier.
 // Same roundings as step_merge followed by the in-order mean.
-template <int R, bool BF16, int NT, bool FULL>
+// STAGED: the gradients are asked for when everything else has arrived, so that a wave has
+// three quarters of its loads in flight.
+template <int R, bool BF16, int NT, bool FULL, bool STAGED>
 __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
                                                     uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= t.count) ? 0u : (t.count - e0 < 4u) ? t.count - e0 : 4u;
-    const float4 z = ld4<0>(a.z + t.aoff + e0);                    // shared by the K waves: cacheable
+    float4 z;                                                      // shared by the K waves: cacheable
+    if constexpr (!STAGED) z = ld4<0>(a.z + t.aoff + e0);
     for (uint32_t p = 0; p < passes; ++p) {
         ReplicaTile<BF16> q[R];
         float4 x[R], v[R], g[R], ss[R];
@@ -924,11 +929,18 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
             kw[r] = w + (p * R + (uint32_t)r) * W;
             q[r] = r == 0 && p == 0u ? replica_tile<BF16>(a, t, rec0, kw[r]) : replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
         }
-        ld_caller<R, BF16, NT, FULL, true, true>(q, e0, n, g, x);
+        ld_caller<R, BF16, NT, FULL, !STAGED, true>(q, e0, n, g, x);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             v[r] = ld4<NT>(q[r].v + e0);
+            if constexpr (STAGED) {
+                if (r == 0 && p == 0u) z = ld4<0>(a.z + t.aoff + e0);
+            }
             ss[r] = ld4<NT>(q[r].s + e0);
+        }
+        if constexpr (STAGED) {
+            wait_for_loads();
+            ld_caller<R, BF16, NT, FULL, true, false>(q, e0, n, g, x);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -958,14 +970,13 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
     }
 }
 
-template <int R, bool BF16, int NT>
+template <int R, bool BF16, int NT, bool STAGED>
 __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a, const uint32_t passes)
 {
     extern __shared__ float lds[];                        // [K][256]
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = a.wpb;
-    for (uint32_t i = 0; i < a.delay; ++i) __builtin_amdgcn_s_sleep(8);
     bool again = false;
     for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
         const uint32_t tensor = tensor_of(a, tile);
@@ -975,8 +986,8 @@ __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a
         for (uint32_t row = 0; row < rows; ++row) {
             if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
             again = true;
-            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
-            else step_merge_mean_row<R, BF16, NT, false>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            else step_merge_mean_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
     }
 }

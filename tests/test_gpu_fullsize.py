@@ -99,12 +99,13 @@ def _compare_everything(dev, orc, step, z_ties):
     return assert_same(dev.ctx.read_state(B.STATE_Z), orc.z, f"z step {step}", max_bit_diffs=z_ties)
 
 
-def _full_size_run(cfg, fused_mean=False, full_every_step=True, sample=None, T=None):
+def _full_size_run(cfg, fused_mean=False, full_every_step=True, sample=None, T=None, **changes):
     import dataclasses
     from paper_2203_13085_amd.driver import DeviceReplicas
     w = W.config(cfg)
     if T is not None:
         w = dataclasses.replace(w, T=T)
+    w = dataclasses.replace(w, **changes)
     bf16 = w.storage == "bf16"
     nt = len(w.numels)
     wd = [w.weight_decay] * nt
@@ -166,6 +167,14 @@ def test_full_size_every_element_every_step(cfg):
 def test_full_size_fused_mean_every_element_every_step():
     # configs[3] (a global update every step) through lasgd_step_merge_average
     _full_size_run(3, fused_mean=True)
+
+
+@pytest.mark.parametrize("K,storage", [(8, "f32"), (12, "f32"), (12, "bf16")])
+def test_full_size_fused_mean_in_one_kernel(K, storage):
+    """The ResNet-18 list, which streams, through lasgd_step_merge_average at replica counts that stay in one kernel: whole
+    loads and two workgroups a CU at K = 8, two replicas a wave with staged loads at K = 12 (MobileNetV2 with its sixteen
+    replicas, above, takes two kernels)."""
+    _full_size_run(1, fused_mean=True, T=2, m=1, K=K, storage=storage)
 
 
 def test_full_size_hundred_steps():

@@ -97,20 +97,20 @@ def test_fused_mean_mixes_with_the_two_stream_calls():
         dev.close()
 
 
-@pytest.mark.parametrize("m", [1, 3])
-def test_fused_mean_graph_replay_equals_eager(m):
+def _graph_replay_equals_eager(w, m, tuning=None):
     """m-1 local steps + the fused call captured as one graph and replayed several times, with
     eager library work and host synchronisation between the replays: every replay must give the
     oracle's state (z included: the graph writes it in place)."""
     import torch
     from oracle import lasgd_oracle as O32
     from paper_2203_13085_amd.driver import DeviceReplicas
-    w = W.small(K=4, numels=(70000, 5, 1024, 4099), m=m)
     x0, grads = packed_inputs(w)
     wd = [w.weight_decay] * len(w.numels)
     dev = DeviceReplicas(w, weight_decay=wd)
     o = O32.Oracle(w.K, w.numels, w.momentum, w.nesterov, wd)
     try:
+        if tuning:
+            dev.ctx.set_tuning(**tuning)
         g = grads(1)
         o.set_model(x0); dev.load_model(x0); dev.load_grads(g)
         o.prologue(g, w.lr); dev.prologue(w.lr)
@@ -153,6 +153,18 @@ def test_fused_mean_graph_replay_equals_eager(m):
         compare_state(dev, o, 99)
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("m", [1, 3])
+def test_fused_mean_graph_replay_equals_eager(m):
+    _graph_replay_equals_eager(W.small(K=4, numels=(70000, 5, 1024, 4099), m=m), m)
+
+
+@pytest.mark.parametrize("K", [12, 13])
+def test_streaming_fused_call_replays_from_a_graph(K):
+    """The streaming forms under capture: one kernel with staged loads, and from K = 13 on update + in-order mean, two
+    nodes of the graph.  The split mean of the eager cycles in between is set to one part, so that z is bit-exact."""
+    _graph_replay_equals_eager(W.small(K=K, numels=(9000, 5, 1024, 513), m=2), 2, tuning=dict(nontemporal=3, avg_split=1))
 
 
 @pytest.mark.parametrize("storage,K", [("f32", 1), ("f32", 3), ("f32", 8), ("bf16", 16), ("f32", 17), ("bf16", 33),
@@ -208,6 +220,13 @@ def test_streaming_shapes_of_the_group_calls(K, storage):
             assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("K", [1, 8, 10, 14, 15, 16, 24])
+def test_streaming_shapes_at_the_rules_edges(K, storage):
+    """Both sides of each line of the shape rules that the test above leaves out."""
+    test_streaming_shapes_of_the_group_calls(K, storage)
 
 
 @pytest.mark.parametrize("storage,K,R,hint", [("bf16", 40, 1, 3), ("f32", 40, 2, 3), ("bf16", 33, 1, 4), ("f32", 64, 2, 4),
