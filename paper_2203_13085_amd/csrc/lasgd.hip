@@ -355,6 +355,7 @@ lasgd_status enqueue_apply(lasgd_ctx *c, int op, float lr, int resnap, const Ext
     return launch_apply(c, p);
 }
 
+constexpr uint64_t kWavesOnChip = 256u * 32u;     // 256 CUs hold at most 32 waves each
 // Streaming, lasgd_step_merge_average holds up to this many replicas in one workgroup; beyond, it takes two kernels.
 constexpr uint32_t kOneKernelMaxK = 12;
 
@@ -371,17 +372,22 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
 {
     GroupShape g{};
     const uint32_t K = (uint32_t)c->K;
-    const bool streaming = (c->tune.nontemporal & 3) != 0, bf16 = c->storage == LASGD_BF16;
-    // Replicas a wave takes at a time.  A wave with one replica has the fewest loads to wait for, but a workgroup of
-    // more than eight waves leaves slots empty until a whole workgroup's worth is free on one CU.  us on MI355X, R = 1
-    // against 2 (SGD-AR): ResNet-50 list K = 8 664, 688; ResNet-18 K = 12 460, 477; MobileNetV2 K = 13 196, 160; bf16 with
-    // its three more streams changes over earlier, ResNet-18 K = 10 467, 377.  R = 2 against 4: MobileNetV2 K = 24 308, 312,
-    // K = 32 433, 411.  In the memory-side cache two a wave from K = 9 on: MobileNetV2's first 60 tensors K = 16 8.0, 7.0.
+    const bool streaming = (c->tune.nontemporal & 3) != 0;
+    // Replicas a wave takes at a time, us on MI355X.
+    // SGD-AR, streaming: one, with the models asked for when the gradients are there (staged), up to K = 12 and at 15 and 16;
+    // workgroups of 13 and 14 such waves leave 6 and 4 of a CU's 32 slots empty.  One / two a wave: ResNet-18 list K = 12
+    // 466 / 481, 13 520 / 519, 16 630 / 698, bf16 480 / 487, 551 / 536, 662 / 695; ResNet-50 K = 13 1190 / 1170, bf16
+    // 1320 / 1217.  All loads at once / staged: ResNet-18 bf16 K = 6 260 / 234, 8 320 / 311, fp32 K = 10 406 / 389, K = 16
+    // 727 / 630.  Two against four: MobileNetV2 K = 24 304 / 318, K = 32 433 / 411.
+    // SGD-AR in the memory-side cache: one a wave while all waves fit the chip at once (small ragged list bf16 K = 8 4.3 / 5.2),
+    // else two from K = 4 on (2^20 elements bf16 K = 4 16.8 / 15.0, MobileNetV2 bf16 K = 6 82 / 69, fp32 K = 3 32.9 / 32.9).
     // Fused update (its sum is the last thing a workgroup does): one a wave up to K = 9, streaming see below; in the
     // memory-side cache one / two at 2^20 elements K = 8 44.1 / 43.3, K = 16 100 / 92; 300,000 elements K = 16 27.1 / 25.6.
     const bool paced = streaming && kind == 1 && K <= kOneKernelMaxK && c->tune.group_r <= 0;
-    if (kind == 0) g.R = K <= (streaming && !bf16 ? 12u : 8u) ? 1u : K <= (streaming ? 24u : 32u) ? 2u : 4u;
-    else g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
+    const bool at_once = (uint64_t)c->tables->ntiles * K <= kWavesOnChip;
+    if (kind == 1) g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
+    else if (streaming) g.R = K <= 12u || K == 15u || K == 16u ? 1u : K <= 24u ? 2u : 4u;
+    else g.R = K <= (at_once ? kGroupWaves : 3u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     if (c->tune.group_r > 0) g.R = (uint32_t)c->tune.group_r;
     if (g.R > K) g.R = K >= 4 ? 4 : K >= 2 ? 2 : 1;
     g.W = (K + g.R - 1) / g.R;
@@ -392,6 +398,7 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     g.grid = dim3((uint32_t)blocks);
     g.bs = dim3(64u * g.W);
     g.lds = (size_t)K * 256u * sizeof(float);
+    g.staged = kind == 0 && streaming && g.R == 1u;
     if (paced) {
         // Paced like the other kernels (pace_lds): about 60 KiB of loads in flight per CU, in whole workgroups.  Up to
         // K = 9 a wave issues all the loads of its replica, 4 KiB, and the LDS a workgroup asks for leaves room for 16 to
@@ -414,7 +421,7 @@ hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t s
 {
 #define LASGD_GROUP(RR)                                                                                  \
     do {                                                                                                 \
-        if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT>), g.grid, g.bs, g.lds, st, a, g.passes); \
+        if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes); \
         else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes);         \
     } while (0)
     if (g.R == 1) LASGD_GROUP(1);
@@ -1060,7 +1067,7 @@ template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hi
     // below that the extra wave is free and shortens the call (K = 4, n = 300,000 4.5 against 4.9), and from K = 12 on one
     // a wave is ahead again (n = 1,000,003 31.6 against 34.2).
     uint32_t R = a.K <= kGroupWaves ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
-    if (NT == 0 && a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > 8192u) R = 2u;
+    if (NT == 0 && a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > kWavesOnChip) R = 2u;
     a.W = (a.K + R - 1u) / R;
     const dim3 bs(64u * a.W);
     const size_t lds = (size_t)a.K * 256u * sizeof(float);

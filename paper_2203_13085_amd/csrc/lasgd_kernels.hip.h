@@ -807,13 +807,14 @@ __device__ __forceinline__ void ld_caller(const ReplicaTile<BF16> (&q)[R], uint3
 // the K gradients are averaged (fp64 in replica order, one rounding to fp32) and
 // every replica takes the local update with that mean gradient.  Same 20 bytes
 // per replica-parameter as a local step.
-template <int R, bool BF16, int NT, bool FULL>
+// STAGED: the models are asked for when the gradients have arrived, and fly while these go round through LDS.
+template <int R, bool BF16, int NT, bool FULL, bool STAGED>
 __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
                                            uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= t.count) ? 0u : (t.count - e0 < 4u) ? t.count - e0 : 4u;
-    // first pass: the model loads are issued with the gradient loads, ahead of the exchange
+    // first pass: the model loads are issued ahead of the exchange
     float4 x[R], v[R];
     ReplicaTile<BF16> rt[R];
     bool mine[R];
@@ -825,7 +826,11 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             mine[r] = kw < a.K;
             rt[r] = r == 0 ? replica_tile<BF16>(a, t, rec0, kw) : replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u, tensor);
         }
-        ld_caller<R, BF16, NT, FULL, true, true>(rt, e0, n, g, x);
+        ld_caller<R, BF16, NT, FULL, true, !STAGED>(rt, e0, n, g, x);
+        if constexpr (STAGED) {
+            wait_for_loads();
+            ld_caller<R, BF16, NT, FULL, false, true>(rt, e0, n, g, x);
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = ld4<NT>(rt[r].v + e0);
 #pragma unroll
@@ -882,7 +887,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
     }
 }
 
-template <int R, bool BF16, int NT>
+template <int R, bool BF16, int NT, bool STAGED>
 __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const uint32_t passes)
 {
     extern __shared__ float lds[];                        // [K][256]
@@ -898,8 +903,8 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
         for (uint32_t row = 0; row < rows; ++row) {
             if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
             again = true;
-            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
-            else sgd_ar_row<R, BF16, NT, false>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            else sgd_ar_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
     }
 }

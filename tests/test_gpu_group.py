@@ -256,3 +256,27 @@ def test_replicas_a_wave_as_asked_for(storage, K, R, hint):
                 np.testing.assert_array_equal(dev.params(k), orc.x16[k])
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("K", [3, 4, 8, 16])
+def test_sgd_ar_in_cache_with_more_waves_than_the_chip_holds(K):
+    """Beyond 8192 waves the in-cache shape takes two replicas a wave from K = 4 on; below, one (the list above is small)."""
+    from oracle import lasgd_oracle as O32
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    w = W.small(K=K, numels=(8193 * 256 // K + 3, 5))
+    x0, grads = packed_inputs(w)
+    wd = [1e-3, 0.0]
+    orc = O32.Oracle(K, w.numels, w.momentum, w.nesterov, wd)
+    dev = DeviceReplicas(w, weight_decay=wd)
+    try:
+        orc.set_model(x0); dev.load_model(x0)
+        g = grads(0)
+        dev.load_grads(g)
+        for _ in range(2):
+            orc.sgd_ar_step(g, w.lr)
+            dev.ctx.sgd_ar_step(w.lr)
+        for k in range(K):
+            assert_close(dev.ctx.read_state(B.STATE_X, k), orc.x[k], f"x replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
+    finally:
+        dev.close()
