@@ -289,7 +289,8 @@ lasgd_status lasgd_read_state(lasgd_ctx *ctx, int32_t which, int32_t k, int32_t 
  * device (the buffers).  stream: hipStream_t (NULL = default stream); one kernel
  * is enqueued on it, the call does not wait for it.  z is not an output: it stays
  * on the chip, so calls on different streams share nothing.  Vectors longer than
- * LASGD_STATIC_MAX_N elements are refused.  Error text: lasgd_last_error(NULL).
+ * LASGD_STATIC_MAX_N elements are refused: a caller may rely on that limit, which
+ * no buffer of the library stands behind.  Error text: lasgd_last_error(NULL).
  * Errors: INVALID (NULL, K outside 1..64, n < 1, NULL / misaligned / overlapping
  * buffer), UNSUPPORTED (n > LASGD_STATIC_MAX_N), HIP.  A failed call leaves the caller's
  * buffers untouched.

@@ -1054,6 +1054,8 @@ void lasgd_destroy(lasgd_ctx *c)
 } // extern "C"
 
 // ---- the allocation-free entry point ---------------------------------------
+// The limit is part of the interface, which promises to refuse longer vectors; the kernel would take them (64-bit offsets,
+// one workgroup per 256 elements).
 constexpr int64_t kStaticMaxN = LASGD_STATIC_MAX_N;
 
 namespace {
@@ -1088,8 +1090,7 @@ extern "C" lasgd_status lasgd_global_update_static(int32_t K, int64_t n, float *
         if (n < 1) return fail(nullptr, LASGD_ERR_INVALID, "n = %lld: nothing to update", (long long)n);
         if (n > kStaticMaxN)
             return fail(nullptr, LASGD_ERR_UNSUPPORTED,
-                        "n = %lld exceeds the static buffer of this entry point (LASGD_STATIC_MAX_N = %lld elements); "
-                        "split the vector or use a context",
+                        "n = %lld exceeds LASGD_STATIC_MAX_N = %lld elements; split the vector or use a context",
                         (long long)n, (long long)kStaticMaxN);
         FlatArgs a{};
         for (int32_t k = 0; k < K; ++k) {

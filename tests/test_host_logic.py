@@ -112,6 +112,8 @@ def test_static_global_update_validates_before_any_device_call():
     assert L.lasgd_global_update_static(2, 8, buf, cross, 1, None) == B.ERR_INVALID
     assert b"overlaps" in L.lasgd_last_error(None)
     assert L.lasgd_global_update_static(2, B.STATIC_MAX_N + 1, buf, same, 1, None) == B.ERR_UNSUPPORTED
+    text = L.lasgd_last_error(None).decode()
+    assert "LASGD_STATIC_MAX_N" in text and "buffer" not in text      # the call keeps none
     assert b"LASGD_STATIC_MAX_N" in L.lasgd_last_error(None)
     text = open(os.path.join(ROOT, "include", "lasgd.h")).read()
     m = re.search(r"#define LASGD_STATIC_MAX_N \((\d+)ll << (\d+)\)", text)

@@ -1,8 +1,7 @@
 """The allocation-free entry point, lasgd_global_update_static, against the
 context calls it is a variant of (lasgd_average + lasgd_merge) and against the
-oracle: bit for bit, on two calls in a row that share the library's static
-device buffer, the second on a smaller, ragged vector.  Device memory in use
-must not change across either call."""
+oracle: bit for bit, on two calls in a row, the second on a smaller, ragged
+vector.  Device memory in use must not change across either call."""
 import numpy as np
 import pytest
 import torch
@@ -75,11 +74,11 @@ def _one_call(K, n, resnapshot, seed):
 
 def test_static_global_update_two_calls_second_smaller():
     _one_call(K=8, n=1_000_003, resnapshot=True, seed=21)
-    _one_call(K=3, n=4_098, resnapshot=False, seed=22)       # smaller; stale z beyond n must not matter
+    _one_call(K=3, n=4_098, resnapshot=False, seed=22)       # smaller: nothing of the first call remains
 
 
 def test_static_global_update_at_the_maximum_size():
-    """n = LASGD_STATIC_MAX_N exactly (the whole static buffer), K = 2, inputs drawn on the device."""
+    """n = LASGD_STATIC_MAX_N exactly, K = 2, inputs drawn on the device."""
     n, K = B.STATIC_MAX_N, 2
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(3)
