@@ -93,7 +93,11 @@ typedef struct {
     int32_t max_blocks;    /* cap on workgroups per launch (grid-stride beyond it); <0 = no cap      */
     int32_t avg_split;     /* waves of a workgroup that share one tile's K replicas in average (1,2,4) */
     int32_t avg_max_blocks;/* cap on workgroups of the average kernel; <0 = no cap                   */
-    int32_t nontemporal;   /* 1: streaming hint on loads, 2: on stores, 3: both, 4: none             */
+    int32_t nontemporal;   /* 1: streaming hint on loads, 2: on stores, 3: both, 4: none.  With a hint on, the
+                              kernels also take their streaming shapes: the step and merge kernels bound
+                              their waves per CU through LDS that they ask for and do not use (up to a CU's
+                              160 KiB among the waves of a local step), and lasgd_step_merge_average takes
+                              two kernels beyond 12 replicas.  4 switches that off too                    */
     int32_t chunk_step;    /* work-item order of local_step / snapshot: tiles are taken in chunks of this
                               many; inside a chunk replica after replica.  1 = the replicas of a tile are
                               adjacent; <0 = whole replica after whole replica                       */
@@ -106,7 +110,7 @@ typedef struct {
     int32_t group_r;       /* replicas one wave takes at a time in the one-workgroup-per-tile kernels
                               (lasgd_step_merge_average, lasgd_sgd_ar_step): 1, 2 or 4; the workgroup has
                               ceil(K / group_r) waves, at most 16; a value > 0 also keeps
-                              lasgd_step_merge_average in one kernel.  <0 = default (chosen from K)         */
+                              lasgd_step_merge_average in one kernel.  <0 = default (from K and the size)   */
 } lasgd_tuning;
 
 /*
@@ -197,8 +201,8 @@ lasgd_status lasgd_step_merge(lasgd_ctx *ctx, float lr, int32_t resnapshot);
  * exactly lasgd_step_merge(lr, 1) followed by lasgd_average, same roundings, but
  * the K replicas of each tile meet in on-chip memory, so the sent models are not
  * read back for the mean (more than 12 replicas of a model beyond the memory-side
- * cache take two kernels, which is faster there).  Everything runs on the main stream (after the pending
- * average), nothing on the side stream; afterwards the new mean counts as
+ * cache take two kernels, which is faster there).  Everything runs on the main
+ * stream (after the pending average), nothing on the side stream; afterwards the new mean counts as
  * launched, exactly as after lasgd_average.  Meant for cadences with nothing to
  * overlap the All-Reduce with (a global update every step, tau_max = 1 in Sec. 5.2).
  * Errors: as lasgd_step_merge, plus STATE when the pending average is partial or

@@ -169,11 +169,12 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // 256 MB memory-side cache.  A local step sweeps one replica after the other
 // (the longest contiguous runs); merges take the tiles in chunks of 8192 (8 MB
 // of z per chunk, 1 MB per XCD) so that the chunk's z is still in L2 when the
-// next replica needs it.  The split mean (256-thread workgroups with LDS) wins
-// from K = 8 upwards, with two groups of waves up to K = 11 and four beyond: merge + mean,
-// us at split 1 / 2 / 4: ResNet-18 K = 8 303 / 306 / 301, ResNet-50 K = 8 654 / 648 / 649,
-// step + update + mean ResNet-18 K = 10 598 / 595 / 599, K = 12 705 / 706 / 701,
-// MobileNetV2 K = 16 281 / 287 / 280, K = 24 415 / 422 / 414.
+// next replica needs it.  The mean's replicas are split over two groups of waves from
+// K = 8 and over four from K = 12 on (256-thread workgroups with LDS): merge + mean, us at
+// split 1 / 2 / 4: ResNet-50 list K = 8 664 / 655 / 656, K = 12 982 / 975 / 963, K = 16
+// 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178
+// (profiles/mean_launch_shape_sweep.txt).  The in-order mean of lasgd_step_merge_average
+// takes split 1: its z is to be that of the one-kernel form to the bit.
 lasgd_tuning default_tuning(const lasgd_ctx &c)
 {
     lasgd_tuning t{};
@@ -195,13 +196,15 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 // How many waves a CU may hold at once in the streaming kernels, set through the LDS a workgroup asks for (and does
 // not use): 160 KiB in granules of 1280 bytes.  The memory system is fastest with about 60 KiB of loads in flight per
 // CU; with all 32 waves a CU the kernels reach it through L2 misses that evict each other.  us at 0 (32 waves), 5 (25),
-// 6 (21), 7 (18), 8 (16), 10 (12) granules a wave:
-//   local step (3 KiB of loads a wave)     ResNet-50 K = 8       642  636  629  619  633    -     bf16 663  647  631  616  626  (9: 646)
-//   update and step (4 KiB, and z)         ResNet-50 K = 8 *    1078 1074 1061 1040 1034 1022     * with the mean, 150
-//   global update (2 KiB, and z)           ResNet-50 K = 8 *     667  657  647  654  678  743
-//   snapshot (1 KiB)                       ResNet-50 K = 8       252  276  285  308  336  393
-// Where the state stays in the memory-side cache (no streaming hint) nothing is gained: MobileNetV2 K = 6 60 us at any of
-// these counts.
+// 6 (21), 7 (18), 8 (16), 10 (12) granules a wave, ResNet-50 list, K = 8 (profiles/waves_in_flight_sweep.txt, with others):
+//   local step (3 KiB of loads a wave, and a word before them)   629  607  605  611  598  648     bf16 657  653  637  618  627  668
+//   step + update (4 KiB, and z), with the mean                 1088 1087 1070 1039 1030 1021
+//   global update (2 KiB, and z), with the mean                  672  660  653  657  683  754
+//   snapshot (1 KiB)                                             251  276  279  299  331  396
+// fp32 local steps take 6 and not 8: beside the mean on a second stream 21 waves were the better count.
+// Nothing is gained where the state stays in the memory-side cache (no streaming hint).
+// A caller's kernel on another stream does not wait longer for a CU: a bf16 product of 4096^3 beside local steps took
+// 643-697 us, and 650-712 when the steps held all 32 waves and no LDS.
 constexpr uint32_t kLdsGranule = 1280;
 constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
 uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)

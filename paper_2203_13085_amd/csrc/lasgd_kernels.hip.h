@@ -25,14 +25,13 @@ struct Tile {
     float wd;          // the tensor's weight decay
 };
 
-// What the kernels look up: one 16-byte record per tensor and one pointer pair per
-// (replica, tensor).  A tile's tensor is named by its block of 64 tiles; the top bit
+// What the kernels look up: one 32-byte record per (replica, tensor).  A tile's tensor is named by its block of 64 tiles; the top bit
 // says that more tensors start inside the block, and then the tile is compared with
 // the following tensors' first tiles, sixteen at a time.
 //
 // The tables are read through the scalar cache.  They are per block and per tensor
-// and not per tile (161 tensors, 10^5 tiles: 6 KB of blocks, 2.5 KB each of records
-// and pointers of one replica), so a few hundred waves in a row find them there, and
+// and not per tile (161 tensors, 10^5 tiles: 6 KB of blocks, 5.2 KB of records of
+// one replica), so a few hundred waves in a row find them there, and
 // a scalar hit does not queue behind the streaming loads of other waves as a vector
 // load does.  A record per tile, read through the vector path, made every wave wait twice
 // for the loaded memory system before its first data load: at 24 waves a CU that cost
