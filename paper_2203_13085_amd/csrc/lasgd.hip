@@ -377,8 +377,8 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     const uint32_t K = (uint32_t)c->K;
     const bool streaming = (c->tune.nontemporal & 3) != 0;
     // Replicas a wave takes at a time, us on MI355X.
-    // SGD-AR, streaming: one, with the models asked for when the gradients are there (staged), up to K = 12 and at 15 and 16;
-    // workgroups of 13 and 14 such waves leave 6 and 4 of a CU's 32 slots empty.  One / two a wave: ResNet-18 list K = 12
+    // SGD-AR, streaming: one, with the models asked for when the gradients are there (staged), up to K = 12, and beyond where
+    // two workgroups of such waves fill 30 of a CU's 32 slots or more (13 and 14 fill 26 and 28).  One / two a wave: ResNet-18 list K = 12
     // 466 / 481, 13 520 / 519, 16 630 / 698, bf16 480 / 487, 551 / 536, 662 / 695; ResNet-50 K = 13 1190 / 1170, bf16
     // 1320 / 1217.  All loads at once / staged: ResNet-18 bf16 K = 6 260 / 234, 8 320 / 311, fp32 K = 10 406 / 389, K = 16
     // 727 / 630.  Two against four: MobileNetV2 K = 24 304 / 318, K = 32 433 / 411.
@@ -389,7 +389,7 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     const bool paced = streaming && kind == 1 && K <= kOneKernelMaxK && c->tune.group_r <= 0;
     const bool at_once = (uint64_t)c->tables->ntiles * K <= kWavesOnChip;
     if (kind == 1) g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
-    else if (streaming) g.R = K <= 12u || K == 15u || K == 16u ? 1u : K <= 24u ? 2u : 4u;
+    else if (streaming) g.R = K <= 12u || (2u * K >= 30u && K <= kGroupWaves) ? 1u : K <= 24u ? 2u : 4u;
     else g.R = K <= (at_once ? kGroupWaves : 3u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     if (c->tune.group_r > 0) g.R = (uint32_t)c->tune.group_r;
     if (g.R > K) g.R = K >= 4 ? 4 : K >= 2 ? 2 : 1;

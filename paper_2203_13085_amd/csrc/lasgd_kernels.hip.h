@@ -292,8 +292,7 @@ template <bool FULL> __device__ __forceinline__ uint32_t lane_elems(uint32_t e0,
 // that have all four elements, and only the one lane that a tensor's odd end leaves
 // with one to three goes element by element: all its loads before its first store,
 // as everywhere, so that the wave waits once for memory.
-// Small ragged list, K = 3: snapshot 4.0 -> 3.1 us,
-// local step 3.4 -> 3.2.  ALONE: the operation is the whole kernel's, not one of several in a masked call.
+// ALONE: the operation is the whole kernel's, not one of several in a masked call.
 template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT, bool ALONE>
 __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const void *gu, float *xm,
                                            float *v, float *s, const float4 (&zt)[VEC], float wd,
