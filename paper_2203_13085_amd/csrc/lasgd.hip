@@ -206,6 +206,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 // A caller's kernel on another stream does not wait longer for a CU: a bf16 product of 4096^3 beside local steps took
 // 643-697 us, and 650-712 when the steps held all 32 waves and no LDS.
 constexpr uint32_t kLdsGranule = 1280;
+constexpr size_t kCuLds = 163840;
 constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
 uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
 {
@@ -1065,17 +1066,30 @@ namespace {
 
 template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hipStream_t st)
 {
-    // One wave per replica while a workgroup can hold that many (16), then two or four replicas a wave.  Measured with
-    // 1, 2, 4 replicas a wave at n = 12e6: K = 4 125, 129, 131 us, K = 8 258, 269, 273, K = 16 546, 562, 565.  Two replicas
-    // a wave win for K = 4..8 where the vectors stay in the memory-side cache and the waves are more than the chip holds
-    // at once (8192): K = 8, n = 2^19 13.8 us against 16.1, n = 600,000 13.5 against 13.9, K = 4, n = 2^20 12.4 against 14.0;
-    // below that the extra wave is free and shortens the call (K = 4, n = 300,000 4.5 against 4.9), and from K = 12 on one
-    // a wave is ahead again (n = 1,000,003 31.6 against 34.2).
-    uint32_t R = a.K <= kGroupWaves ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
-    if (NT == 0 && a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > kWavesOnChip) R = 2u;
+    size_t lds = (size_t)a.K * 256u * sizeof(float);
+    uint32_t R;                 // replicas a wave
+    if (NT != 0) {
+        // Streaming.  The memory system is fastest with about 24 replicas' rows on a CU (24 KiB of s, then 24 KiB of x), as
+        // whole workgroups: the LDS a workgroup asks for leaves room for 24 / K of them, two at least.  us over three states
+        // in turn, one replica a wave, everything at once and no bound / staged and bounded with one, two, four a wave:
+        // K = 2 131 / 125, 125; K = 3 193 / 188, 189; K = 4 267 / 252, 249, 250; K = 6 397 / 386, 382, 385; K = 8 557 / 536, 529, 529;
+        // K = 12 811 / 790, 783, 780; K = 16 1132 / 1112, 1109, 1100; K = 32 467 / -, 466, 472.  One group more or fewer on a CU costs
+        // 1-2 or 3-20 %.  Other work between the calls changes none of this (K = 8 555 / 533, 526).
+        R = a.K <= 3u ? 1u : a.K <= 2u * kGroupWaves ? (a.K == 12u || a.K == 16u ? 4u : 2u) : 4u;
+        const uint32_t groups = a.K <= 24u ? 24u / a.K : 1u;
+        const size_t pace = kCuLds / groups / kLdsGranule * kLdsGranule;
+        lds = pace > lds ? (pace < kMaxLds ? pace : kMaxLds) : lds;
+    } else {
+        // In the memory-side cache.  One wave per replica while a workgroup can hold that many (16), then two or four replicas
+        // a wave.  Two win for K = 4..8 where the waves are more than the chip holds
+        // at once (8192): K = 8, n = 2^19 13.8 us against 16.1, n = 600,000 13.5 against 13.9, K = 4, n = 2^20 12.4 against 14.0;
+        // below that the extra wave is free and shortens the call (K = 4, n = 300,000 4.5 against 4.9), and from K = 12 on one
+        // a wave is ahead again (n = 1,000,003 31.6 against 34.2).
+        R = a.K <= kGroupWaves ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
+        if (a.K >= 4u && a.K <= 8u && (uint64_t)blocks * a.K > kWavesOnChip) R = 2u;
+    }
     a.W = (a.K + R - 1u) / R;
     const dim3 bs(64u * a.W);
-    const size_t lds = (size_t)a.K * 256u * sizeof(float);
     if (R == 1u) hipLaunchKernelGGL((flat_update_kernel<1, NT>), dim3(blocks), bs, lds, st, a);
     else if (R == 2u) hipLaunchKernelGGL((flat_update_kernel<2, NT>), dim3(blocks), bs, lds, st, a);
     else hipLaunchKernelGGL((flat_update_kernel<4, NT>), dim3(blocks), bs, lds, st, a);

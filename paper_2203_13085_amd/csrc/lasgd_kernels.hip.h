@@ -700,18 +700,45 @@ template <int NT, bool FULL> __device__ __forceinline__ void row_st16(uint16_t *
     if (n > 2u) p[e0 + 2u] = (uint16_t)bf16_round(a.z);
 }
 
+// The next N rows of the exchange buffer, added to four columns' fp64 sums in replica order.  The N reads are issued
+// before the first addition: one dependent read after the other costs 130 cycles each.
+template <int N> __device__ __forceinline__ void add_rows(const float *p, double &a0, double &a1, double &a2, double &a3)
+{
+    float4 q[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) q[k] = *reinterpret_cast<const float4 *>(p + k * 256);
+#pragma unroll
+    for (int k = 0; k < N; ++k) LASGD_ACC4(q[k]);
+}
+
 // The mean of one row over its K values per element, which lie in lds[K][256]; every wave gets its lanes' columns.
 // Up to K = 8 every wave sums them itself, which saves a barrier; beyond, up to four waves finish one column per
 // thread and turn: only that thread reads the column, so the mean may replace replica 0's value in it.  SGD-AR mix,
 // bare probe, every wave / shared: K = 4 6.12 / 6.01 TB/s, K = 8 6.08 / 6.01, K = 12 6.02 / 6.09, K = 16 5.51 / 5.89.
-template <class MEAN>
+// AT_ONCE: all reads of the up to eight rows before the first addition, where few waves are on a CU to hide them.  It
+// takes 20 registers more, too many for two sixteen-wave workgroups a CU in the SGD-AR step and with four replicas a wave.
+template <bool AT_ONCE, class MEAN>
 __device__ __forceinline__ float4 row_mean(float *lds, uint32_t K, uint32_t W, uint32_t lane, MEAN mean_of)
 {
     if (K <= 8u) {
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (uint32_t k = 0; k < K; ++k) {
-            const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + lane * 4u);
-            LASGD_ACC4(q);
+        if constexpr (AT_ONCE) {
+            const float *p = lds + lane * 4u;
+            switch (K) {
+            case 1: add_rows<1>(p, a0, a1, a2, a3); break;
+            case 2: add_rows<2>(p, a0, a1, a2, a3); break;
+            case 3: add_rows<3>(p, a0, a1, a2, a3); break;
+            case 4: add_rows<4>(p, a0, a1, a2, a3); break;
+            case 5: add_rows<5>(p, a0, a1, a2, a3); break;
+            case 6: add_rows<6>(p, a0, a1, a2, a3); break;
+            case 7: add_rows<7>(p, a0, a1, a2, a3); break;
+            default: add_rows<8>(p, a0, a1, a2, a3); break;
+            }
+        } else {
+            for (uint32_t k = 0; k < K; ++k) {
+                const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + lane * 4u);
+                LASGD_ACC4(q);
+            }
         }
         return make_float4(mean_of(a0), mean_of(a1), mean_of(a2), mean_of(a3));
     }
@@ -850,7 +877,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             if (kw[r] < a.K) *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = g[r];
     }
     __syncthreads();
-    const float4 gbar = row_mean(lds, a.K, W, lane, [&a](double acc) { return group_mean_of(acc, a); });
+    const float4 gbar = row_mean<false>(lds, a.K, W, lane, [&a](double acc) { return group_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(step_elem(comp(x[r], c), comp(v[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
@@ -1008,13 +1035,14 @@ __global__ __launch_bounds__(256) void poison_kernel(float *z, uint64_t n)
 // pass.  Same arithmetic and rounding order as the kernels above; replica
 // pointers travel in the kernel arguments.
 //
-// Bound by HBM.  One workgroup per 256 elements and one wave per replica (R of
-// them beyond 16 replicas): s and x are read once, the K values of s meet in
+// Bound by HBM.  One workgroup per 256 elements, R replicas a wave: s and x are read once, the K values of s meet in
 // LDS, and z stays on the chip, so a replica-parameter moves 16 bytes where a
-// mean kernel followed by an update kernel moves 20 and z on top.
-// Measured, K = 8: n = 25,557,032 554 us = 5.9 TB/s (the two kernels: 871 us), n = 300,000
-// 8.3 us (14.2), n = 1000 3.3 us (5.9: one launch instead of two); K = 64, n = 3,000,000
-// 609 us (735).
+// mean kernel followed by an update kernel moves 20 and z on top.  Where the vectors stream (NT), x is asked for when s
+// has arrived, and flies while s goes round through LDS, so that a wave puts half of its 2 KiB a replica in flight at a time.
+// launch_flat_update holds the shape's rule and what it measured.
+// n = 25,000,000, us over three states in turn (before: one replica a wave, both loads at once, as many groups as fit): K = 8 511
+// = 6.3 TB/s (542), K = 4 248 (264), K = 12 787 (814).  n = 300,000, K = 8 8.3 (a mean kernel and an update kernel: 14.2).
+// Pointers of x and s side by side, one 16-byte scalar load a replica, were 2-4 % slower in the cache (n = 10^6, K = 6 17.4 / 18.0).
 struct FlatArgs {
     float *x[64];       // local models, n elements each
     float *s[64];       // sent models
@@ -1046,13 +1074,18 @@ __device__ __forceinline__ void flat_update_row(const FlatArgs &a, float *lds, u
         sp[r] = a.s[mine[r] ? kw : a.K - 1u] + first;
         xp[r] = a.x[mine[r] ? kw : a.K - 1u] + first;
         ss[r] = row_ld<NT, FULL>(sp[r], e0, n);
-        x[r] = row_ld<NT, FULL>(xp[r], e0, n);
+        if constexpr (NT == 0) x[r] = row_ld<NT, FULL>(xp[r], e0, n);
+    }
+    if constexpr (NT != 0) {
+        wait_for_loads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = row_ld<NT, FULL>(xp[r], e0, n);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (mine[r]) *reinterpret_cast<float4 *>(lds + (size_t)(w + (uint32_t)r * W) * 256u + e0) = ss[r];
     __syncthreads();
-    const float4 z = row_mean(lds, a.K, W, lane, [&a](double acc) { return flat_mean_of(acc, a); });
+    const float4 z = row_mean<(NT != 0 && R < 4)>(lds, a.K, W, lane, [&a](double acc) { return flat_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(comp(x[r], c) = merge_elem(compv(x[r], c), compv(ss[r], c), compv(z, c));)

@@ -150,3 +150,31 @@ def test_static_global_update_every_group_shape(K):
                 np.testing.assert_array_equal(_bits(gs[k, :n]), _bits(orc.s[k]), err_msg=f"sent replica {k}")
             np.testing.assert_array_equal(_bits(gx[:, n:n + 8]), _bits(hx[:, n:]))
             np.testing.assert_array_equal(_bits(gs[:, n:n + 8]), _bits(hs[:, n:]))
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 33, 64])
+def test_static_global_update_streaming_shapes(K):
+    """Vectors beyond the memory-side cache take shapes of their own: replicas a wave, and workgroups a CU through the LDS
+    they ask for.  Same roundings: the fp64 sum in replica order, one division, one rounding to fp32, then z + (x - s)."""
+    n = (32 << 20) // K + 259                                # K n floats: just over 128 MiB; an odd last tile
+    gen = torch.Generator(device="cuda:0").manual_seed(K)
+    pad = (n + 3) // 4 * 4
+    x = torch.randn(K, pad, generator=gen, device="cuda:0")
+    s = torch.randn(K, pad, generator=gen, device="cuda:0")
+    if K == 1:
+        n = B.STATIC_MAX_N                                   # the longest vector the call takes
+    acc = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    for k in range(K):
+        acc += s[k, :n].double()
+    z = (acc / K).float()
+    want = torch.stack([z + (x[k, :n] - s[k, :n]) for k in range(K)])
+    behind = (x[:, n:].clone(), s[:, n:].clone())
+    torch.cuda.synchronize()
+    say(f"[no-alloc] streaming K={K} n={n}")
+    B.global_update_static([t.data_ptr() for t in x], [t.data_ptr() for t in s], n, True)
+    torch.cuda.synchronize()
+    assert torch.equal(x[:, :n].view(torch.int32), want.view(torch.int32))
+    assert torch.equal(s[:, :n].view(torch.int32), want.view(torch.int32))
+    assert torch.equal(x[:, n:], behind[0]) and torch.equal(s[:, n:], behind[1])
+    del x, s, acc, z, want
+    torch.cuda.empty_cache()
