@@ -208,15 +208,23 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 constexpr uint32_t kLdsGranule = 1280;
 constexpr size_t kCuLds = 163840;
 constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
+// Step + update asks for a word of its model before its loads, as the fp32 local step always does, and then runs 16 waves a CU in
+// place of 12, up to 1e8 replica-parameters.  A pass's us without / with, over three states in turn (and with other work between
+// the passes): MobileNetV2 list K = 16, every step 285 / 280 (287 / 290), with m = 2 456 / 449 (460 / 455), partial rounds 411 / 402 (422 / 416);
+// ResNet-18 K = 8 (9.4e7), adaptive rounds 826 / 818 (847 / 841), K = 4, m = 4 671 / 663; ResNet-50 K = 4 (1.0e8), m = 2 844 / 846 (863 / 862).
+// Beyond, ResNet-18 K = 24, m = 3 3858 / 3882, ResNet-50 K = 8, m = 4 2868 / 2876.  Two or three words gain on the fp32 step in a loop of
+// nothing but steps, from what the last step left in the memory-side cache, and lose 0.3-1.3 % with other work between.
+bool word_first(int op, uint64_t replica_params) { return op == OP_STEP_MERGE && replica_params <= 100000000u; }
 uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
 {
     if (!(nt & 3)) return 0;
-    uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? 10u : 0u;
+    const uint32_t step_merge = nt & 4 ? 8u : 10u;        // with a word first, and without
+    uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? step_merge : 0u;
     if (xa && op == OP_STEP_MERGE) {         // replicas that only step or only merge load less: the mean over the waves
         const uint32_t both = (uint32_t)__builtin_popcountll(xa->step_mask & xa->merge_mask);
         const uint32_t step = (uint32_t)__builtin_popcountll(xa->step_mask & ~xa->merge_mask);
         const uint32_t merge = (uint32_t)__builtin_popcountll(xa->merge_mask & ~xa->step_mask);
-        granules = (10u * both + 7u * step + 6u * merge) / (both + step + merge);
+        granules = (step_merge * both + 7u * step + 6u * merge) / (both + step + merge);
     }
     const uint32_t bytes = granules * kLdsGranule * vec * waves_per_block;
     return bytes < kMaxLds ? bytes : (uint32_t)kMaxLds;
@@ -227,9 +235,21 @@ hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, 
 {
     const uint32_t lds = pace_lds(OP, BF16, xa, nt, VEC, bs.x / 64u);
     if (xa) {      // extended variants: hints all on or all off
+        if constexpr (VEC == 1 && OP == OP_STEP_MERGE) {
+            if (nt == 7) {
+                hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 7>), grid, bs, lds, st, a, *xa);
+                return hipGetLastError();
+            }
+        }
         if (nt & 3) hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 3>), grid, bs, lds, st, a, *xa);
         else hipLaunchKernelGGL((apply_ext_kernel<VEC, OP, BF16, 0>), grid, bs, lds, st, a, *xa);
         return hipGetLastError();
+    }
+    if constexpr (VEC == 1 && OP == OP_STEP_MERGE) {
+        if (nt == 7) {
+            hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 7>), grid, bs, lds, st, a);
+            return hipGetLastError();
+        }
     }
     switch (nt & 3) {
     case 0: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 0>), grid, bs, lds, st, a); break;
@@ -337,7 +357,9 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
 lasgd_status launch_apply(lasgd_ctx *c, const ApplyPlan &p)
 {
     const bool bf16 = c->storage == LASGD_BF16;
-    const int vec = c->tune.vec, nt = c->tune.nontemporal;
+    const int vec = c->tune.vec;
+    int nt = c->tune.nontemporal;
+    if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad)) nt |= 4;
     const ExtArgs *xa = p.has_ext ? &p.ext : nullptr;
     hipError_t e = hipSuccess;
     switch (p.op) {

@@ -104,6 +104,7 @@ struct ExtArgs {
 };
 
 // ---- 128-bit / 64-bit accesses, optionally with the streaming hint --------
+// NT: 1 the hint on loads, 2 on stores; 4 belongs to the kernels that ask for a word of their model before their loads.
 // Every pointer the kernels dereference is device (global) memory.  Pointers
 // that come out of the tables are generic as far as the compiler can tell and
 // would be accessed with FLAT instructions; casting to the global address
@@ -329,8 +330,8 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     // come: the busier the memory, the later.  us, with 18 waves a CU (pace_lds) / with 21 and this word: ResNet-18 list
     // K = 8 283 / 273, ResNet-50 K = 8 621 / 594, K = 24 1901 / 1863, K = 32 2495 / 2493, MobileNetV2 K = 16 172 / 165.
     // bf16 gains below 3e8 replica-parameters (ResNet-50 K = 8 622 / 607) and loses beyond (ResNet-18 K = 32 1140 / 1156,
-    // ResNet-50 K = 32 2478 / 2492), so it goes without; so do the steps inside a masked step_merge.
-    if constexpr (ALONE && OP == OP_STEP && !BF16 && FULL && (NT & 3) != 0) wait_for_word(xf);
+    // ResNet-50 K = 32 2478 / 2492), so it goes without.  Step + update, masked or not, asks where NT says so (word_first).
+    if constexpr (FULL && ((ALONE && OP == OP_STEP && !BF16 && (NT & 3) != 0) || (NT & 4) != 0)) wait_for_word(xf);
     // all loads first: up to 4*VEC independent 128-bit loads in flight per lane
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {

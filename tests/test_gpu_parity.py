@@ -524,3 +524,12 @@ def test_tensor_lookup_at_probe_edges(tensors):
     """Lists that one probe of sixteen holds whole, and the first that it does not; all in the first block of tiles."""
     w = W.small(K=2, numels=[(256, 1, 3)[i % 3] for i in range(tensors)], m=1, T=2)
     run_parity(w, weight_decay=[1e-4 * (i % 7) for i in range(tensors)])
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("K,vec", [(1, 1), (5, 1), (16, 1), (5, 2)])
+def test_streaming_step_merge_with_a_word_first(storage, K, vec):
+    """The streaming form of step + update for lists of this size asks for a word of its model before its loads (tiles of
+    256 elements): a tensor of one full tile, ones around it, and several tiles with a ragged end.  vec = 2: the form without."""
+    w = W.small(K=K, numels=(256, 255, 257, 1, 4099), storage=storage, m=2, T=5)
+    run_parity(w, tuning=dict(nontemporal=3, vec=vec))
