@@ -154,6 +154,14 @@ lasgd_status lasgd_init_master(lasgd_ctx *ctx);
 lasgd_status lasgd_local_step(lasgd_ctx *ctx, float lr);
 
 /*
+ * Every bound gradient buffer of every replica to zero, in one launch: what a training loop does before the backward
+ * passes accumulate into them.  stream: hipStream_t the backward passes run on (NULL = default stream); ordering
+ * against the main stream, which reads the gradients, is the caller's.  Changes no state of the context.
+ * Errors: STATE (a replica is unbound), HIP.
+ */
+lasgd_status lasgd_zero_grads(lasgd_ctx *ctx, void *stream);
+
+/*
  * The send of Algorithm 1 (steps 4 and 9c): the model handed to the All-Reduce is
  * kept, s[k] <- x[k].  Main stream.
  * Errors: STATE (an average is in flight and not yet merged: the side stream

@@ -27,7 +27,8 @@ EXPORTS = ["lasgd_create", "lasgd_bind", "lasgd_init_master", "lasgd_local_step"
            "lasgd_read_state", "lasgd_sync", "lasgd_set_tuning", "lasgd_get_tuning",
            "lasgd_last_error", "lasgd_destroy", "lasgd_local_step_ex", "lasgd_snapshot_ex",
            "lasgd_average_ex", "lasgd_merge_ex", "lasgd_step_merge_ex", "lasgd_set_elastic",
-           "lasgd_sgd_ar_step", "lasgd_global_update_static", "lasgd_step_merge_average"]
+           "lasgd_sgd_ar_step", "lasgd_global_update_static", "lasgd_step_merge_average",
+           "lasgd_zero_grads"]
 
 
 class LasgdError(RuntimeError):
@@ -73,6 +74,7 @@ def load() -> ctypes.CDLL:
     L.lasgd_init_master.argtypes = [P]
     L.lasgd_local_step.argtypes = [P, f32]
     L.lasgd_snapshot.argtypes = [P]
+    L.lasgd_zero_grads.argtypes = [P, P]
     L.lasgd_average.argtypes = [P]
     L.lasgd_average_done.argtypes = [P, ctypes.POINTER(i32)]
     L.lasgd_merge.argtypes = [P, i32]
@@ -145,6 +147,7 @@ class Context:
         if st != OK:
             raise LasgdError(st, self._L.lasgd_last_error(None).decode())
         self._h = h
+        self.bound_grads = [None] * self.K        # per replica: the gradient addresses in effect (a ctypes array)
 
     # -- plumbing ---------------------------------------------------------
     def _check(self, st: int) -> None:
@@ -170,12 +173,17 @@ class Context:
         pa = (ctypes.c_void_p * n)(*params)
         ga = (ctypes.c_void_p * n)(*grads)
         self._check(self._L.lasgd_bind(self._h, k, pa, ga))
+        self.bound_grads[k] = ga
 
     def init_master(self) -> None:
         self._check(self._L.lasgd_init_master(self._h))
 
     def local_step(self, lr: float) -> None:
         self._check(self._L.lasgd_local_step(self._h, lr))
+
+    def zero_grads(self, stream: Optional[int] = None) -> None:
+        """Every bound gradient buffer to zero, on `stream` (a raw handle; None = the default stream)."""
+        self._check(self._L.lasgd_zero_grads(self._h, stream or None))
 
     def snapshot(self) -> None:
         self._check(self._L.lasgd_snapshot(self._h))

@@ -833,6 +833,31 @@ lasgd_status lasgd_local_step_ex(lasgd_ctx *c, const float *lr, uint64_t mask)
     return do_local_step(c, lr, 0.f, mask);
 }
 
+lasgd_status lasgd_zero_grads(lasgd_ctx *c, void *stream)
+{
+    if (!c) return LASGD_ERR_INVALID;
+    if (c->n_bound != c->K) return fail(c, LASGD_ERR_STATE, "%d of %d replicas are bound", c->n_bound, c->K);
+    ApplyArgs a{};
+    fill_common(c, a);
+    a.chunk = a.ntiles;
+    a.by_chunk = make_div(a.ntiles);
+    a.nitems = a.ntiles * a.K;           // upload_tables refuses more than 2^31 / 64 tiles
+    a.nwaves = c->tune.max_blocks > 0 && a.nitems > (uint32_t)c->tune.max_blocks ? (uint32_t)c->tune.max_blocks : a.nitems;
+    const dim3 grid(a.nwaves), bs(64);
+    const hipStream_t st = (hipStream_t)stream;
+    const bool hint = (c->tune.nontemporal & 2) != 0;
+    if (c->storage == LASGD_BF16) {
+        if (hint) hipLaunchKernelGGL((zero_grads_kernel<true, 2>), grid, bs, 0, st, a);
+        else hipLaunchKernelGGL((zero_grads_kernel<true, 0>), grid, bs, 0, st, a);
+    } else {
+        if (hint) hipLaunchKernelGGL((zero_grads_kernel<false, 2>), grid, bs, 0, st, a);
+        else hipLaunchKernelGGL((zero_grads_kernel<false, 0>), grid, bs, 0, st, a);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    return LASGD_OK;
+}
+
 lasgd_status lasgd_snapshot(lasgd_ctx *c)
 {
     if (!c) return LASGD_ERR_INVALID;

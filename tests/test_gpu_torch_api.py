@@ -88,3 +88,61 @@ def test_zero_grad_clears_every_gradient_in_place():
             opt.zero_grad()
     finally:
         opt.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("hint", [3, 4])
+def test_zero_grad_clears_every_bound_gradient_and_nothing_else(dtype, hint):
+    """One launch over the records: tensors around a tile's 256 elements and a lane's four, several tensors in a block of
+    tiles; what lies behind a gradient's end stays."""
+    from paper_2203_13085_amd.torch_api import LASGD
+    numels = [1, 3, 4, 5, 255, 256, 257, 1030, 2, 70001]
+    dev, guard = torch.device("cuda:0"), 8
+    nets, slabs = [], []
+    for k in range(3):
+        net = torch.nn.Module()
+        net.ps = torch.nn.ParameterList([torch.nn.Parameter(torch.zeros(n, device=dev, dtype=dtype)) for n in numels])
+        for p in net.ps:
+            slab = torch.full((p.numel() + guard,), 7.0, device=dev, dtype=dtype)
+            p.grad = slab[:p.numel()]
+            slabs.append(slab)
+        nets.append(net)
+    opt = LASGD(nets, lr=0.1)
+    try:
+        opt.ctx.set_tuning(nontemporal=hint)
+        before = [p.grad._version for p in opt._flat]
+        for _ in range(2):
+            opt.zero_grad()
+            torch.cuda.synchronize()
+            for slab, p in zip(slabs, opt._flat):
+                assert not p.grad.any() and bool((slab[p.numel():] == 7.0).all())
+            for slab in slabs:
+                slab.fill_(7.0)
+        assert all(p.grad._version > v for p, v in zip(opt._flat, before))
+        # a gradient elsewhere: cleared where it is now, as before; the bound buffer is not touched
+        moved = torch.full_like(opt._flat[5], 3.0)
+        opt._flat[5].grad = moved
+        opt.zero_grad()
+        torch.cuda.synchronize()
+        assert not moved.any() and bool((slabs[5] == 7.0).all()) and not opt._flat[4].grad.any()
+        opt._flat[5].grad = None
+        with pytest.raises(AttributeError):
+            opt.zero_grad()
+        with pytest.raises(AssertionError):
+            opt.step()
+    finally:
+        opt.close()
+
+
+def test_zero_grad_is_seen_by_a_graph_that_saved_the_gradient():
+    from paper_2203_13085_amd.torch_api import LASGD
+    net = torch.nn.Linear(8, 8, device="cuda:0")
+    opt = LASGD([net], lr=0.1)
+    try:
+        w = torch.ones(8, device="cuda:0", requires_grad=True)
+        y = (net.bias.grad * w).sum()                       # saves the gradient for w's backward
+        opt.zero_grad()
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            y.backward()
+    finally:
+        opt.close()
