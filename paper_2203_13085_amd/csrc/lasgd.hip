@@ -5,6 +5,7 @@
 // keeps computing", Sec. 4):
 //   main stream:  local_step ... snapshot/merge --evA--> ...        wait evZ, merge
 //   side stream:                          wait evA, average --evZ-->
+// (a mean that is over before the events around it would be stays on the main stream, see mean_on_main)
 // evA orders the side stream's reads of s after the main stream's writes;
 // evZ orders the main stream's reads of z after the side stream's writes.
 // The state machine refuses call orders in which s or z could be overwritten
@@ -757,6 +758,16 @@ static bool is_capturing(hipStream_t st)
     return cs != hipStreamCaptureStatusNone;
 }
 
+// A mean on the side stream costs the host an event, a wait, an event and a wait, about 20 us, and both streams their waits.
+// One that moves no more than 16 MiB is done in 3 to 6 us, so it stays on the main stream.  A cycle's us on two streams /
+// on one: K = 3, m = 2, 5000 elements 31 / 11, 10^5 31 / 13, 4e5 (6.4 MB) 38 / 19, 10^6 (16 MB) 40 / 32; K = 8, m = 4, 4e5 (14 MB) 56 / 53;
+// K = 32, m = 4, 10^5 (13 MB) 56 / 53.  Beyond: K = 8, m = 4, 10^6 (36 MB) 123 / 124.  With other work between the calls a longer mean is
+// worth hiding behind it.
+static bool mean_on_main(uint32_t participants, uint64_t npad)
+{
+    return (participants + 1ull) * npad * sizeof(float) <= (16ull << 20);
+}
+
 static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)
 {
     // every refusal comes before the first event or launch
@@ -765,27 +776,29 @@ static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)
     if (c->pending_mask) return fail(c, LASGD_ERR_STATE, "the previous average has not been merged by all its participants");
     if (mask & ~c->snap_mask) return fail(c, LASGD_ERR_STATE, "no snapshot to average for some of these replicas");
     const bool captured = is_capturing(c->main);
-    if (c->side != c->main) {
+    const bool on_main = c->side == c->main || mean_on_main((uint32_t)__builtin_popcountll(mask), c->npad);
+    const hipStream_t stream = on_main ? c->main : c->side;
+    if (!on_main) {
         LASGD_HIP(c, hipEventRecord(c->evA, c->main));
         LASGD_HIP(c, hipStreamWaitEvent(c->side, c->evA, 0));
     }
     // the first mean initialises the centre: there is no earlier z to blend with
     const bool elastic = c->beta != 1.f && c->center_valid;
     if (c->tune.race_probe > 0 && !elastic) {
-        // debugging aid: z is poisoned on the side stream just before the mean rewrites it
-        hipLaunchKernelGGL(poison_kernel, dim3(1024), dim3(256), 0, c->side, c->z, c->npad);
+        // debugging aid: z is poisoned on the mean's stream just before the mean rewrites it
+        hipLaunchKernelGGL(poison_kernel, dim3(1024), dim3(256), 0, stream, c->z, c->npad);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "poison launch failed: %s", hipGetErrorString(e));
     }
-    st = enqueue_average(c, mask, elastic, c->side, c->tune.avg_split);
+    st = enqueue_average(c, mask, elastic, stream, c->tune.avg_split);
     if (st != LASGD_OK) return st;
-    // from here on the side stream reads s and writes z: the state says so even if the event below fails
+    // from here on that stream reads s and writes z: the state says so even if the event below fails
     c->pending_mask = mask;
     c->avg_ever = true;
     c->center_valid = true;
     c->avg_in_graph = captured;
-    c->z_on_main = c->side == c->main;
-    LASGD_HIP(c, hipEventRecord(c->evZ, c->side));
+    c->z_on_main = on_main;
+    LASGD_HIP(c, hipEventRecord(c->evZ, stream));
     return LASGD_OK;
 }
 

@@ -359,3 +359,34 @@ def test_only_the_named_replicas_are_touched(K, step_mask, merge_mask, hint):
                 assert_close(dev.ctx.read_state(B.STATE_S, k), one.s[0], f"s replica {k}")
         finally:
             dev.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_means_that_change_streams_from_round_to_round(storage):
+    """K = 8, 500,003 elements: a mean over all replicas moves 18 MB and takes the side stream, one over three moves 8 MB and
+    stays on the main stream.  Rounds of both kinds and both call forms follow each other without a host wait; the poll
+    answers for either."""
+    w = W.small(K=8, numels=(500_003,), storage=storage, m=1, T=1)
+    orc, dev, grads = _pair(w)
+    c = dev.ctx
+    full = (1 << w.K) - 1
+    try:
+        c.set_tuning(avg_split=1, race_probe=1)                # the in-order mean; z is poisoned before each
+        g = grads(0)
+        dev.load_grads(g)                                      # one gradient set for every step
+        orc.local_step(g, w.lr); c.local_step(w.lr)
+        orc.snapshot(); c.snapshot()
+        for mask in (full, 0b00000111, full, 0b10010001, 0b01100000, full, full, 0b00001110, full):
+            orc.average(mask=mask); c.average_ex(mask)
+            orc.local_step(g, w.lr); c.local_step(w.lr)
+            if mask == 0b10010001:
+                orc.merge(True, mask=mask); c.merge_ex(mask, True)
+            else:
+                orc.local_step(g, w.lr)
+                orc.merge(True, mask=mask)
+                c.step_merge_ex([w.lr] * w.K, full, mask, True)
+        c.sync()
+        assert c.average_done()
+        compare_state(dev, orc, 0)
+    finally:
+        dev.close()
