@@ -97,7 +97,9 @@ typedef struct {
                               kernels also take their streaming shapes: the step and merge kernels bound
                               their waves per CU through LDS that they ask for and do not use (up to a CU's
                               160 KiB among the waves of a local step), and lasgd_step_merge_average takes
-                              two kernels beyond 12 replicas.  4 switches that off too                    */
+                              two kernels beyond 12 replicas.  4 switches that off too.  Until it is set, each call
+                              decides by the size of its arrays (read back: what the steps, updates and
+                              the mean take); once set, it holds for every call                           */
     int32_t chunk_step;    /* work-item order of local_step / snapshot: tiles are taken in chunks of this
                               many; inside a chunk replica after replica.  1 = the replicas of a tile are
                               adjacent; <0 = whole replica after whole replica                       */

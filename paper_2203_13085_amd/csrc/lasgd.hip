@@ -77,6 +77,8 @@ struct lasgd_ctx {
     float alpha = 1.f, beta = 1.f;   // elastic coefficients (Sec. 3, Eq. 5-6); 1, 1 = Algorithm 1
 
     lasgd_tuning tune{};
+    bool hint_asked = false;         // the caller has set tune.nontemporal: it holds for every call
+    bool fused_cycle = false;        // the pending mean was made by lasgd_step_merge_average: the steps in between go by its rule
     std::string err;
 };
 
@@ -166,8 +168,7 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // tile (one 128-bit vector per lane), one wave per (tile, replica), a grid that
 // covers all items in one-wave workgroups (the waves are independent, and
 // single-wave groups dispatch and retire with the least friction), and the
-// streaming hint on every access except z once the state no longer fits the
-// 256 MB memory-side cache.  A local step sweeps one replica after the other
+// streaming hint on every access except z from the sizes of hint_of on.  A local step sweeps one replica after the other
 // (the longest contiguous runs); merges take the tiles in chunks of 8192 (8 MB
 // of z per chunk, 1 MB per XCD) so that the chunk's z is still in L2 when the
 // next replica needs it.  The mean's replicas are split over two groups of waves from
@@ -176,6 +177,29 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178
 // (profiles/mean_launch_shape_sweep.txt).  The in-order mean of lasgd_step_merge_average
 // takes split 1: its z is to be that of the one-kernel form to the bit.
+//
+// From which size of one array of all replicas (x, v, s or the gradients) on a call takes the streaming hint.  The 256 MB
+// memory-side cache would hold three or four arrays of 64 MB, but only for a program that calls nothing else: us without / with
+// the hint, in a loop over one state | over three states in turn | with 1 GiB of other work between the passes.
+//   cycle, m = 2, K = 4, 16 MB an array    39 / 41    40 / 45    53 / 48       bf16, 24 MB   56 / 58    60 / 62    73 / 65
+//                        24 MB             56 / 56    60 / 60    75 / 64             32 MB   73 / 74    82 / 79    89 / 82
+//                        32 MB             73 / 73    81 / 77    92 / 80             72 MB  160 / 158  167 / 162  180 / 168
+//                        53 MB            112 / 115  124 / 118  146 / 124     MobileNetV2 list, K = 8, 112 MB      268 / 228
+//                       104 MB            234 / 218  246 / 219  259 / 227     ResNet-18 list, K = 2, 94 MB         231 / 198
+//   sgd_ar_step, K = 4, 32 MB              26 / 27    28 / 29    41 / 32       K = 8, 112 MB  89 / 99   112 / 95   121 / 98
+//                       53 MB              41 / 43    54 / 46    64 / 48       bf16 K = 5, 70 MB 55 / 62   72 / 63    77 / 66
+//   step_merge_average, K = 4, 53 MB      201 / 223  210 / 226  226 / 232     K = 8, 112 MB  456 / 480   468 / 462  479 / 473
+// Local steps between two fused updates go by the fused update's line (with the hint of a cycle's, K = 4, 53 MB, m = 2 208 / 218 us).
+// Gradients just cleared are written to next, so zero_grads keeps them in the cache as long as they may fit.
+enum Use { USE_CYCLE, USE_SGD_AR, USE_FUSED, USE_ZERO };
+int hint_of(const lasgd_ctx *c, Use use)
+{
+    if (c->hint_asked) return c->tune.nontemporal;
+    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
+    const uint64_t from = use == USE_CYCLE ? 28ull << 20 : use == USE_SGD_AR ? 40ull << 20 : 128ull << 20;
+    return array >= from ? 3 : 0;
+}
+
 lasgd_tuning default_tuning(const lasgd_ctx &c)
 {
     lasgd_tuning t{};
@@ -185,7 +209,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.max_blocks = -1;
     t.avg_split = c.K >= 12 ? 4 : c.K >= 8 ? 2 : 1;
     t.avg_max_blocks = -1;
-    t.nontemporal = ((uint64_t)c.K * c.npad * sizeof(float) >= (128ull << 20)) ? 3 : 0;
+    t.nontemporal = hint_of(&c, USE_CYCLE);
     t.waves_per_block = 1;
     t.chunk_step = -1;
     t.chunk_merge = 8192;
@@ -359,7 +383,7 @@ lasgd_status launch_apply(lasgd_ctx *c, const ApplyPlan &p)
 {
     const bool bf16 = c->storage == LASGD_BF16;
     const int vec = c->tune.vec;
-    int nt = c->tune.nontemporal;
+    int nt = hint_of(c, p.op == OP_STEP && c->fused_cycle ? USE_FUSED : USE_CYCLE);
     if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad)) nt |= 4;
     const ExtArgs *xa = p.has_ext ? &p.ext : nullptr;
     hipError_t e = hipSuccess;
@@ -399,7 +423,7 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
 {
     GroupShape g{};
     const uint32_t K = (uint32_t)c->K;
-    const bool streaming = (c->tune.nontemporal & 3) != 0;
+    const bool streaming = (hint_of(c, kind == 0 ? USE_SGD_AR : USE_FUSED) & 3) != 0;
     // Replicas a wave takes at a time, us on MI355X.
     // SGD-AR, streaming: one, with the models asked for when the gradients are there (staged), up to K = 12, and beyond where
     // two workgroups of such waves fill 30 of a CU's 32 slots or more (13 and 14 fill 26 and 28).  One / two a wave: ResNet-18 list K = 12
@@ -514,7 +538,7 @@ lasgd_status enqueue_average(lasgd_ctx *c, uint64_t mask, bool elastic, hipStrea
     a.blocks = (uint32_t)blocks;
     a.threads = split == 1 ? bs1 : 256u;
     const dim3 grid((uint32_t)blocks);
-    const bool nt = (c->tune.nontemporal & 1) != 0;
+    const bool nt = (hint_of(c, USE_CYCLE) & 1) != 0;
     const bool ext = elastic || mask != c->all;
     hipError_t e = ext ? launch_average<true>(a, grid, stream, split, nt, bs1) : launch_average<false>(a, grid, stream, split, nt, bs1);
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "average launch failed: %s", hipGetErrorString(e));
@@ -797,6 +821,7 @@ static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)
     c->avg_ever = true;
     c->center_valid = true;
     c->avg_in_graph = captured;
+    c->fused_cycle = false;
     c->z_on_main = on_main;
     LASGD_HIP(c, hipEventRecord(c->evZ, stream));
     return LASGD_OK;
@@ -858,7 +883,7 @@ lasgd_status lasgd_zero_grads(lasgd_ctx *c, void *stream)
     a.nwaves = c->tune.max_blocks > 0 && a.nitems > (uint32_t)c->tune.max_blocks ? (uint32_t)c->tune.max_blocks : a.nitems;
     const dim3 grid(a.nwaves), bs(64);
     const hipStream_t st = (hipStream_t)stream;
-    const bool hint = (c->tune.nontemporal & 2) != 0;
+    const bool hint = (hint_of(c, USE_ZERO) & 2) != 0;
     if (c->storage == LASGD_BF16) {
         if (hint) hipLaunchKernelGGL((zero_grads_kernel<true, 2>), grid, bs, 0, st, a);
         else hipLaunchKernelGGL((zero_grads_kernel<true, 0>), grid, bs, 0, st, a);
@@ -954,7 +979,7 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     fill_common(c, a);
     a.neg_lr = -lr;
     const GroupShape g = group_shape(c, 0);
-    hipError_t e = launch_group(0, a, g, c->main, c->storage == LASGD_BF16, c->tune.nontemporal);
+    hipError_t e = launch_group(0, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_SGD_AR));
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     return LASGD_OK;
 }
@@ -970,7 +995,7 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
     if (c->alpha != 1.f || c->beta != 1.f)
         return fail(c, LASGD_ERR_STATE, "elastic coefficients are set: use lasgd_step_merge and lasgd_average");
     const bool captured = is_capturing(c->main);
-    if (c->K > (int32_t)kOneKernelMaxK && (c->tune.nontemporal & 3) && c->tune.group_r <= 0) {
+    if (c->K > (int32_t)kOneKernelMaxK && (hint_of(c, USE_FUSED) & 3) && c->tune.group_r <= 0) {
         // Streaming from 13 replicas on, workgroups that hold all replicas of a tile lose more to their shape than the
         // second pass over s costs: update, then the in-order mean.  us, one kernel / two: K = 12 ResNet-18
         // 667 / 706, bf16 697 / 716, ResNet-50 bf16 1542 / 1563, MobileNetV2 bf16 217 / 216; K = 13 737 / 765, 768 / 776,
@@ -989,7 +1014,7 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         a.resnap = 1;
         const GroupShape g = group_shape(c, 1);
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
-        hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, c->tune.nontemporal);
+        hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_FUSED));
         if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     }
     // every replica has merged and re-sent, and the mean of the sent models is (being) written to z
@@ -997,6 +1022,7 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
     c->snap_mask = c->all;
     c->pending_mask = c->all;
     c->avg_in_graph = captured;
+    c->fused_cycle = true;
     c->z_on_main = true;
     LASGD_HIP(c, hipEventRecord(c->evZ, c->main));
     return LASGD_OK;
@@ -1083,6 +1109,7 @@ static lasgd_status set_tuning_impl(lasgd_ctx *c, const lasgd_tuning *t)
         if (st != LASGD_OK) return st;
     }
     c->tune = n;
+    if (t->nontemporal) c->hint_asked = true;
     return LASGD_OK;
 }
 

@@ -390,3 +390,30 @@ def test_means_that_change_streams_from_round_to_round(storage):
         compare_state(dev, orc, 0)
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("K,n", [(1, 7_400_003), (4, 1_900_001), (4, 2_700_001)])
+def test_calls_on_both_sides_of_the_hints_lines(K, n, storage):
+    """From 28, 40 and 128 MiB an array on, steps / updates / means, the SGD-AR step and the fused update stream; the calls
+    mix on one context (28 and 30 MiB, 29 and 41): the same results whichever form each takes."""
+    w = W.small(K=K, numels=(n, 129), storage=storage, m=1, T=1)
+    orc, dev, grads = _pair(w)
+    c = dev.ctx
+    try:
+        c.set_tuning(avg_split=1)
+        g = grads(0)
+        dev.load_grads(g)
+        orc.sgd_ar_step(g, w.lr); c.sgd_ar_step(w.lr)
+        orc.snapshot(); c.snapshot()
+        orc.average(); c.average()
+        orc.local_step(g, w.lr); orc.merge(True); c.step_merge(w.lr, True)
+        orc.average(); c.average()
+        for _ in range(2):
+            orc.local_step(g, w.lr); c.local_step(w.lr)
+            orc.local_step(g, w.lr); orc.merge(True); orc.average(); c.step_merge_average(w.lr)
+        orc.local_step(g, w.lr); orc.merge(True); c.local_step(w.lr); c.merge(True)
+        c.sync()
+        compare_state(dev, orc, 0)
+    finally:
+        dev.close()
