@@ -171,10 +171,11 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // streaming hint on every access except z from the sizes of hint_of on.  A local step sweeps one replica after the other
 // (the longest contiguous runs); merges take the tiles in chunks of 8192 (8 MB
 // of z per chunk, 1 MB per XCD) so that the chunk's z is still in L2 when the
-// next replica needs it.  The mean's replicas are split over two groups of waves from
-// K = 8 and over four from K = 12 on (256-thread workgroups with LDS): merge + mean, us at
-// split 1 / 2 / 4: ResNet-50 list K = 8 664 / 655 / 656, K = 12 982 / 975 / 963, K = 16
-// 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178
+// next replica needs it.  The mean's replicas are split over four groups of waves from K = 12 on (256-thread workgroups
+// with LDS): merge + mean, us at split 1 / 2 / 4: ResNet-50 list K = 12 982 / 975 / 963, K = 16
+// 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178.  Below, two groups bring nothing
+// on large lists (a cycle, ResNet-50 K = 8 2857 / 2857, ResNet-18 K = 8 1291 / 1290) and cost 2-3 % on small ones (K = 8, 10^5 elements
+// 14.1 / 14.5, 7e5 34.6 / 35.8; K = 10, 1.5e6 81.7 / 83.6)
 // (profiles/mean_launch_shape_sweep.txt).  The in-order mean of lasgd_step_merge_average
 // takes split 1: its z is to be that of the one-kernel form to the bit.
 //
@@ -207,7 +208,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.kper_step = 1;
     t.kper_merge = 1;
     t.max_blocks = -1;
-    t.avg_split = c.K >= 12 ? 4 : c.K >= 8 ? 2 : 1;
+    t.avg_split = c.K >= 12 ? 4 : 1;
     t.avg_max_blocks = -1;
     t.nontemporal = hint_of(&c, USE_CYCLE);
     t.waves_per_block = 1;
