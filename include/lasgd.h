@@ -129,7 +129,8 @@ lasgd_status lasgd_create(const lasgd_config *cfg, lasgd_ctx **out);
  * numel[t] elements of the storage dtype, 16-byte aligned; the host arrays
  * [n_tensors] are copied, the device buffers stay the caller's and must
  * outlive their use.  May be called again to re-point a replica (e.g. at a
- * rotating gradient buffer); waits for work already enqueued.  16-byte
+ * rotating gradient buffer); waits for work already enqueued on the main stream and
+ * for every lasgd_zero_grads on whatever stream (then for the whole device).  16-byte
  * alignment is all that is required; for full speed let every tensor start on
  * a 1 KiB boundary (512 bytes for bf16), the size of one wave's access: the
  * library's own arrays are laid out that way, and tiles that start 256 or 512
@@ -159,6 +160,8 @@ lasgd_status lasgd_local_step(lasgd_ctx *ctx, float lr);
  * Every bound gradient buffer of every replica to zero, in one launch: what a training loop does before the backward
  * passes accumulate into them.  stream: hipStream_t the backward passes run on (NULL = default stream); ordering
  * against the main stream, which reads the gradients, is the caller's.  Changes no state of the context.
+ * lasgd_bind and lasgd_destroy wait for it, and for replays of graphs it was recorded into that are queued by then; a
+ * replay clears what is bound when it runs.  lasgd_sync does not wait for it, unless the stream is one of the context's.
  * Errors: STATE (a replica is unbound), HIP.
  */
 lasgd_status lasgd_zero_grads(lasgd_ctx *ctx, void *stream);
@@ -316,7 +319,7 @@ lasgd_status lasgd_read_state(lasgd_ctx *ctx, int32_t which, int32_t k, int32_t 
 lasgd_status lasgd_global_update_static(int32_t K, int64_t n, float *const *x, float *const *sent,
                                         int32_t resnapshot, void *stream);
 
-/* Wait until both streams have finished everything this context enqueued. */
+/* Wait until both streams have finished everything this context enqueued on them. */
 lasgd_status lasgd_sync(lasgd_ctx *ctx);
 
 /* Change launch-shape knobs (waits for enqueued work first).  A graph captured

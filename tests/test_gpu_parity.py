@@ -252,6 +252,58 @@ def test_rebinding_gradient_buffers():
         dev.close()
 
 
+@pytest.mark.parametrize("streams", [1, 2])
+def test_rebinding_waits_for_clears_on_other_streams(streams):
+    """lasgd_zero_grads behind a long queue on a stream the library does not know, then bind to other buffers without a
+    wait of the caller's: the clear reaches the buffers that were bound when it was issued, all of them and no others.
+    Two streams: the queued clear is not the last one that was issued."""
+    import torch
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    w = W.small(K=3, numels=(70000, 5, 1024, 4099))
+    dev = DeviceReplicas(w, weight_decay=[0.0] * 4)
+    try:
+        busy = torch.zeros(64 << 20, device=dev.dev)
+        alt = [torch.full_like(t, 7.0) for t in dev.g]
+        for t in dev.g:
+            t.fill_(5.0)
+        queue = torch.cuda.Stream(device=dev.dev)
+        other = torch.cuda.Stream(device=dev.dev)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(queue):
+            for _ in range(200):                       # some 20 ms of work
+                busy.add_(1.0)
+        dev.ctx.zero_grads(queue.cuda_stream)
+        if streams == 2:
+            dev.ctx.zero_grads(other.cuda_stream)
+        for k in range(w.K):
+            dev.ctx.bind(k, [dev.x[k].data_ptr() + int(off) * 4 for off in dev.off[:-1]],
+                         [alt[k].data_ptr() + int(off) * 4 for off in dev.off[:-1]])
+        torch.cuda.synchronize()
+        for k in range(w.K):
+            assert not dev.g[k][dev._idx].any(), f"replica {k}: the buffers bound at the time of the clear"
+            assert bool((alt[k] == 7.0).all()), f"replica {k}: the buffers bound afterwards"
+        # a clear recorded into a graph is waited for too, whenever it is replayed
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=queue):
+            dev.ctx.zero_grads(queue.cuda_stream)
+        for rep in range(3):
+            new = [torch.full_like(t, 3.0) for t in dev.g]
+            torch.cuda.synchronize()
+            with torch.cuda.stream(queue):
+                for _ in range(200):
+                    busy.add_(1.0)
+                graph.replay()
+            for k in range(w.K):
+                dev.ctx.bind(k, [dev.x[k].data_ptr() + int(off) * 4 for off in dev.off[:-1]],
+                             [new[k].data_ptr() + int(off) * 4 for off in dev.off[:-1]])
+            torch.cuda.synchronize()
+            for k in range(w.K):
+                assert not alt[k][dev._idx].any() and bool((new[k] == 3.0).all()), f"replay {rep}, replica {k}"
+            alt = new
+    finally:
+        dev.close()
+
+
 @pytest.mark.parametrize("m", [1, 3])
 def test_graph_replay_equals_eager(m):
     """A captured cycle replayed several times, with eager library work and host
