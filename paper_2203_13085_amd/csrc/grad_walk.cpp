@@ -3,6 +3,7 @@
 // missing, 60 more to gather them).  Host code only; nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <c10/core/impl/COW.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/variable.h>
 
@@ -10,9 +11,9 @@ namespace {
 
 enum State : long { PLAIN = 0, OTHER = 1, MISSING = 2 };
 
-// A gradient that its buffer stands for entirely: dense, contiguous, of the parameter's own size, type and device, and
-// without anything that an operation on it would have to record or hand on (autograd history, forward-mode
-// tangents, transforms, subclasses with a dispatcher of their own).
+// A gradient that its buffer stands for entirely: dense, contiguous, of the parameter's own size, type and device, with
+// a buffer of its own (a lazy clone's is shared until one side writes), and without anything that an operation on it would
+// have to record or hand on (autograd history, forward-mode tangents, transforms, subclasses with a dispatcher of their own).
 bool plain(const at::Tensor &p, const at::Tensor &g)
 {
     const c10::TensorImpl *impl = g.unsafeGetTensorImpl();
@@ -22,7 +23,8 @@ bool plain(const at::Tensor &p, const at::Tensor &g)
                                               c10::DispatchKey::ZeroTensor});
     return !impl->is_python_dispatch() && !impl->key_set().has_any(wrapped) && g.layout() == c10::kStrided &&
            !g.is_inference() && !g.requires_grad() && !g._fw_grad(0).defined() && g.scalar_type() == p.scalar_type() &&
-           g.device() == p.device() && g.numel() == p.numel() && g.is_contiguous();
+           g.device() == p.device() && g.numel() == p.numel() && g.is_contiguous() &&
+           !c10::impl::cow::is_cow_data_ptr(g.storage().data_ptr());
 }
 
 // state(params, type, addresses or None, touch) -> PLAIN, OTHER or MISSING (some gradient is None).

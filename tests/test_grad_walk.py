@@ -102,11 +102,19 @@ def _forward_mode():
     return p
 
 
-@pytest.mark.parametrize("make", [_strided, _with_history, _inference, _sparse, _swapped_data, _negative, _other_type, _forward_mode])
+def _lazy_clone():
+    p = P(torch.zeros(4))
+    p.grad = torch.ones(4)
+    p._at = p.grad.data_ptr()                         # asked for later, it would un-share the buffer
+    p._other = torch._lazy_clone(p.grad)              # one buffer until somebody writes
+    return p
+
+
+@pytest.mark.parametrize("make", [_lazy_clone, _strided, _with_history, _inference, _sparse, _swapped_data, _negative, _other_type, _forward_mode])
 def test_anything_but_a_plain_gradient_goes_the_general_way(make):
     p = make()
     try:
-        at = 0 if p.grad.layout != torch.strided else p.grad.data_ptr()
+        at = p._at if hasattr(p, "_at") else 0 if p.grad.layout != torch.strided else p.grad.data_ptr()
         a = np.array([at], dtype=np.uint64)
         if not p.grad.is_inference():
             v = p.grad._version
