@@ -13,7 +13,7 @@ enum State : long { PLAIN = 0, OTHER = 1, MISSING = 2 };
 
 // A gradient that its buffer stands for entirely: dense, contiguous, of the parameter's own size, type and device, with
 // a buffer of its own (a lazy clone's is shared until one side writes), and without anything that an operation on it would
-// have to record or hand on (autograd history, forward-mode tangents, transforms, subclasses with a dispatcher of their own).
+// have to record or hand on (autograd history, forward-mode tangents, transforms, subclasses in C++ or in Python).
 bool plain(const at::Tensor &p, const at::Tensor &g)
 {
     const c10::TensorImpl *impl = g.unsafeGetTensorImpl();
@@ -21,7 +21,8 @@ bool plain(const at::Tensor &p, const at::Tensor &g)
                                               c10::DispatchKey::Functionalize, c10::DispatchKey::Batched,
                                               c10::DispatchKey::Conjugate, c10::DispatchKey::Negative,
                                               c10::DispatchKey::ZeroTensor});
-    return !impl->is_python_dispatch() && !impl->key_set().has_any(wrapped) && g.layout() == c10::kStrided &&
+    const PyObject *seen = impl->pyobj_slot()->load_pyobj();       // none: Python has never seen it, so it is no subclass there
+    return (!seen || (PyObject *)Py_TYPE(seen) == THPVariableClass) && !impl->is_python_dispatch() && !impl->key_set().has_any(wrapped) && g.layout() == c10::kStrided &&
            !g.is_inference() && !g.requires_grad() && !g._fw_grad(0).defined() && g.scalar_type() == p.scalar_type() &&
            g.device() == p.device() && g.numel() == p.numel() && g.is_contiguous() &&
            !c10::impl::cow::is_cow_data_ptr(g.storage().data_ptr());

@@ -110,7 +110,17 @@ def _lazy_clone():
     return p
 
 
-@pytest.mark.parametrize("make", [_lazy_clone, _strided, _with_history, _inference, _sparse, _swapped_data, _negative, _other_type, _forward_mode])
+def _torch_function_subclass():
+    class G(torch.Tensor):                            # no dispatcher of its own: only Python's __torch_function__
+        @classmethod
+        def __torch_function__(cls, func, types, args=(), kwargs=None):
+            return super().__torch_function__(func, types, args, kwargs or {})
+    p = P(torch.zeros(4))
+    p.grad = torch.ones(4).as_subclass(G)
+    return p
+
+
+@pytest.mark.parametrize("make", [_lazy_clone, _torch_function_subclass, _strided, _with_history, _inference, _sparse, _swapped_data, _negative, _other_type, _forward_mode])
 def test_anything_but_a_plain_gradient_goes_the_general_way(make):
     p = make()
     try:
