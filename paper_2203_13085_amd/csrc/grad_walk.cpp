@@ -28,26 +28,38 @@ bool plain(const at::Tensor &p, const at::Tensor &g)
            !c10::impl::cow::is_cow_data_ptr(g.storage().data_ptr());
 }
 
-// state(params, type, addresses or None, touch) -> PLAIN, OTHER or MISSING (some gradient is None).
-// PLAIN: every entry of `params` is exactly a `type` and has a gradient; with addresses also: it is plain, at its address.
+// A buffer of n 64-bit values, or nothing for None; false with an exception set where it is neither.
+struct Column {
+    Py_buffer view{};
+    const uint64_t *at = nullptr;
+    bool take(PyObject *o, Py_ssize_t n, const char *what)
+    {
+        if (o == Py_None) return true;
+        if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
+        at = static_cast<const uint64_t *>(view.buf);
+        if (view.len == n * (Py_ssize_t)sizeof(uint64_t)) return true;
+        PyErr_SetString(PyExc_ValueError, what);
+        return false;
+    }
+    ~Column()
+    {
+        if (view.obj) PyBuffer_Release(&view);
+    }
+};
+
+// state(params, type, addresses or None, touch, sizes = None) -> PLAIN, OTHER or MISSING (some gradient is None).
+// PLAIN: every entry of `params` is exactly a `type` and has a gradient; with addresses also: it is plain, at its address, and
+// with sizes as many bytes long as was bound there (a parameter may have been cut down together with its gradient).
 // touch: if PLAIN, the gradients' version counters go up by one, as after an operation in place.
 PyObject *state(PyObject *, PyObject *args)
 {
-    PyObject *params, *type, *addresses;
+    PyObject *params, *type, *addresses, *sizes = Py_None;
     int touch;
-    if (!PyArg_ParseTuple(args, "O!OOp", &PyList_Type, &params, &type, &addresses, &touch)) return nullptr;
+    if (!PyArg_ParseTuple(args, "O!OOp|O", &PyList_Type, &params, &type, &addresses, &touch, &sizes)) return nullptr;
     const Py_ssize_t n = PyList_GET_SIZE(params);
-    Py_buffer view{};
-    const uint64_t *want = nullptr;
-    if (addresses != Py_None) {
-        if (PyObject_GetBuffer(addresses, &view, PyBUF_SIMPLE) != 0) return nullptr;
-        if (view.len != n * (Py_ssize_t)sizeof(uint64_t)) {
-            PyBuffer_Release(&view);
-            PyErr_SetString(PyExc_ValueError, "one address for every parameter");
-            return nullptr;
-        }
-        want = static_cast<const uint64_t *>(view.buf);
-    }
+    Column address, size;
+    if (!address.take(addresses, n, "one address for every parameter") || !size.take(sizes, n, "one size for every parameter"))
+        return nullptr;
     long found = PLAIN;
     try {
         for (Py_ssize_t i = 0; i < n && found != MISSING; ++i) {
@@ -59,17 +71,18 @@ PyObject *state(PyObject *, PyObject *args)
             const at::Tensor &p = THPVariable_Unpack(o);
             const at::Tensor &g = p.grad();
             if (!g.defined()) found = MISSING;
-            else if (want && found == PLAIN && !(plain(p, g) && (uint64_t)(uintptr_t)g.const_data_ptr() == want[i])) found = OTHER;
+            else if (address.at && found == PLAIN &&
+                     !(plain(p, g) && (uint64_t)(uintptr_t)g.const_data_ptr() == address.at[i] &&
+                       (!size.at || (uint64_t)g.nbytes() == size.at[i])))
+                found = OTHER;
         }
         if (found == PLAIN && touch)
             for (Py_ssize_t i = 0; i < n; ++i)
                 torch::autograd::impl::bump_version(THPVariable_Unpack(PyList_GET_ITEM(params, i)).grad());
     } catch (const std::exception &e) {
-        if (want) PyBuffer_Release(&view);
         PyErr_SetString(PyExc_RuntimeError, e.what());
         return nullptr;
     }
-    if (want) PyBuffer_Release(&view);
     return PyLong_FromLong(found);
 }
 

@@ -17,6 +17,7 @@ from __future__ import annotations
 
 from typing import List, Optional, Sequence
 
+import numpy as np
 import torch
 
 from . import _grad_walk
@@ -45,6 +46,7 @@ class LASGD:
             for p, q in zip(ps, first):
                 assert p.shape == q.shape and p.dtype == dtype and p.device == dev and p.is_contiguous()
         self._flat = [p for ps in self.params for p in ps]
+        self._bytes = np.array([p.numel() * p.element_size() for p in self._flat], dtype=np.uint64)    # what the library clears
         self.lr, self.m, self.tau, self.t = float(lr), int(m), 0, 0
         self.device = dev
         self.main = torch.cuda.Stream(device=dev)
@@ -69,7 +71,8 @@ class LASGD:
         # The gradients sit where the library reads them, so the library clears them, in one launch, once a native walk has
         # seen that every one is there, at its address and plain.  A list of 632 tensors (MobileNetV2, K = 4) took
         # _foreach_zero_ eight launches and, with the list and the version counters, 170 us of host time; this takes 20.
-        if self._eager() and _grad_walk.state(self._flat, torch.nn.Parameter, b"".join(self.ctx.bound_grads), True) == 0:
+        if self._eager() and _grad_walk.state(self._flat, torch.nn.Parameter, b"".join(self.ctx.bound_grads), True,
+                                            self._bytes) == 0:
             self.ctx.zero_grads(torch.cuda.current_stream(self.device).cuda_stream)
             return
         grads = [p.grad for p in self._flat]
@@ -121,7 +124,6 @@ class LASGD:
 
     def center(self) -> torch.Tensor:
         """The current mean model z (flat, fp32), e.g. for evaluation."""
-        import numpy as np
         return torch.from_numpy(np.ascontiguousarray(self.ctx.read_state(B.STATE_Z)))
 
     def close(self) -> None:

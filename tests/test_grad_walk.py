@@ -136,10 +136,28 @@ def test_anything_but_a_plain_gradient_goes_the_general_way(make):
             p._level.__exit__(None, None, None)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_a_gradient_of_another_length_than_was_bound(dtype):
+    ps = _params(dtype)
+    a, sizes = _addr(ps), np.array([p.numel() * p.element_size() for p in ps], dtype=np.uint64)
+    assert _grad_walk.state(ps, P, a, True, sizes) == PLAIN
+    ps[2].data = ps[2].data[:1]                       # parameter and gradient shortened in step, at the bound address
+    ps[2].grad = ps[2].grad[:1]
+    assert ps[2].grad.data_ptr() == a[2] and ps[2].grad.shape == ps[2].shape
+    versions = [p.grad._version for p in ps]
+    assert _grad_walk.state(ps, P, a, True, sizes) == OTHER and [p.grad._version for p in ps] == versions
+    ps[0].data, ps[0].grad = ps[0].data.to(torch.float64), None      # the same number of elements, of another width
+    ps[0].grad = torch.ones(3, 4, dtype=torch.float64)
+    wide = np.array([ps[0].grad.data_ptr()], dtype=np.uint64)
+    assert _grad_walk.state(ps[:1], P, wide, True, sizes[:1].copy()) == OTHER
+
+
 def test_bad_arguments_are_refused():
     ps = _params()
     with pytest.raises(ValueError):
         _grad_walk.state(ps, P, b"12345678", True)
+    with pytest.raises(ValueError):
+        _grad_walk.state(ps, P, _addr(ps), True, b"12345678")
     with pytest.raises(TypeError):
         _grad_walk.state(tuple(ps), P, None, True)
     assert _grad_walk.state([1, 2], P, None, True) == OTHER
