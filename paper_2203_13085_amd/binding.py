@@ -159,6 +159,10 @@ class Context:
             self._L.lasgd_destroy(self._h)
             self._h = None
 
+    @property
+    def is_open(self) -> bool:
+        return bool(getattr(self, "_h", None))
+
     def __del__(self):
         try:
             self.close()

@@ -84,10 +84,11 @@ class LASGD:
                 g.zero_()
 
     def _eager(self) -> bool:
-        # nobody watches torch's operations, and no graph is recorded that could outlive this object's tables
+        # the library's tables are there, nobody watches torch's operations, and no graph is recorded that could outlive the tables
         return (torch._C._len_torch_dispatch_stack() == 0 and torch._C._len_torch_function_stack() == 0
                 and torch._C._functorch.peek_interpreter_stack() is None and not torch.compiler.is_compiling()
-                and torch.cuda.current_device() == self.device.index and not torch.cuda.is_current_stream_capturing())
+                and self.ctx.is_open and torch.cuda.current_device() == self.device.index
+                and not torch.cuda.is_current_stream_capturing())
 
     def _check_bound(self) -> None:
         # a dropped or replaced .grad would leave the library reading a stale buffer

@@ -146,3 +146,16 @@ def test_zero_grad_is_seen_by_a_graph_that_saved_the_gradient():
             y.backward()
     finally:
         opt.close()
+
+
+def test_zero_grad_after_close():
+    """The gradients are the modules' own and outlive the library's tables."""
+    from paper_2203_13085_amd.torch_api import LASGD
+    net = torch.nn.Linear(8, 8, device="cuda:0")
+    opt = LASGD([net], lr=0.1)
+    for p in net.parameters():
+        p.grad.fill_(2.0)
+    opt.close()
+    opt.zero_grad()
+    torch.cuda.synchronize()
+    assert not any(p.grad.any() for p in net.parameters())
