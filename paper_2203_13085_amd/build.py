@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "lasgd.hip")
 LIB = os.path.join(HERE, "liblasgd_hip.so")
 WALK_SRC = os.path.join(HERE, "csrc", "grad_walk.cpp")
-WALK_LIB = os.path.join(HERE, "_grad_walk.so")
+WALK_LIB = os.path.join(HERE, "_grad_walk" + sysconfig.get_config_var("EXT_SUFFIX"))     # another Python does not load it
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17",
@@ -36,7 +36,7 @@ def build_grad_walk(verbose: bool = False) -> str:
            sysconfig.get_paths()["include"]]
     lib = os.path.join(root, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           *["-isystem" + d for d in inc], "-o", WALK_LIB, WALK_SRC, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+           f'-DLASGD_TORCH_VERSION="{torch.__version__}"', *["-isystem" + d for d in inc], "-o", WALK_LIB, WALK_SRC, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-Wl,-rpath," + lib]
     if verbose:
         print(" ".join(cmd), flush=True)

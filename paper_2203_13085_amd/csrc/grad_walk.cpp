@@ -92,4 +92,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_grad_walk", nullptr, -1, methods,
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__grad_walk() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__grad_walk()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", LASGD_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -15,13 +15,31 @@ change; clear them with `zero_grad()` of this class (or
 """
 from __future__ import annotations
 
+import warnings
 from typing import List, Optional, Sequence
 
 import numpy as np
 import torch
 
-from . import _grad_walk
 from . import binding as B
+
+
+def _load_walk():
+    """The native walk over gradients, or None (and a warning) where it was not built for this very torch: it reads torch's
+    objects through the headers it was compiled against.  Everything works without it, with walks in Python."""
+    try:
+        from . import _grad_walk
+        if _grad_walk.torch_version == torch.__version__:
+            return _grad_walk
+        why = f"it was built for torch {_grad_walk.torch_version}, this is {torch.__version__}"
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    warnings.warn(f"the native walk over gradients is left out, zero_grad() and step() take longer: {why} "
+                  "(build it with `python -m paper_2203_13085_amd.build`)", RuntimeWarning, stacklevel=2)
+    return None
+
+
+_walk = _load_walk()
 
 
 class LASGD:
@@ -71,8 +89,8 @@ class LASGD:
         # The gradients sit where the library reads them, so the library clears them, in one launch, once a native walk has
         # seen that every one is there, at its address and plain.  A list of 632 tensors (MobileNetV2, K = 4) took
         # _foreach_zero_ eight launches and, with the list and the version counters, 170 us of host time; this takes 20.
-        if self._eager() and _grad_walk.state(self._flat, torch.nn.Parameter, b"".join(self.ctx.bound_grads), True,
-                                            self._bytes) == 0:
+        if _walk and self._eager() and _walk.state(self._flat, torch.nn.Parameter, b"".join(self.ctx.bound_grads), True,
+                                                   self._bytes) == 0:
             self.ctx.zero_grads(torch.cuda.current_stream(self.device).cuda_stream)
             return
         grads = [p.grad for p in self._flat]
@@ -92,7 +110,7 @@ class LASGD:
 
     def _check_bound(self) -> None:
         # a dropped or replaced .grad would leave the library reading a stale buffer
-        if _grad_walk.state(self._flat, torch.nn.Parameter, None, False) == 0:
+        if _walk and _walk.state(self._flat, torch.nn.Parameter, None, False) == 0:
             return
         for p in self._flat:
             assert p.grad is not None, "a gradient buffer was dropped (use zero_grad(set_to_none=False))"

@@ -161,3 +161,32 @@ def test_bad_arguments_are_refused():
     with pytest.raises(TypeError):
         _grad_walk.state(tuple(ps), P, None, True)
     assert _grad_walk.state([1, 2], P, None, True) == OTHER
+
+
+@pytest.mark.parametrize("missing", [True, False])
+def test_the_torch_class_works_without_the_walk(monkeypatch, missing):
+    """Not built, or built for another torch: the module imports, says so, and walks in Python."""
+    import importlib
+    import sys
+    import paper_2203_13085_amd
+    from paper_2203_13085_amd import torch_api
+    if missing:
+        monkeypatch.delattr(paper_2203_13085_amd, "_grad_walk", raising=False)
+        monkeypatch.setitem(sys.modules, "paper_2203_13085_amd._grad_walk", None)      # import fails
+    else:
+        monkeypatch.setattr(_grad_walk, "torch_version", "0.0.0")
+    try:
+        with pytest.warns(RuntimeWarning, match="native walk"):
+            api = importlib.reload(torch_api)
+        opt = api.LASGD.__new__(api.LASGD)
+        opt._flat = _params()
+        opt._check_bound()
+        opt.zero_grad()
+        assert not any(p.grad.any() for p in opt._flat)
+        opt._flat[1].grad = None
+        with pytest.raises(AssertionError):
+            opt._check_bound()
+    finally:
+        monkeypatch.undo()
+        importlib.reload(torch_api)
+    assert torch_api._walk is _grad_walk
