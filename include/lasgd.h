@@ -97,9 +97,13 @@ typedef struct {
                               kernels also take their streaming shapes: the step and merge kernels bound
                               their waves per CU through LDS that they ask for and do not use (up to a CU's
                               160 KiB among the waves of a local step), and lasgd_step_merge_average takes
-                              two kernels beyond 12 replicas.  4 switches that off too.  Until it is set, each call
-                              decides by the size of its arrays (read back: what the steps, updates and
-                              the mean take); once set, it holds for every call                           */
+                              two kernels beyond 12 replicas.  4 switches that off too.  Once set, it holds for
+                              every call.  <0 = default: each call decides by the size of one array of all
+                              replicas, from 28 MiB on for steps, updates and the mean, 40 MiB for
+                              lasgd_sgd_ar_step, 128 MiB for lasgd_step_merge_average.  These sizes are right
+                              for a program that has other memory to move between the calls; one that calls
+                              nothing else, on a single state that fits the 256 MB memory-side cache, gains
+                              1-3 % with 4 up to 64 MB an array (lasgd_sgd_ar_step 5-13 % up to 112 MB)    */
     int32_t chunk_step;    /* work-item order of local_step / snapshot: tiles are taken in chunks of this
                               many; inside a chunk replica after replica.  1 = the replicas of a tile are
                               adjacent; <0 = whole replica after whole replica                       */
@@ -328,7 +332,7 @@ lasgd_status lasgd_sync(lasgd_ctx *ctx);
  * Errors: INVALID (NULL, a field outside its documented values), HIP, ALLOC. */
 lasgd_status lasgd_set_tuning(lasgd_ctx *ctx, const lasgd_tuning *t);
 
-/* The knobs currently in effect. */
+/* The knobs currently in effect; handing them back to lasgd_set_tuning changes nothing. */
 lasgd_status lasgd_get_tuning(const lasgd_ctx *ctx, lasgd_tuning *out);
 
 /* Text of the last failure on this context ("" if none); owned by the context.

@@ -78,8 +78,7 @@ struct lasgd_ctx {
     bool center_valid = false;   // z has been computed at least once
     float alpha = 1.f, beta = 1.f;   // elastic coefficients (Sec. 3, Eq. 5-6); 1, 1 = Algorithm 1
 
-    lasgd_tuning tune{};
-    bool hint_asked = false;         // the caller has set tune.nontemporal: it holds for every call
+    lasgd_tuning tune{};             // .nontemporal: 1..4 as the caller has set it, for every call; -1 = by call and size (hint_of)
     bool fused_cycle = false;        // the pending mean was made by lasgd_step_merge_average: the steps in between go by its rule
     std::string err;
 };
@@ -197,7 +196,7 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 enum Use { USE_CYCLE, USE_SGD_AR, USE_FUSED, USE_ZERO };
 int hint_of(const lasgd_ctx *c, Use use)
 {
-    if (c->hint_asked) return c->tune.nontemporal;
+    if (c->tune.nontemporal >= 0) return c->tune.nontemporal & 3;           // 4, no hint, is 0
     const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
     const uint64_t from = use == USE_CYCLE ? 28ull << 20 : use == USE_SGD_AR ? 40ull << 20 : 128ull << 20;
     return array >= from ? 3 : 0;
@@ -212,7 +211,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.max_blocks = -1;
     t.avg_split = c.K >= 12 ? 4 : 1;
     t.avg_max_blocks = -1;
-    t.nontemporal = hint_of(&c, USE_CYCLE);
+    t.nontemporal = -1;
     t.waves_per_block = 1;
     t.chunk_step = -1;
     t.chunk_merge = 8192;
@@ -1105,8 +1104,8 @@ static lasgd_status set_tuning_impl(lasgd_ctx *c, const lasgd_tuning *t)
     }
     if (t->avg_max_blocks) n.avg_max_blocks = t->avg_max_blocks;
     if (t->nontemporal) {
-        if (t->nontemporal < 0 || t->nontemporal > 4) return fail(c, LASGD_ERR_INVALID, "nontemporal outside 0..4");
-        n.nontemporal = t->nontemporal == 4 ? 0 : t->nontemporal;      // 4 = switch the hints off again
+        if (t->nontemporal > 4) return fail(c, LASGD_ERR_INVALID, "nontemporal must be 1, 2, 3 or 4 (or negative for the default)");
+        n.nontemporal = t->nontemporal < 0 ? -1 : t->nontemporal;
     }
     if (t->waves_per_block) {
         if (t->waves_per_block != 1 && t->waves_per_block != 2 && t->waves_per_block != 4)
@@ -1128,7 +1127,6 @@ static lasgd_status set_tuning_impl(lasgd_ctx *c, const lasgd_tuning *t)
         if (st != LASGD_OK) return st;
     }
     c->tune = n;
-    if (t->nontemporal) c->hint_asked = true;
     return LASGD_OK;
 }
 

@@ -49,6 +49,33 @@ def test_streaming_hints_do_not_change_results():
         run_parity(W.small(K=3), tuning=dict(nontemporal=nt))
 
 
+@pytest.mark.parametrize("n", [300, 2_000_000])
+def test_tuning_round_trip(n):
+    """What get_tuning reports, handed back, changes nothing, from any state; the hint goes back to the choice by call and size.
+    2,000,000 elements, K = 4: 30.5 MiB an array, where the calls choose differently."""
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    dev = DeviceReplicas(W.small(K=4, numels=(n,)))
+    try:
+        c = dev.ctx
+        fresh = c.get_tuning()
+        assert fresh["nontemporal"] == -1
+        for hint in (-1, 1, 2, 3, 4, -5):
+            c.set_tuning(nontemporal=hint)
+            at = c.get_tuning()
+            assert at["nontemporal"] == max(hint, -1)
+            c.set_tuning(**at)
+            assert c.get_tuning() == at
+            c.set_tuning(vec=2)                         # another knob leaves the hint alone
+            assert c.get_tuning()["nontemporal"] == at["nontemporal"]
+            c.set_tuning(**fresh)
+            assert c.get_tuning() == fresh
+        with pytest.raises(B.LasgdError) as e:
+            c.set_tuning(nontemporal=5)
+        assert e.value.status == B.ERR_INVALID and c.get_tuning() == fresh
+    finally:
+        dev.close()
+
+
 def test_same_stream_for_both():
     run_parity(W.small(K=3), side_stream=False)
 
