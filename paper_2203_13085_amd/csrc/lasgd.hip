@@ -234,6 +234,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 // 643-697 us, and 650-712 when the steps held all 32 waves and no LDS.
 constexpr uint32_t kLdsGranule = 1280;
 constexpr size_t kCuLds = 163840;
+constexpr size_t kOneGroupLds = (kCuLds / 2 / kLdsGranule + 1) * kLdsGranule;      // two workgroups with this do not fit a CU
 constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
 // Step + update asks for a word of its model before its loads, as the fp32 local step always does, and then runs 16 waves a CU in
 // place of 12, up to 1e8 replica-parameters.  A pass's us without / with, over three states in turn (and with other work between
@@ -1175,15 +1176,24 @@ template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hi
     uint32_t R;                 // replicas a wave
     if (NT != 0) {
         // Streaming.  The memory system is fastest with about 24 replicas' rows on a CU (24 KiB of s, then 24 KiB of x), as
-        // whole workgroups: the LDS a workgroup asks for leaves room for 24 / K of them, two at least.  us over three states
-        // in turn, one replica a wave, everything at once and no bound / staged and bounded with one, two, four a wave:
-        // K = 2 131 / 125, 125; K = 3 193 / 188, 189; K = 4 267 / 252, 249, 250; K = 6 397 / 386, 382, 385; K = 8 557 / 536, 529, 529;
-        // K = 12 811 / 790, 783, 780; K = 16 1132 / 1112, 1109, 1100; K = 32 467 / -, 466, 472.  One group more or fewer on a CU costs
-        // 1-2 or 3-20 %.  Other work between the calls changes none of this (K = 8 555 / 533, 526).
-        R = a.K <= 3u ? 1u : a.K <= 2u * kGroupWaves ? (a.K == 12u || a.K == 16u ? 4u : 2u) : 4u;
-        const uint32_t groups = a.K <= 24u ? 24u / a.K : 1u;
-        const size_t pace = kCuLds / groups / kLdsGranule * kLdsGranule;
-        lds = pace > lds ? (pace < kMaxLds ? pace : kMaxLds) : lds;
+        // whole workgroups: the LDS a workgroup asks for leaves room for 24 / K of them, two at least up to K = 24.  us over three
+        // states in turn, one replica a wave, everything at once and no bound / staged and bounded with one, two, four a wave:
+        // K = 2 131 / 125, 125; K = 3 193 / 188, 189; K = 4 267 / 252, 249, 250; K = 6 397 / 386, 382, 385; K = 8 557 / 536, 529, 529.
+        // Two or four a wave from K = 12 on is a matter of 0.5 % either way (150 MB an array, K = 12: 107.8 / 110.2; 1100 MB 707.6 / 705.7).
+        // One group more or fewer on a CU costs 1-2 or 3-20 %.  Other work between the calls changes none of this
+        // (K = 8 555 / 533, 526).  Vectors of 150 to 1100 MB together, before / staged with this rule: K = 9 -2 to -3 %,
+        // K = 10 -1 to -3.5, K = 12 +1 to -4, K = 16 0 to -2, K = 20 -1 to -3.6, K = 24 to 32 -0.3 to -0.8.
+        // K = 25 to 32, two groups a CU / one, 450 MB: K = 25 336 / 323, K = 27 356 / 342, K = 29 337 / 330, K = 32 351 / 345.
+        // Four replicas a wave, K > 32, have enough in flight to wait for s alone at no gain, and are bounded to two groups: at once
+        // and no bound / staged / at once and bounded, K = 33, n = 3.5e6 329.0 / 327.3 / 322.8, K = 40, 4e6 423.6 / 426.1 / 422.4,
+        // K = 48, 3e6 451.7 / 456.4 / 451.4, K = 64, 3e6 560.3 / 563.4 / 560.3.
+        R = a.K <= kFlatOneMaxK ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
+        size_t pace = kOneGroupLds;
+        if (a.K <= 24u || R == 4u) {
+            pace = kCuLds / (a.K <= 12u ? 24u / a.K : 2u) / kLdsGranule * kLdsGranule;
+            if (pace > kMaxLds) pace = kMaxLds;
+        }
+        if (pace > lds) lds = pace;
     } else {
         // In the memory-side cache.  One wave per replica while a workgroup can hold that many (16), then two or four replicas
         // a wave.  Two win for K = 4..8 where the waves are more than the chip holds

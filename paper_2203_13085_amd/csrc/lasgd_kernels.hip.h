@@ -714,29 +714,27 @@ template <int N> __device__ __forceinline__ void add_rows(const float *p, double
     for (int k = 0; k < N; ++k) LASGD_ACC4(q[k]);
 }
 
+// The same for K rows, FROM <= K <= TO.
+template <int FROM, int TO> __device__ __forceinline__ void add_rows_of(uint32_t K, const float *p, double &a0, double &a1, double &a2, double &a3)
+{
+    if constexpr (FROM < TO)
+        if (K != (uint32_t)FROM) return add_rows_of<FROM + 1, TO>(K, p, a0, a1, a2, a3);
+    add_rows<FROM>(p, a0, a1, a2, a3);
+}
+
 // The mean of one row over its K values per element, which lie in lds[K][256]; every wave gets its lanes' columns.
 // Up to K = 8 every wave sums them itself, which saves a barrier; beyond, up to four waves finish one column per
 // thread and turn: only that thread reads the column, so the mean may replace replica 0's value in it.  SGD-AR mix,
 // bare probe, every wave / shared: K = 4 6.12 / 6.01 TB/s, K = 8 6.08 / 6.01, K = 12 6.02 / 6.09, K = 16 5.51 / 5.89.
-// AT_ONCE: all reads of the up to eight rows before the first addition, where few waves are on a CU to hide them.  It
-// takes 20 registers more, too many for two sixteen-wave workgroups a CU in the SGD-AR step and with four replicas a wave.
-template <bool AT_ONCE, class MEAN>
+// FROM .. TO, if not 0: the kernel's K up to eight, and all reads of the rows come before the first addition, where few waves
+// are on a CU to hide them.  It takes 20 registers more, too many for two sixteen-wave workgroups a CU in the SGD-AR step.
+template <int FROM, int TO, class MEAN>
 __device__ __forceinline__ float4 row_mean(float *lds, uint32_t K, uint32_t W, uint32_t lane, MEAN mean_of)
 {
     if (K <= 8u) {
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        if constexpr (AT_ONCE) {
-            const float *p = lds + lane * 4u;
-            switch (K) {
-            case 1: add_rows<1>(p, a0, a1, a2, a3); break;
-            case 2: add_rows<2>(p, a0, a1, a2, a3); break;
-            case 3: add_rows<3>(p, a0, a1, a2, a3); break;
-            case 4: add_rows<4>(p, a0, a1, a2, a3); break;
-            case 5: add_rows<5>(p, a0, a1, a2, a3); break;
-            case 6: add_rows<6>(p, a0, a1, a2, a3); break;
-            case 7: add_rows<7>(p, a0, a1, a2, a3); break;
-            default: add_rows<8>(p, a0, a1, a2, a3); break;
-            }
+        if constexpr (TO > 0) {
+            add_rows_of<FROM, TO>(K, lds + lane * 4u, a0, a1, a2, a3);
         } else {
             for (uint32_t k = 0; k < K; ++k) {
                 const float4 q = *reinterpret_cast<const float4 *>(lds + (size_t)k * 256u + lane * 4u);
@@ -880,7 +878,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             if (kw[r] < a.K) *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = g[r];
     }
     __syncthreads();
-    const float4 gbar = row_mean<false>(lds, a.K, W, lane, [&a](double acc) { return group_mean_of(acc, a); });
+    const float4 gbar = row_mean<0, 0>(lds, a.K, W, lane, [&a](double acc) { return group_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(step_elem(comp(x[r], c), comp(v[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
@@ -1071,9 +1069,9 @@ __global__ __launch_bounds__(256) void poison_kernel(float *z, uint64_t n)
 //
 // Bound by HBM.  One workgroup per 256 elements, R replicas a wave: s and x are read once, the K values of s meet in
 // LDS, and z stays on the chip, so a replica-parameter moves 16 bytes where a
-// mean kernel followed by an update kernel moves 20 and z on top.  Where the vectors stream (NT), x is asked for when s
-// has arrived, and flies while s goes round through LDS, so that a wave puts half of its 2 KiB a replica in flight at a time.
-// launch_flat_update holds the shape's rule and what it measured.
+// mean kernel followed by an update kernel moves 20 and z on top.  Where the vectors stream (NT) and a wave has one replica or
+// two, x is asked for when s has arrived, and flies while s goes round through LDS, so that a wave puts half of its 2 KiB a
+// replica in flight at a time.  launch_flat_update holds the shape's rule and what it measured.
 // n = 25,000,000, us over three states in turn (before: one replica a wave, both loads at once, as many groups as fit): K = 8 511
 // = 6.3 TB/s (542), K = 4 248 (264), K = 12 787 (814).  n = 300,000, K = 8 8.3 (a mean kernel and an update kernel: 14.2).
 // Pointers of x and s side by side, one 16-byte scalar load a replica, were 2-4 % slower in the cache (n = 10^6, K = 6 17.4 / 18.0).
@@ -1092,10 +1090,13 @@ __device__ __forceinline__ float flat_mean_of(double acc, const FlatArgs &a)
     return (float)(a.use_mul ? acc * a.inv_k : acc / a.k_as_double);
 }
 
+constexpr uint32_t kFlatOneMaxK = 3;      // streaming: up to so many replicas one a wave, beyond two
+
 template <int R, int NT, bool FULL>
 __device__ __forceinline__ void flat_update_row(const FlatArgs &a, float *lds, uint64_t first, uint32_t count,
                                                 uint32_t w, uint32_t W, uint32_t lane)
 {
+    constexpr bool STAGED = NT != 0 && R < 4;
     const uint32_t e0 = lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= count) ? 0u : (count - e0 < 4u) ? count - e0 : 4u;
     float4 x[R], ss[R];
@@ -1108,9 +1109,9 @@ __device__ __forceinline__ void flat_update_row(const FlatArgs &a, float *lds, u
         sp[r] = a.s[mine[r] ? kw : a.K - 1u] + first;
         xp[r] = a.x[mine[r] ? kw : a.K - 1u] + first;
         ss[r] = row_ld<NT, FULL>(sp[r], e0, n);
-        if constexpr (NT == 0) x[r] = row_ld<NT, FULL>(xp[r], e0, n);
+        if constexpr (!STAGED) x[r] = row_ld<NT, FULL>(xp[r], e0, n);
     }
-    if constexpr (NT != 0) {
+    if constexpr (STAGED) {
         wait_for_loads();
 #pragma unroll
         for (int r = 0; r < R; ++r) x[r] = row_ld<NT, FULL>(xp[r], e0, n);
@@ -1119,7 +1120,8 @@ __device__ __forceinline__ void flat_update_row(const FlatArgs &a, float *lds, u
     for (int r = 0; r < R; ++r)
         if (mine[r]) *reinterpret_cast<float4 *>(lds + (size_t)(w + (uint32_t)r * W) * 256u + e0) = ss[r];
     __syncthreads();
-    const float4 z = row_mean<(NT != 0 && R < 4)>(lds, a.K, W, lane, [&a](double acc) { return flat_mean_of(acc, a); });
+    const float4 z = row_mean<!STAGED ? 0 : R == 1 ? 1 : (int)kFlatOneMaxK + 1, !STAGED ? 0 : R == 1 ? (int)kFlatOneMaxK : 8>(
+        lds, a.K, W, lane, [&a](double acc) { return flat_mean_of(acc, a); });
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         LASGD_FOR4(comp(x[r], c) = merge_elem(compv(x[r], c), compv(ss[r], c), compv(z, c));)

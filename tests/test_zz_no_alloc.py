@@ -152,7 +152,7 @@ def test_static_global_update_every_group_shape(K):
             np.testing.assert_array_equal(_bits(gs[:, n:n + 8]), _bits(hs[:, n:]))
 
 
-@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 33, 64])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 16, 17, 25, 32, 33, 64])
 def test_static_global_update_streaming_shapes(K):
     """Vectors beyond the memory-side cache take shapes of their own: replicas a wave, and workgroups a CU through the LDS
     they ask for.  Same roundings: the fp64 sum in replica order, one division, one rounding to fp32, then z + (x - s)."""
@@ -177,4 +177,51 @@ def test_static_global_update_streaming_shapes(K):
     assert torch.equal(s[:, :n].view(torch.int32), want.view(torch.int32))
     assert torch.equal(x[:, n:], behind[0]) and torch.equal(s[:, n:], behind[1])
     del x, s, acc, z, want
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("K", [8, 25, 40])
+def test_static_global_update_streaming_under_capture(K):
+    """Every bound of workgroups a CU (K = 25: more LDS a workgroup than 64 KiB) through a graph: replays with eager calls and
+    host waits between them."""
+    n = (32 << 20) // K + 259
+    pad = (n + 3) // 4 * 4
+    gen = torch.Generator(device="cuda:0").manual_seed(K)
+    x = torch.randn(K, pad, generator=gen, device="cuda:0")
+    s = torch.randn(K, pad, generator=gen, device="cuda:0")
+    step = torch.randn(K, pad, generator=gen, device="cuda:0")
+    hx, hs = x.clone(), s.clone()
+    xp, sp = [t.data_ptr() for t in x], [t.data_ptr() for t in s]
+
+    def expect():
+        hx.add_(step)
+        acc = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+        for k in range(K):
+            acc += hs[k, :n].double()
+        z = (acc / K).float()
+        for k in range(K):
+            hx[k, :n] = z + (hx[k, :n] - hs[k, :n])
+            hs[k, :n] = hx[k, :n]
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert torch.equal(x.view(torch.int32), hx.view(torch.int32)) and torch.equal(s.view(torch.int32), hs.view(torch.int32)), what
+
+    def eager(stream=None):
+        x.add_(step)
+        B.global_update_static(xp, sp, n, True, stream)
+
+    torch.cuda.synchronize()
+    say(f"[no-alloc] streaming under capture K={K} n={n}")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        eager(side.cuda_stream)
+    for rep in range(4):
+        graph.replay()
+        expect()
+        check(f"replay {rep}")
+        eager()
+        expect()
+        check(f"eager call {rep}")
+    del x, s, step, hx, hs
     torch.cuda.empty_cache()
