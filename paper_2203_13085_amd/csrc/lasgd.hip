@@ -174,9 +174,10 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 // of z per chunk, 1 MB per XCD) so that the chunk's z is still in L2 when the
 // next replica needs it.  The mean's replicas are split over four groups of waves from K = 12 on (256-thread workgroups
 // with LDS): merge + mean, us at split 1 / 2 / 4: ResNet-50 list K = 12 982 / 975 / 963, K = 16
-// 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178.  Below, two groups bring nothing
-// on large lists (a cycle, ResNet-50 K = 8 2857 / 2857, ResNet-18 K = 8 1291 / 1290) and cost 2-3 % on small ones (K = 8, 10^5 elements
-// 14.1 / 14.5, 7e5 34.6 / 35.8; K = 10, 1.5e6 81.7 / 83.6)
+// 1296 / 1294 / 1277, and the same on two streams; MobileNetV2 K = 16 178 / 183 / 178.  From 8 to 11 two groups
+// where the mean runs beside the steps on the other stream, one where it has the GPU to itself.  A cycle, us at split 1 / 2, two streams:
+// ResNet-50 K = 8, m = 4 2851 / 2847, ResNet-18 K = 8 1291 / 1288, bf16 K = 10, m = 2 957 / 951, MobileNetV2 K = 8 235.4 / 234.5, 10^6 elements
+// K = 8 79.4 / 79.1, K = 10 94.5 / 94.2; one stream: 2831 / 2832, 1295 / 1296, 943 / 945, 228.8 / 229.6, 75.0 / 75.3, 91.0 / 91.0, 2e6 K = 8 135.0 / 136.6
 // (profiles/mean_launch_shape_sweep.txt).  The in-order mean of lasgd_step_merge_average
 // takes split 1: its z is to be that of the one-kernel form to the bit.
 //
@@ -202,6 +203,16 @@ int hint_of(const lasgd_ctx *c, Use use)
     return array >= from ? 3 : 0;
 }
 
+// A mean on the side stream costs the host an event, a wait, an event and a wait, about 20 us, and both streams their waits.
+// One that moves no more than 16 MiB is done in 3 to 6 us, so it stays on the main stream.  A cycle's us on two streams /
+// on one: K = 3, m = 2, 5000 elements 31 / 11, 10^5 31 / 13, 4e5 (6.4 MB) 38 / 19, 10^6 (16 MB) 40 / 32; K = 8, m = 4, 4e5 (14 MB) 56 / 53;
+// K = 32, m = 4, 10^5 (13 MB) 56 / 53.  Beyond: K = 8, m = 4, 10^6 (36 MB) 123 / 124.  With other work between the calls a longer mean is
+// worth hiding behind it.
+bool mean_on_main(uint32_t participants, uint64_t npad)
+{
+    return (participants + 1ull) * npad * sizeof(float) <= (16ull << 20);
+}
+
 lasgd_tuning default_tuning(const lasgd_ctx &c)
 {
     lasgd_tuning t{};
@@ -209,7 +220,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.kper_step = 1;
     t.kper_merge = 1;
     t.max_blocks = -1;
-    t.avg_split = c.K >= 12 ? 4 : 1;
+    t.avg_split = c.K >= 12 ? 4 : c.K >= 8 && c.side != c.main && !mean_on_main((uint32_t)c.K, c.npad) ? 2 : 1;
     t.avg_max_blocks = -1;
     t.nontemporal = -1;
     t.waves_per_block = 1;
@@ -797,16 +808,6 @@ static lasgd_status do_snapshot(lasgd_ctx *c, uint64_t mask)
     if (st != LASGD_OK) return st;
     c->snap_mask |= mask;
     return LASGD_OK;
-}
-
-// A mean on the side stream costs the host an event, a wait, an event and a wait, about 20 us, and both streams their waits.
-// One that moves no more than 16 MiB is done in 3 to 6 us, so it stays on the main stream.  A cycle's us on two streams /
-// on one: K = 3, m = 2, 5000 elements 31 / 11, 10^5 31 / 13, 4e5 (6.4 MB) 38 / 19, 10^6 (16 MB) 40 / 32; K = 8, m = 4, 4e5 (14 MB) 56 / 53;
-// K = 32, m = 4, 10^5 (13 MB) 56 / 53.  Beyond: K = 8, m = 4, 10^6 (36 MB) 123 / 124.  With other work between the calls a longer mean is
-// worth hiding behind it.
-static bool mean_on_main(uint32_t participants, uint64_t npad)
-{
-    return (participants + 1ull) * npad * sizeof(float) <= (16ull << 20);
 }
 
 static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)

@@ -76,6 +76,20 @@ def test_tuning_round_trip(n):
         dev.close()
 
 
+@pytest.mark.parametrize("K,n,side,split", [(7, 600_000, True, 1), (8, 500_003, True, 2), (8, 400_000, True, 1), (8, 500_003, False, 1),
+                                            (11, 400_000, True, 2), (12, 1000, False, 4)])
+def test_default_split_of_the_mean(K, n, side, split):
+    """Two groups of waves from 8 to 11 replicas where the mean takes the side stream (beyond 16 MiB), and the results with it."""
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    w = W.small(K=K, numels=(n,), m=2, T=3)
+    dev = DeviceReplicas(w, side_stream=side)
+    try:
+        assert dev.ctx.get_tuning()["avg_split"] == split
+    finally:
+        dev.close()
+    assert run_parity(w, side_stream=side, z_exact=split == 1, every_step=False) <= 5
+
+
 def test_same_stream_for_both():
     run_parity(W.small(K=3), side_stream=False)
 
