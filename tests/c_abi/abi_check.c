@@ -5,9 +5,10 @@
  * the state after every step with the CPU oracle (test infrastructure, linked
  * as a separate shared library), bit for bit.
  *
- * Usage: abi_check [K] [m] [T] [fused]      exit status 0 = all steps identical.
+ * Usage: abi_check [K] [m] [T] [fused] [n0]      exit status 0 = all steps identical.
  * fused = 1: the global update and the next All-Reduce go out as one call,
- * lasgd_step_merge_average.  At the end the context-free, allocation-free
+ * lasgd_step_merge_average.  n0: elements of the first tensor (a mean beyond 16 MiB
+ * takes the side stream).  At the end the context-free, allocation-free
  * lasgd_global_update_static is checked on copies of the final state.
  */
 #include <hip/hip_runtime_api.h>
@@ -38,7 +39,7 @@ static float draw(uint64_t seed, uint64_t step, uint64_t k, uint64_t e, float sc
 }
 
 enum { NT = 4 };
-static const int64_t numel[NT] = {5000, 3, 1024, 257};
+static int64_t numel[NT] = {5000, 3, 1024, 257};
 static const float wd[NT] = {1e-4f, 0.0f, 1e-3f, 0.0f};
 
 int main(int argc, char **argv)
@@ -46,10 +47,11 @@ int main(int argc, char **argv)
     const int K = argc > 1 ? atoi(argv[1]) : 3, m = argc > 2 ? atoi(argv[2]) : 2, T = argc > 3 ? atoi(argv[3]) : 6;
     const int fused = argc > 4 ? atoi(argv[4]) : 0;
     const float lr = 0.05f, mu = 0.9f;
+    if (argc > 5) numel[0] = atoll(argv[5]);
+    if (K < 1 || K > 64 || m < 1 || T < 0 || numel[0] < 1) { fprintf(stderr, "bad arguments\n"); return 1; }
     int64_t N = 0, off[NT + 1];
     for (int t = 0; t < NT; ++t) { off[t] = N; N += numel[t]; }
     off[NT] = N;
-    if (K < 1 || K > 64 || m < 1 || T < 0) { fprintf(stderr, "bad arguments\n"); return 1; }
 
     /* host state of the oracle */
     float **ox = calloc(K, sizeof *ox), **ov = calloc(K, sizeof *ov), **os = calloc(K, sizeof *os), **og = calloc(K, sizeof *og);

@@ -226,14 +226,17 @@ def test_mask_order_rules():
 
 @pytest.mark.parametrize("tau_max", [1, 3, 5])
 @pytest.mark.parametrize("fused_mean", [False, True])
-def test_live_polling_replayed_through_the_oracle(tau_max, fused_mean):
+@pytest.mark.parametrize("n", [1 << 18, 1 << 19])
+def test_live_polling_replayed_through_the_oracle(n, tau_max, fused_mean):
     """The real adaptive rule: poll "All Reduce done" on the device, cap at
     tau_max.  Which iterations fire depends on timing, so the decisions are
     recorded and replayed through the oracle; whatever they were, the states
-    must agree, and no replica may take more than tau_max steps per All-Reduce."""
-    w = W.small(K=8, numels=(1 << 18, 4096, 100), T=24)
+    must agree, and no replica may take more than tau_max steps per All-Reduce.
+    2^19 elements: means of 18 MiB, on the side stream; 2^18: on the main stream."""
+    w = W.small(K=8, numels=(n, 4096, 100), T=24)
     orc, dev, grads = _pair(w)
     try:
+        dev.ctx.set_tuning(avg_split=1)        # the in-order mean
         g = grads(1)
         dev.load_grads(g)              # one gradient set for every step: no host sync inside the loop
         orc.prologue(g, w.lr)
@@ -259,17 +262,20 @@ def test_live_polling_replayed_through_the_oracle(tau_max, fused_mean):
         dev.close()
 
 
-@pytest.mark.parametrize("seed", range(16))
+@pytest.mark.parametrize("seed", range(20))
 def test_random_legal_call_sequences(seed):
     """Randomly drawn, legal sequences of the extended calls (masked steps with
     per-replica step sizes, partial means, staggered partial merges with and
     without re-sending, late snapshots, elastic coefficients, the fused
     step + global update + next mean where it is legal): device and oracle
-    must agree after every call group."""
+    must agree after every call group.  The last seeds have a longer list, whose means
+    over four replicas and more take the side stream."""
     r = np.random.default_rng(500 + seed)
     K = int(r.integers(1, 9))
     storage = "bf16" if seed % 3 == 2 else "f32"
     numels = tuple(int(n) for n in r.choice([1, 3, 64, 255, 256, 257, 1000, 2049], size=int(r.integers(1, 5))))
+    if seed >= 16:
+        K, numels = 4 + K // 2, (900_003,) + numels
     w = W.small(K=K, numels=numels, storage=storage, momentum=float(r.choice([0.0, 0.9])),
                 nesterov=bool(r.integers(0, 2)))
     if w.momentum == 0.0:
@@ -393,10 +399,10 @@ def test_means_that_change_streams_from_round_to_round(storage):
 
 
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
-@pytest.mark.parametrize("K,n", [(1, 7_400_003), (4, 1_900_001), (4, 2_700_001)])
+@pytest.mark.parametrize("K,n", [(1, 7_400_003), (4, 1_834_000), (4, 1_900_001), (4, 2_700_001), (4, 8_390_000)])
 def test_calls_on_both_sides_of_the_hints_lines(K, n, storage):
     """From 28, 40 and 128 MiB an array on, steps / updates / means, the SGD-AR step and the fused update stream; the calls
-    mix on one context (28 and 30 MiB, 29 and 41): the same results whichever form each takes."""
+    mix on one context (28.2, 27.99, 29, 41.2 and 128.03 MiB): the same results whichever form each takes."""
     w = W.small(K=K, numels=(n, 129), storage=storage, m=1, T=1)
     orc, dev, grads = _pair(w)
     c = dev.ctx
@@ -415,5 +421,42 @@ def test_calls_on_both_sides_of_the_hints_lines(K, n, storage):
         orc.local_step(g, w.lr); orc.merge(True); c.local_step(w.lr); c.merge(True)
         c.sync()
         compare_state(dev, orc, 0)
+    finally:
+        dev.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("step_mask,merge_mask", [((1 << 64) - 1, 0xf0f0f0f0f0f0f0f0), (0x00000000ffffffff, (1 << 64) - 1),
+                                                  (0x8000000000000001, 0x4000000000000001)])
+def test_masked_step_merge_of_more_than_1e8_replica_parameters(step_mask, merge_mask, storage):
+    """The masked streaming form that asks for no word of its model first: K = 64 and 6200 short tensors, whose slots of 256
+    elements count.  Ragged tensors, full tiles, and several tiles in one."""
+    numels = tuple({0: 256, 25: 515, 50: 255, 75: 257}.get(i % 100, 1 + i % 3) for i in range(6200))
+    w = W.small(K=64, numels=numels, storage=storage, m=1, T=1)
+    rng = np.random.default_rng(11)
+    cast = W.to_bf16_bits if storage == "bf16" else (lambda a: a)
+    x0 = cast(rng.standard_normal(w.N).astype(np.float32) * np.float32(0.02))
+    g = [cast(rng.standard_normal(w.N).astype(np.float32) * np.float32(1e-3)) for _ in range(w.K)]
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    wd = [w.weight_decay] * len(numels)
+    orc = O32.Oracle(w.K, numels, w.momentum, w.nesterov, wd, storage=storage)
+    dev = DeviceReplicas(w, weight_decay=wd)
+    assert 64 * sum((n + 255) // 256 * 256 for n in numels) > 100_000_000
+    lrs = [0.01 * (1 + k % 3) for k in range(64)]
+    try:
+        dev.ctx.set_tuning(avg_split=1)
+        orc.set_model(x0); dev.load_model(x0); dev.load_grads(g)
+        orc.prologue(g, w.lr); dev.prologue(w.lr)
+        orc.local_step(g, lrs, mask=step_mask); orc.merge(True, mask=merge_mask)
+        dev.ctx.step_merge_ex(lrs, step_mask, merge_mask, True)
+        for k in range(64):                    # every replica's parameters; the state tensor by tensor of some of each kind
+            if storage == "bf16":
+                np.testing.assert_array_equal(dev.params(k), orc.x16[k], err_msg=f"x16 replica {k}")
+            else:
+                assert_close(dev.params(k), orc.x[k], f"x replica {k}")
+        for k in (0, 5, 32, 62, 63):
+            assert_close(dev.ctx.read_state(B.STATE_X, k), orc.x[k], f"x replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_S, k), orc.s[k], f"s replica {k}")
     finally:
         dev.close()

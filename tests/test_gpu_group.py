@@ -46,12 +46,14 @@ def test_fused_mean_mobilenet_list_every_step():
     assert run_parity(w, fused_mean=True) == 0
 
 
-def test_fused_mean_mixes_with_the_two_stream_calls():
-    """Cycles alternate between step_merge + average (side stream) and the fused call;
+@pytest.mark.parametrize("n", [5000, 650_003])
+def test_fused_mean_mixes_with_the_two_stream_calls(n):
+    """Cycles alternate between step_merge + average (650,003 elements, a mean of 17 MiB: on
+    the side stream; 5000: on the main stream) and the fused call;
     average_done works after either; the protocol errors are the documented ones."""
     from oracle import lasgd_oracle as O32
     from paper_2203_13085_amd.driver import DeviceReplicas
-    w = W.small(K=6, numels=(5000, 3, 700), m=1, T=8)
+    w = W.small(K=6, numels=(n, 3, 700), m=1, T=8)
     wd = [w.weight_decay] * len(w.numels)
     x0, grads = packed_inputs(w)
     orc = O32.Oracle(w.K, w.numels, w.momentum, w.nesterov, wd)

@@ -345,14 +345,15 @@ def test_rebinding_waits_for_clears_on_other_streams(streams):
         dev.close()
 
 
-@pytest.mark.parametrize("m", [1, 3])
-def test_graph_replay_equals_eager(m):
+@pytest.mark.parametrize("m,n", [(1, 70000), (3, 70000), (1, 1_100_003), (3, 1_100_003)])
+def test_graph_replay_equals_eager(m, n):
     """A captured cycle replayed several times, with eager library work and host
-    synchronisation between the replays, must give the oracle's state every time."""
+    synchronisation between the replays, must give the oracle's state every time.  1,100,003
+    elements: a mean of 21 MiB, so that the fork to the side stream and the join are captured."""
     import torch
     from oracle import lasgd_oracle as O32
     from paper_2203_13085_amd.driver import DeviceReplicas
-    w = W.small(K=4, numels=(70000, 5, 1024, 4099), m=m)
+    w = W.small(K=4, numels=(n, 5, 1024, 4099), m=m)
     x0, grads = packed_inputs(w)
     wd = [w.weight_decay] * len(w.numels)
     dev = DeviceReplicas(w, weight_decay=wd)
@@ -404,13 +405,15 @@ def test_graph_replay_equals_eager(m):
         dev.close()
 
 
-def test_graph_survives_a_change_of_tile_size():
+@pytest.mark.parametrize("n", [9000, 1_500_003])
+def test_graph_survives_a_change_of_tile_size(n):
     """A cycle captured with 256-element tiles is replayed after the context has moved on to
-    1024-element tiles (and back): the graph still points at a live tile table."""
+    1024-element tiles (and back): the graph still points at a live tile table.  On one stream
+    (9000 elements) and with the mean, of 23 MiB, on the side stream."""
     import torch
     from oracle import lasgd_oracle as O32
     from paper_2203_13085_amd.driver import DeviceReplicas
-    w = W.small(K=3, numels=(9000, 5, 1024, 4099), m=2)
+    w = W.small(K=3, numels=(n, 5, 1024, 4099), m=2)
     x0, grads = packed_inputs(w)
     wd = [w.weight_decay] * len(w.numels)
     dev = DeviceReplicas(w, weight_decay=wd)
