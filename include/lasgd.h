@@ -7,7 +7,7 @@
  * made meanwhile (Algorithm 1, Sec. 4).  This library holds K workers
  * ("replicas", the paper's P nodes) on ONE GPU and implements the per-iteration
  * arithmetic of that algorithm; the All-Reduce becomes a reduction over the K
- * sent models in device memory, run on a second stream.
+ * sent models in device memory, run on a second stream (a short one on the first).
  *
  * Conventions
  *   - One opaque context owns all K replicas.  Every operation is an
@@ -111,7 +111,7 @@ typedef struct {
                               a short window; multiples of 32 keep a tile on one XCD's L2)           */
     int32_t waves_per_block; /* independent waves per workgroup in the multi-tensor kernels: 1, 2 or 4  */
     int32_t race_probe;    /* debugging aid, 1 = on, <0 = off (default): lasgd_average first fills z with NaN
-                              on the side stream, so a global update that did not wait for the mean shows
+                              on the stream the mean runs on, so a global update that did not wait for the mean shows
                               as NaN in the parameters.  Results are unchanged when the ordering holds.  */
     int32_t group_r;       /* replicas one wave takes at a time in the one-workgroup-per-tile kernels
                               (lasgd_step_merge_average, lasgd_sgd_ar_step): 1, 2 or 4; the workgroup has
@@ -173,8 +173,8 @@ lasgd_status lasgd_zero_grads(lasgd_ctx *ctx, void *stream);
 /*
  * The send of Algorithm 1 (steps 4 and 9c): the model handed to the All-Reduce is
  * kept, s[k] <- x[k].  Main stream.
- * Errors: STATE (an average is in flight and not yet merged: the side stream
- * may still be reading s), HIP.
+ * Errors: STATE (an average is in flight and not yet merged: it may still be
+ * reading s), HIP.
  */
 lasgd_status lasgd_snapshot(lasgd_ctx *ctx);
 
@@ -258,7 +258,8 @@ lasgd_status lasgd_local_step_ex(lasgd_ctx *ctx, const float *lr, uint64_t mask)
 lasgd_status lasgd_snapshot_ex(lasgd_ctx *ctx, uint64_t mask);
 
 /* z <- mean over the replicas in `mask` (non-empty) of s[k]; with beta != 1
- * (lasgd_set_elastic) blended into the previous centre.  Side stream.
+ * (lasgd_set_elastic) blended into the previous centre.  Side stream, or the main stream
+ * for a mean that moves no more than 16 MiB, as lasgd_average; the participants count.
  * Errors: as lasgd_average, per participant. */
 lasgd_status lasgd_average_ex(lasgd_ctx *ctx, uint64_t mask);
 

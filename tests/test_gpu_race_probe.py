@@ -1,7 +1,7 @@
 """The cross-stream ordering of z under the race probe.
 
-With tuning race_probe = 1, lasgd_average fills z with NaN on the side stream
-right before the mean rewrites it.  The main stream's next global update must
+With tuning race_probe = 1, lasgd_average fills z with NaN on the mean's stream (here the
+side stream, the means being long) right before the mean rewrites it.  The main stream's next global update must
 wait for the end of that mean (the z event); if it did not, it would read NaN
 wherever the mean had not arrived yet, and NaN would stay in the parameters for
 good.  The probe changes no result when the ordering holds, so the runs are
