@@ -12,7 +12,8 @@
  * Conventions
  *   - One opaque context owns all K replicas.  Every operation is an
  *     asynchronous enqueue on a stream borrowed from the caller; nothing
- *     blocks the host except lasgd_read_state, lasgd_sync and lasgd_destroy.
+ *     blocks the host except lasgd_bind, lasgd_set_tuning, lasgd_read_state,
+ *     lasgd_sync and lasgd_destroy.
  *   - All pointers named "device" are HIP device pointers; all others are
  *     host pointers.  Config and pointer arrays are copied during the call.
  *   - Errors are return codes; nothing throws or aborts.  Every argument and
