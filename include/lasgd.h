@@ -30,8 +30,10 @@
  *   (one device buffer per replica k and tensor t, numel[t] elements, 16-byte
  *   aligned, fp32 or bf16 according to `storage`), and both streams.
  * Memory owned by the library:  momentum v[k], sent models s[k], the mean z,
- *   the fp32 master copy of the parameters when storage is bf16, and the
- *   lookup tables.
+ *   the fp32 master copy of the parameters when storage is bf16 (from 8 MiB of it
+ *   on a global update that re-sends leaves the model in s alone until the next
+ *   step; once a call has been recorded into a graph, in both), and the lookup
+ *   tables.
  *
  * Paper <-> calls.  Prologue (steps 1-5): lasgd_local_step(eta_0),
  *   lasgd_snapshot, lasgd_average.  Loop iteration without global update

@@ -67,6 +67,15 @@ struct lasgd_ctx {
     std::vector<char> bound;
     int32_t n_bound = 0;
 
+    // bf16 storage: where each replica's model is (bit k = replica k), see place_models
+    uint64_t at_s = 0;               // in s[k], which it has just re-sent, and nowhere else
+    bool both_places = true;         // a global update that re-sends writes the master copy too: small models, and any of which
+                                     // a call has been recorded into a graph
+    bool settled = true;             // both_places: all models are back in the master copies, on the main stream
+    uint64_t settle_mask = 0;        // those that were in s when a call was first recorded
+    unsigned long long settle_graph = 0;   // the capture that the copy was last recorded into
+    uint32_t *settle_done = nullptr;       // device word, see settle_kernel
+
     // protocol state (bit k = replica k)
     bool master_ready = false;   // bf16: master copy initialised
     uint64_t all = 0;            // every replica
@@ -393,9 +402,57 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     return LASGD_OK;
 }
 
-lasgd_status launch_apply(lasgd_ctx *c, const ApplyPlan &p)
+// Is this stream recording into a graph rather than executing?  id: which capture, one of its own for each.
+bool is_capturing(hipStream_t st, unsigned long long *id = nullptr)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if ((id ? hipStreamGetCaptureInfo(st, &cs, id) : hipStreamIsCapturing(st, &cs)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+// bf16 storage: before a call that reads or writes the models.  A global update that re-sends leaves the model in s alone
+// (apply_tile), and c->at_s says where each call finds it.  A recorded call cannot go by that: it is replayed whenever the
+// caller likes.  So once a call has been recorded, every update writes the master copy too, recorded or not, and models that
+// are in s at that moment are copied back once (settle_kernel), by the first graph that is replayed or the first call that runs.
+//
+// From 8 MiB an array on.  us, both places / s alone, an update every step, every third step, two fused ones, K = 4:
+// 0.3 MB an array 10 / 10, 21 / 21, 16 / 16; 4 MB 13.7 / 13.1, 25.2 / 23.7, 20.3 / 18.5; 16 MB 27.8 / 22.4, 55.9 / 51.9,
+// 52.6 / 45.3; 32 MB 54.0 / 44.6, 109.9 / 106.6, 98.9 / 79.0.  A graph recorded while models are in s keeps the copy's kernel
+// as its first node, which from the second replay on does nothing in 1.7 us: more than is to be gained below.
+constexpr uint64_t kOneCopyFrom = 8ull << 20;
+constexpr uint32_t kSettleBlocks = 256;
+lasgd_status place_models(lasgd_ctx *c)
+{
+    if (c->storage != LASGD_BF16) return LASGD_OK;
+    unsigned long long id = 0;
+    const bool capturing = !(c->both_places && c->settled) && is_capturing(c->main, &id);
+    if (!c->both_places) {
+        if (!capturing) return LASGD_OK;
+        c->both_places = true;
+        c->settle_mask = c->at_s;
+        c->settled = !c->settle_mask;
+        c->at_s = 0;
+    }
+    if (c->settled || (capturing && c->settle_graph == id)) return LASGD_OK;
+    hipLaunchKernelGGL(settle_kernel, dim3(kSettleBlocks), dim3(256), 0, c->main, c->x32, c->s, c->npad, c->settle_mask, c->settle_done);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    if (capturing) c->settle_graph = id;
+    else c->settled = true;
+    return LASGD_OK;
+}
+
+// Plans before it launches: after the last check of a call, and just before its launch.
+lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
 {
     const bool bf16 = c->storage == LASGD_BF16;
+    const lasgd_status st = place_models(c);
+    if (st != LASGD_OK) return st;
+    p.a.at_s = c->at_s;
+    p.a.also_x = c->both_places ? 1 : 0;
     const int vec = c->tune.vec;
     int nt = hint_of(c, p.op == OP_STEP && c->fused_cycle ? USE_FUSED : USE_CYCLE);
     if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad)) nt |= 4;
@@ -409,6 +466,12 @@ lasgd_status launch_apply(lasgd_ctx *c, const ApplyPlan &p)
     default: e = launch_vec<OP_INIT, true>(p.a, nullptr, p.grid, p.bs, c->main, vec, nt); break;
     }
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    if (bf16 && p.op != OP_SNAPSHOT) {
+        const bool merging = p.op == OP_MERGE || p.op == OP_STEP_MERGE;
+        const uint64_t stepped = p.op == OP_MERGE ? 0 : xa ? xa->step_mask : c->all, merged = !merging ? 0 : xa ? xa->merge_mask : c->all;
+        c->at_s &= ~(stepped | merged);
+        if (p.a.resnap && !c->both_places) c->at_s |= merged;
+    }
     return LASGD_OK;
 }
 
@@ -487,8 +550,10 @@ hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t s
 #define LASGD_GROUP(RR)                                                                                  \
     do {                                                                                                 \
         if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes); \
-        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes);         \
+        else if (BF16 && at_s) hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, BF16>), g.grid, g.bs, g.lds, st, a, g.passes); \
+        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, false>), g.grid, g.bs, g.lds, st, a, g.passes);  \
     } while (0)
+    const bool at_s = a.at_s == (a.K == 64u ? ~0ull : (1ull << a.K) - 1ull);
     if (g.R == 1) LASGD_GROUP(1);
     else if (g.R == 2) LASGD_GROUP(2);
     else LASGD_GROUP(4);
@@ -568,17 +633,6 @@ lasgd_status check_ready_to_step(lasgd_ctx *c, float lr)
     return LASGD_OK;
 }
 
-// Is this stream recording into a graph rather than executing?
-bool is_capturing(hipStream_t st)
-{
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return cs != hipStreamCaptureStatusNone;
-}
-
 // Until no queued clear of the gradients can still read the records.  Clears run on streams that the caller names and may
 // since have destroyed, so this waits for the device: an event after each clear would do for the stream alone, but costs
 // every clear 3.5 us on the device (MobileNetV2 list, K = 4, clear + accumulate + step twice 251 us without, 258 with).
@@ -596,6 +650,7 @@ void release(lasgd_ctx *c)
     for (const lasgd_ctx::Tables &t : c->tables_by_vec)
         if (t.mem) (void)hipFree(t.mem);
     if (c->records) (void)hipFree(c->records);
+    if (c->settle_done) (void)hipFree(c->settle_done);
     if (c->evA) (void)hipEventDestroy(c->evA);
     if (c->evZ) (void)hipEventDestroy(c->evZ);
     delete c;
@@ -656,6 +711,7 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     CREATE_HIP(hipGetDevice(&c->device));
     const bool bf16 = c->storage == LASGD_BF16;
     const uint64_t per = c->npad * sizeof(float);
+    c->both_places = !bf16 || c->K * per < kOneCopyFrom;
     const uint64_t n_arrays = (uint64_t)c->K * (bf16 ? 3 : 2) + 1;       // v, s (, x32), z
     CREATE_HIP(hipMalloc((void **)&c->arena, n_arrays * per));
     CREATE_HIP(hipMemsetAsync(c->arena, 0, n_arrays * per, c->main));
@@ -663,6 +719,10 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     c->s = c->v + (uint64_t)c->K * c->npad;
     c->z = c->s + (uint64_t)c->K * c->npad;
     c->x32 = bf16 ? c->z + c->npad : nullptr;
+    if (bf16) {
+        CREATE_HIP(hipMalloc((void **)&c->settle_done, sizeof(uint32_t)));
+        CREATE_HIP(hipMemset(c->settle_done, 0, sizeof(uint32_t)));
+    }
     const size_t tab = (size_t)c->K * c->n_tensors * sizeof(Record);
     CREATE_HIP(hipMalloc((void **)&c->records, tab));
     CREATE_HIP(hipMemset(c->records, 0, tab));
@@ -799,10 +859,12 @@ static lasgd_status do_snapshot(lasgd_ctx *c, uint64_t mask)
     if ((st = check_mask(c, mask, false, "mask")) != LASGD_OK) return st;
     if (mask & c->pending_mask)
         return fail(c, LASGD_ERR_STATE, "an average over some of these replicas is in flight and not merged: s may still be read");
-    if (mask == c->all) st = enqueue_apply(c, OP_SNAPSHOT, 0.f, 0);
-    else {
+    if ((st = place_models(c)) != LASGD_OK) return st;
+    const uint64_t copied = mask & ~c->at_s;           // a model that is in s only has been sent already
+    if (copied == c->all) st = enqueue_apply(c, OP_SNAPSHOT, 0.f, 0);
+    else if (copied) {
         ExtArgs x{};
-        fill_ext(c, x, nullptr, mask, 0);
+        fill_ext(c, x, nullptr, copied, 0);
         st = enqueue_apply(c, OP_SNAPSHOT, 0.f, 0, &x);
     }
     if (st != LASGD_OK) return st;
@@ -999,8 +1061,11 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     fill_common(c, a);
     a.neg_lr = -lr;
     const GroupShape g = group_shape(c, 0);
+    if ((st = place_models(c)) != LASGD_OK) return st;
+    a.at_s = c->at_s;
     hipError_t e = launch_group(0, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_SGD_AR));
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    c->at_s = 0;
     return LASGD_OK;
 }
 
@@ -1034,8 +1099,12 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         a.resnap = 1;
         const GroupShape g = group_shape(c, 1);
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
+        if ((st = place_models(c)) != LASGD_OK) return st;
+        a.at_s = c->at_s;
+        a.also_x = c->both_places ? 1 : 0;
         hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_FUSED));
         if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+        if (!c->both_places) c->at_s = c->all;
     }
     // every replica has merged and re-sent, and the mean of the sent models is (being) written to z
     // on the main stream: the same state as after lasgd_step_merge(lr, 1) + lasgd_average
@@ -1068,8 +1137,10 @@ lasgd_status lasgd_read_state(lasgd_ctx *c, int32_t which, int32_t k, int32_t te
     if (n != want) return fail(c, LASGD_ERR_INVALID, "n = %lld, expected %lld", (long long)n, (long long)want);
     const bool user_x = which == LASGD_STATE_X && c->storage == LASGD_F32;
     if (user_x && !c->bound[(size_t)k]) return fail(c, LASGD_ERR_STATE, "replica %d is not bound", k);
-    lasgd_status st = lasgd_sync(c);
+    lasgd_status st = which == LASGD_STATE_X ? place_models(c) : LASGD_OK;
     if (st != LASGD_OK) return st;
+    if ((st = lasgd_sync(c)) != LASGD_OK) return st;
+    if (which == LASGD_STATE_X && ((c->at_s >> k) & 1ull)) which = LASGD_STATE_S;
     const float *base = which == LASGD_STATE_V ? c->v : which == LASGD_STATE_S ? c->s : which == LASGD_STATE_Z ? c->z : c->x32;
     const int32_t t0 = tensor < 0 ? 0 : tensor, t1 = tensor < 0 ? c->n_tensors : tensor + 1;
     float *out = dst;

@@ -79,6 +79,10 @@ struct ApplyArgs {
     uint32_t nitems;        // ntiles * kgroups
     float neg_lr, mu;
     int32_t nesterov, resnap;
+    // bf16 storage: bit k says that replica k's model is s[k], which it has just re-sent, and that its master copy is out of
+    // date.  A global update that re-sends leaves it that way unless also_x, and the next step writes the master again.
+    uint64_t at_s;
+    int32_t also_x;
     uint32_t tile_elems;    // 256 * VEC
     uint32_t wpb, nwaves;   // waves per workgroup, and in the grid (the replica-group kernels: workgroups in the grid)
     uint32_t chunk;         // item order, see apply_kernel
@@ -287,15 +291,22 @@ template <bool FULL> __device__ __forceinline__ uint32_t lane_elems(uint32_t e0,
 
 // Apply one operation to VEC rows of one replica's tile.  `count` bounds the ragged
 // path.  x/g point at the tile's first element in the caller's buffers
-// (storage dtype), xm/v/s at the tile's first element in the arenas.
+// (storage dtype), xm/v/s at the tile's first element in the arenas.  bf16 storage: the model is read from xr, which is
+// xm or, where it has just been re-sent (AT_S), s.
 //
 // A ragged tile (the last of a tensor) takes the same 128-bit accesses in the lanes
 // that have all four elements, and only the one lane that a tensor's odd end leaves
 // with one to three goes element by element: all its loads before its first store,
 // as everywhere, so that the wave waits once for memory.
 // ALONE: the operation is the whole kernel's, not one of several in a masked call.
-template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT, bool ALONE>
-__device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const void *gu, float *xm,
+//
+// bf16 storage, where the fp32 model and s are both the library's: a global update that re-sends would write the same values
+// twice, and the next pass would read them from either place.  So it writes s alone, and whoever needs the model next reads it
+// there: 4 bytes a replica-parameter fewer per update, 8 where an update follows directly, which then reads s once.  us before /
+// after, over three states in turn: ResNet-18 list K = 12, two fused updates in a row 1405 / 990; ResNet-50 K = 32, an update
+// every eight steps 21617 / 21212.
+template <int VEC, int OP, bool BF16, int NT, bool FULL, bool EXT, bool ALONE, bool AT_S>
+__device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const void *gu, const float *xr, float *xm,
                                            float *v, float *s, const float4 (&zt)[VEC], float wd,
                                            uint32_t count, uint32_t lane, float neg_lr, float alpha)
 {
@@ -305,11 +316,14 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     constexpr bool NEED_S = (OP == OP_MERGE || OP == OP_STEP_MERGE);
     constexpr bool WRITE_X = (OP != OP_SNAPSHOT);
     constexpr bool WRITE_V = NEED_V || OP == OP_INIT;
-    float *xf = BF16 ? xm : static_cast<float *>(xu);          // where the fp32 model lives
+    const float *xf = BF16 ? xr : static_cast<const float *>(xu);          // where the fp32 model lives
+    float *xw = BF16 ? xm : static_cast<float *>(xu);                      // and where it goes
     uint16_t *x16 = static_cast<uint16_t *>(xu);
     const float *gf = static_cast<const float *>(gu);
     const uint16_t *g16 = static_cast<const uint16_t *>(gu);
+    constexpr bool LOAD_S = NEED_S && !AT_S;
     const bool write_s = (OP == OP_SNAPSHOT) || (NEED_S && a.resnap);
+    const bool write_x = !BF16 || !NEED_S || !a.resnap || a.also_x;
 
     if constexpr (OP == OP_SNAPSHOT && !FULL) {          // a copy
 #pragma unroll
@@ -341,7 +355,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
             if constexpr (NEED_X) x[j] = ld4<NT>(xf + e);
             if constexpr (OP == OP_INIT) x[j] = widen4(ld2<NT>(x16 + e));
             if constexpr (NEED_V) vv[j] = ld4<NT>(v + e);
-            if constexpr (NEED_S) ss[j] = ld4<NT>(s + e);
+            if constexpr (LOAD_S) ss[j] = ld4<NT>(s + e);
         }
     }
     if constexpr (!FULL) {
@@ -354,7 +368,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
                     if constexpr (NEED_X) comp(x[j], c) = *as_global<float>(xf + e + c);
                     if constexpr (OP == OP_INIT) comp(x[j], c) = bf16_widen(*as_global<uint16_t>(x16 + e + c));
                     if constexpr (NEED_V) comp(vv[j], c) = *as_global<float>(v + e + c);
-                    if constexpr (NEED_S) comp(ss[j], c) = *as_global<float>(s + e + c);
+                    if constexpr (LOAD_S) comp(ss[j], c) = *as_global<float>(s + e + c);
                 })
             }
         }
@@ -362,6 +376,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
         const uint32_t e = j * 256u + lane * 4u, n = lane_elems<FULL>(e, count);
+        if constexpr (AT_S) ss[j] = x[j];
         if constexpr (NEED_G)
             LASGD_FOR4(step_elem(comp(x[j], c), comp(vv[j], c), compv(g[j], c), wd, a.mu,
                                  neg_lr, a.nesterov);)
@@ -375,7 +390,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
         if (FULL || n == 4u) {
             if constexpr (WRITE_V) st4<NT>(v + e, vv[j]);
             if constexpr (WRITE_X) {
-                st4<NT>(xf + e, x[j]);
+                if (write_x) st4<NT>(xw + e, x[j]);
                 if constexpr (BF16 && OP != OP_INIT) st2<NT>(x16 + e, round4(x[j]));
             }
             if (write_s) st4<NT>(s + e, x[j]);
@@ -385,7 +400,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
                 LASGD_FOR4(if (c < 3 && (uint32_t)c < n) {
                     if constexpr (WRITE_V) *as_global<float>(v + e + c) = compv(vv[j], c);
                     if constexpr (WRITE_X) {
-                        *as_global<float>(xf + e + c) = compv(x[j], c);
+                        if (write_x) *as_global<float>(xw + e + c) = compv(x[j], c);
                         if constexpr (BF16 && OP != OP_INIT) *as_global<uint16_t>(x16 + e + c) = (uint16_t)bf16_round(compv(x[j], c));
                     }
                     if (write_s) *as_global<float>(s + e + c) = compv(x[j], c);
@@ -481,10 +496,18 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
                 gu = reinterpret_cast<const char *>(rec.g) + t.toff * esz;
             const size_t ao = (size_t)k * a.npad + t.aoff;
             float *xm = BF16 ? a.x32 + ao : nullptr;
+            const bool at_s = BF16 && ((a.at_s >> k) & 1ull);
+            const float *xr = at_s ? a.s + ao : xm;
+#define LASGD_TILE_AT(OPX, NLR, AL, AT)                                                                      \
+    do {                                                                                                     \
+        if (__builtin_expect(full, 1)) apply_tile<VEC, OPX, BF16, NT, true, EXT, OPX == OP, AT>(a, xu, gu, xr, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
+        else apply_tile<VEC, OPX, BF16, NT, false, EXT, OPX == OP, AT>(a, xu, gu, xr, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL);     \
+    } while (0)
 #define LASGD_TILE(OPX, NLR, AL)                                                                             \
     do {                                                                                                     \
-        if (__builtin_expect(full, 1)) apply_tile<VEC, OPX, BF16, NT, true, EXT, OPX == OP>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL); \
-        else apply_tile<VEC, OPX, BF16, NT, false, EXT, OPX == OP>(a, xu, gu, xm, a.v + ao, a.s + ao, zt, t.wd, t.count, lane, NLR, AL);     \
+        constexpr bool MAY = BF16 && (OPX == OP_MERGE || OPX == OP_STEP_MERGE);                              \
+        if (MAY && at_s) LASGD_TILE_AT(OPX, NLR, AL, MAY);                                                   \
+        else LASGD_TILE_AT(OPX, NLR, AL, false);                                                             \
     } while (0)
             if constexpr (!EXT) {
                 LASGD_TILE(OP, a.neg_lr, 1.0f);
@@ -504,6 +527,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
                 }
             }
 #undef LASGD_TILE
+#undef LASGD_TILE_AT
             if (++j == k1) break;
             rec = load_record(a, replica_at<EXT>(a, xa, j), tensor);
         }
@@ -763,7 +787,8 @@ __device__ __forceinline__ float group_mean_of(double acc, const ApplyArgs &a)
 // Where replica k keeps one tile: the fp32 model (the caller's buffer, or the master
 // copy for bf16 storage), the caller's 16-bit parameters and gradient, v and s.
 template <bool BF16> struct ReplicaTile {
-    float *xf, *v, *s;
+    const float *xf;       // read here, written at xw: another place only where the model has just been re-sent (at_s)
+    float *xw, *v, *s;
     uint16_t *x16;
     const void *g;
 };
@@ -774,7 +799,8 @@ __device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, co
     const size_t ao = (size_t)k * a.npad + t.aoff;
     char *xu = reinterpret_cast<char *>(rec.x) + t.toff * ESZ;
     ReplicaTile<BF16> r;
-    r.xf = BF16 ? a.x32 + ao : reinterpret_cast<float *>(xu);
+    r.xw = BF16 ? a.x32 + ao : reinterpret_cast<float *>(xu);
+    r.xf = BF16 && ((a.at_s >> k) & 1ull) ? a.s + ao : r.xw;
     r.x16 = reinterpret_cast<uint16_t *>(xu);
     r.v = a.v + ao;
     r.s = a.s + ao;
@@ -884,7 +910,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
         LASGD_FOR4(step_elem(comp(x[r], c), comp(v[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
         if (mine[r]) {
             row_st<NT, FULL>(rt[r].v, e0, n, v[r]);
-            row_st<NT, FULL>(rt[r].xf, e0, n, x[r]);
+            row_st<NT, FULL>(rt[r].xw, e0, n, x[r]);
             if constexpr (BF16) row_st16<NT, FULL>(rt[r].x16, e0, n, x[r]);
         }
     }
@@ -906,7 +932,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
             LASGD_FOR4(step_elem(comp(xx[r], c), comp(vv[r], c), compv(gbar, c), t.wd, a.mu, a.neg_lr, a.nesterov);)
             if (ok[r]) {
                 row_st<NT, FULL>(q[r].v, e0, n, vv[r]);
-                row_st<NT, FULL>(q[r].xf, e0, n, xx[r]);
+                row_st<NT, FULL>(q[r].xw, e0, n, xx[r]);
                 if constexpr (BF16) row_st16<NT, FULL>(q[r].x16, e0, n, xx[r]);
             }
         }
@@ -943,7 +969,8 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
 // Same roundings as step_merge followed by the in-order mean.
 // STAGED: the gradients are asked for when everything else has arrived, so that a wave has
 // three quarters of its loads in flight.
-template <int R, bool BF16, int NT, bool FULL, bool STAGED>
+// AT_S: every replica's model is the one it sent last (see apply_tile), read once for both.
+template <int R, bool BF16, int NT, bool FULL, bool STAGED, bool AT_S>
 __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
                                                     uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
 {
@@ -967,7 +994,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
             if constexpr (STAGED) {
                 if (r == 0 && p == 0u) z = ld4<0>(a.z + t.aoff + e0);
             }
-            ss[r] = ld4<NT>(q[r].s + e0);
+            if constexpr (!AT_S) ss[r] = ld4<NT>(q[r].s + e0);
         }
         if constexpr (STAGED) {
             wait_for_loads();
@@ -975,11 +1002,12 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if constexpr (AT_S) ss[r] = x[r];
             LASGD_FOR4(step_elem(comp(x[r], c), comp(v[r], c), compv(g[r], c), t.wd, a.mu, a.neg_lr, a.nesterov);)
             LASGD_FOR4(comp(x[r], c) = merge_elem(compv(x[r], c), compv(ss[r], c), compv(z, c));)
             if (kw[r] < a.K) {
                 row_st<NT, FULL>(q[r].v, e0, n, v[r]);
-                row_st<NT, FULL>(q[r].xf, e0, n, x[r]);
+                if (!BF16 || a.also_x) row_st<NT, FULL>(q[r].xw, e0, n, x[r]);
                 if constexpr (BF16) row_st16<NT, FULL>(q[r].x16, e0, n, x[r]);
                 row_st<NT, FULL>(q[r].s, e0, n, x[r]);
                 *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = x[r];
@@ -1001,7 +1029,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
     }
 }
 
-template <int R, bool BF16, int NT, bool STAGED>
+template <int R, bool BF16, int NT, bool STAGED, bool AT_S>
 __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a, const uint32_t passes)
 {
     extern __shared__ float lds[];                        // [K][256]
@@ -1017,8 +1045,8 @@ __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a
         for (uint32_t row = 0; row < rows; ++row) {
             if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
             again = true;
-            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
-            else step_merge_mean_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true, STAGED, AT_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            else step_merge_mean_row<R, BF16, NT, false, STAGED, AT_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
     }
 }
@@ -1052,6 +1080,22 @@ __global__ __launch_bounds__(64) void zero_grads_kernel(const ApplyArgs a)
             }
         }
     }
+}
+
+// bf16 storage, once, before the first work that a recorded graph may hold: the models of `mask` from s back to the master copies.
+// Graphs are replayed at any time, so with one about nothing may depend on where the last call left a model.  Whichever comes
+// first on the main stream, a replay or another call, does the copy; `done` counts the workgroups that have (gridDim.x of them
+// in every launch), and no workgroup can find it full before its own share is done.
+__global__ __launch_bounds__(256) void settle_kernel(float *x32, const float *s, uint64_t npad, uint64_t mask, uint32_t *done)
+{
+    if (*as_global<uint32_t>(done) >= gridDim.x) return;
+    const uint64_t stride = (uint64_t)gridDim.x * 256u;
+    for (; mask; mask &= mask - 1ull) {
+        const uint64_t k = (uint64_t)__builtin_ctzll(mask);
+        for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < npad / 4u; i += stride) st4<3>(x32 + k * npad + i * 4u, ld4<3>(s + k * npad + i * 4u));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0u) atomicAdd(done, 1u);
 }
 
 // Debugging aid for the two-stream protocol: fill z with NaN.

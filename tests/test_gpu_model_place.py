@@ -1,0 +1,149 @@
+"""bf16 storage, from 8 MiB an array on: after a global update that re-sends, the fp32 model is kept once, in s, and the next
+call that needs it reads it there.  Whatever calls follow one another, and whatever graphs are recorded and replayed between them, the state has to be
+the oracle's, to the bit."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2203_13085_amd import workloads as W            # noqa: E402
+from tests.parity_util import compare_state                # noqa: E402
+from tests.test_gpu_ext import _pair                       # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _calls(orc, c, g, w):
+    """The calls by name: each does the same on both sides."""
+    full = (1 << w.K) - 1
+    lrs = [w.lr * (1 - 0.01 * k) for k in range(w.K)]
+
+    def both(o, d):
+        def f(mask=full):
+            o(mask)
+            d(mask)
+        return f
+
+    return {
+        "step": both(lambda m: orc.local_step(g, lrs, mask=m), lambda m: c.local_step_ex(lrs, m)),
+        "plain_step": both(lambda m: orc.local_step(g, w.lr), lambda m: c.local_step(w.lr)),
+        "send": both(lambda m: orc.snapshot(mask=m), lambda m: c.snapshot_ex(m)),
+        "mean": both(lambda m: orc.average(mask=m), lambda m: c.average_ex(m)),
+        "merge": both(lambda m: orc.merge(True, mask=m), lambda m: c.merge_ex(m, True)),
+        "merge_keep": both(lambda m: orc.merge(False, mask=m), lambda m: c.merge_ex(m, False)),
+        "update": both(lambda m: (orc.local_step(g, w.lr), orc.merge(True, mask=m)),
+                       lambda m: c.step_merge(w.lr, True) if m == full else c.step_merge_ex([w.lr] * w.K, full, m, True)),
+        "update_keep": both(lambda m: (orc.local_step(g, w.lr), orc.merge(False)), lambda m: c.step_merge(w.lr, False)),
+        "fused": both(lambda m: (orc.local_step(g, w.lr), orc.merge(True), orc.average()), lambda m: c.step_merge_average(w.lr)),
+        "sgd_ar": both(lambda m: orc.sgd_ar_step(g, w.lr), lambda m: c.sgd_ar_step(w.lr)),
+    }
+
+
+SEQUENCES = [
+    "mean update mean update plain_step mean plain_step update",                 # an update right after an update, and steps between
+    "mean merge mean merge plain_step send mean merge_keep plain_step send mean update_keep send mean update",
+    "mean update sgd_ar mean merge sgd_ar plain_step send mean update",          # the comparator reads the model too
+    "mean fused fused plain_step fused update mean fused merge plain_step",      # one pass after another, and out again
+    "mean:odd update:odd step:odd mean:odd merge:odd step:even mean:odd update:odd send:even mean update",   # some in s, some not
+    "mean merge:even step:odd merge:odd step:low mean fused step:odd update step:even send",
+]
+
+
+SHAPES = [(1, (2_097_001, 3), 4), (5, (700, 3, 256, 420_001), 4), (5, (700, 3, 256, 420_001), 3), (12, (175_003, 64), 3),
+          (13, (161_515, 64), 3), (13, (161_515, 64), 4), (4, (523_265, 500), 4)]        # the last: one row short of 8 MiB
+
+
+@pytest.mark.parametrize("K,numels,hint,sequence", [s + (q,) for s in SHAPES for q in SEQUENCES if s[0] > 1 or ":" not in q])
+def test_sequences_of_calls(K, numels, hint, sequence):
+    w = W.small(K=K, numels=numels, storage="bf16")
+    orc, dev, grads = _pair(w)
+    full = (1 << K) - 1
+    masks = {"odd": 0xaaaaaaaaaaaaaaaa & full, "even": 0x5555555555555555 & full, "low": 1}
+    try:
+        dev.ctx.set_tuning(nontemporal=hint, avg_split=1)
+        g = grads(0)
+        dev.load_grads(g)
+        calls = _calls(orc, dev.ctx, g, w)
+        calls["plain_step"]()
+        calls["send"]()
+        for word in sequence.split():
+            name, _, mask = word.partition(":")
+            calls[name](masks.get(mask, full))
+        compare_state(dev, orc, 0)
+    finally:
+        dev.close()
+
+
+@pytest.mark.parametrize("first", ["replay", "call"])
+@pytest.mark.parametrize("sent", ["all", "some"])
+@pytest.mark.parametrize("fused", [False, True])
+def test_graphs_recorded_while_the_models_are_in_s(fused, sent, first):
+    """Two graphs, a cycle and a lone local step, recorded when all or some of the models are in s only, then replayed and
+    mixed with ordinary calls in either order: a replay has to find the model wherever the last call left it."""
+    w = W.small(K=5, numels=(700, 3, 256, 420_001), storage="bf16")
+    orc, dev, grads = _pair(w)
+    full = (1 << w.K) - 1
+    try:
+        dev.ctx.set_tuning(avg_split=1)
+        g = grads(0)
+        dev.load_grads(g)
+        calls = _calls(orc, dev.ctx, g, w)
+        for name in ("plain_step", "send", "mean", "update"):
+            calls[name]()
+        if fused:
+            calls["mean"]()
+            calls["fused"]()
+        if sent == "some":
+            calls["step"](0b00110)
+        cycle = dev.capture_fused_cycle(w.lr, 2) if fused else dev.capture_cycle(w.lr, 2)
+        step = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(step, stream=dev.main):
+            dev.ctx.local_step(w.lr)
+
+        def replay(graph):
+            with torch.cuda.stream(dev.main):
+                graph.replay()
+            if graph is step:
+                orc.local_step(g, w.lr)
+            elif fused:
+                orc.local_step(g, w.lr); orc.local_step(g, w.lr); orc.merge(True); orc.average()
+            else:
+                orc.average(); orc.local_step(g, w.lr); orc.local_step(g, w.lr); orc.merge(True)
+
+        def eager():
+            if fused:
+                calls["plain_step"]()
+                calls["fused"]()
+            else:
+                calls["mean"]()
+                calls["plain_step"]()
+                calls["update"]()
+
+        for i, what in enumerate([first, "replay", "call", "step", "replay", "replay", "call", "step", "step", "call", "replay"]):
+            eager() if what == "call" else replay(step if what == "step" else cycle)
+            if i % 3 == 0:
+                compare_state(dev, orc, i)
+        compare_state(dev, orc, 99)
+    finally:
+        dev.close()
+
+
+def test_a_model_in_s_is_read_after_recording_before_any_replay():
+    w = W.small(K=3, numels=(700_001, 3), storage="bf16")
+    orc, dev, grads = _pair(w)
+    try:
+        g = grads(0)
+        dev.load_grads(g)
+        calls = _calls(orc, dev.ctx, g, w)
+        for name in ("plain_step", "send", "mean", "update"):
+            calls[name]()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=dev.main):
+            dev.ctx.sgd_ar_step(w.lr)
+        compare_state(dev, orc, 0)
+        for rep in range(3):
+            with torch.cuda.stream(dev.main):
+                graph.replay()
+            orc.sgd_ar_step(g, w.lr)
+            compare_state(dev, orc, rep + 1)
+    finally:
+        dev.close()
