@@ -100,10 +100,10 @@ typedef struct {
                               kernels also take their streaming shapes: the step and merge kernels bound
                               their waves per CU through LDS that they ask for and do not use (up to a CU's
                               160 KiB among the waves of a local step), and lasgd_step_merge_average takes
-                              two kernels beyond 12 replicas.  4 switches that off too.  Once set, it holds for
-                              every call.  <0 = default: each call decides by the size of one array of all
+                              two kernels beyond 12 replicas (bf16 24).  4 switches that off too.
+                              Once set, it holds for every call.  <0 = default: each call decides by the size of one array of all
                               replicas, from 28 MiB on for steps, updates and the mean, 40 MiB for
-                              lasgd_sgd_ar_step, 128 MiB for lasgd_step_merge_average.  These sizes are right
+                              lasgd_sgd_ar_step, 128 MiB (bf16 96) for lasgd_step_merge_average.  These sizes are right
                               for a program that has other memory to move between the calls; one that calls
                               nothing else, on a single state that fits the 256 MB memory-side cache, gains
                               1-3 % with 4 up to 64 MB an array (lasgd_sgd_ar_step 5-13 % up to 112 MB)    */
@@ -223,7 +223,7 @@ lasgd_status lasgd_step_merge(lasgd_ctx *ctx, float lr, int32_t resnapshot);
  * (Algorithm 1 steps 7 and 9a-c, then Sec. 3 Eq. 8 on the models just re-sent):
  * exactly lasgd_step_merge(lr, 1) followed by lasgd_average, same roundings, but
  * the K replicas of each tile meet in on-chip memory, so the sent models are not
- * read back for the mean (more than 12 replicas of a model beyond the memory-side
+ * read back for the mean (more than 12 replicas, bf16 24, of a model beyond the memory-side
  * cache take two kernels, which is faster there).  Everything runs on the main
  * stream (after the pending average), nothing on the side stream; afterwards the new mean counts as
  * launched, exactly as after lasgd_average.  Meant for cadences with nothing to

@@ -201,6 +201,8 @@ lasgd_status upload_tables(lasgd_ctx *c, int vec)
 //   sgd_ar_step, K = 4, 32 MB              26 / 27    28 / 29    41 / 32       K = 8, 112 MB  89 / 99   112 / 95   121 / 98
 //                       53 MB              41 / 43    54 / 46    64 / 48       bf16 K = 5, 70 MB 55 / 62   72 / 63    77 / 66
 //   step_merge_average, K = 4, 53 MB      201 / 223  210 / 226  226 / 232     K = 8, 112 MB  456 / 480   468 / 462  479 / 473
+// bf16 with the model in one place, two fused updates, three in turn | other work between: K = 4, 72 MB 150 / 155    178 / 160; 96 MB 203 / 192    210 / 200;
+// 112 MB 244 / 218    249 / 228; K = 16, 72 MB 144 / 155    170 / 159; 96 MB 196 / 192    208 / 196; with two steps between, 96 MB 539 / 541    554 / 548.
 // Local steps between two fused updates go by the fused update's line (with the hint of a cycle's, K = 4, 53 MB, m = 2 208 / 218 us).
 // Gradients just cleared are written to next, so zero_grads keeps them in the cache as long as they may fit.
 enum Use { USE_CYCLE, USE_SGD_AR, USE_FUSED, USE_ZERO };
@@ -208,7 +210,7 @@ int hint_of(const lasgd_ctx *c, Use use)
 {
     if (c->tune.nontemporal >= 0) return c->tune.nontemporal & 3;           // 4, no hint, is 0
     const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
-    const uint64_t from = use == USE_CYCLE ? 28ull << 20 : use == USE_SGD_AR ? 40ull << 20 : 128ull << 20;
+    const uint64_t from = use == USE_CYCLE ? 28ull << 20 : use == USE_SGD_AR ? 40ull << 20 : use == USE_FUSED && !c->both_places ? 96ull << 20 : 128ull << 20;
     return array >= from ? 3 : 0;
 }
 
@@ -262,11 +264,14 @@ constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgrou
 // ResNet-18 K = 8 (9.4e7), adaptive rounds 826 / 818 (847 / 841), K = 4, m = 4 671 / 663; ResNet-50 K = 4 (1.0e8), m = 2 844 / 846 (863 / 862).
 // Beyond, ResNet-18 K = 24, m = 3 3858 / 3882, ResNet-50 K = 8, m = 4 2868 / 2876.  Two or three words gain on the fp32 step in a loop of
 // nothing but steps, from what the last step left in the memory-side cache, and lose 0.3-1.3 % with other work between.
-bool word_first(int op, uint64_t replica_params) { return op == OP_STEP_MERGE && replica_params <= 100000000u; }
-uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block)
+// Where every model is in s (at_s), a wave has no more to load than for a bf16 local step, and goes by its rule.  An update every
+// step, us at 10 granules / 10 and a word / 6 / 7 / 8 / 6 and a word: ResNet-18 list K = 12 585 / 609 / 542 / 537 / 534 / 542, ResNet-50
+// K = 16 1684 / 1776 / 1574 / 1557 / 1563 / 1596, MobileNetV2 K = 16 (8 granules and a word 227) 238 / 248 / 219 / 218 / 221 / 219.
+bool word_first(int op, uint64_t replica_params, bool at_s) { return op == OP_STEP_MERGE && !at_s && replica_params <= 100000000u; }
+uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, uint32_t waves_per_block, bool at_s)
 {
     if (!(nt & 3)) return 0;
-    const uint32_t step_merge = nt & 4 ? 8u : 10u;        // with a word first, and without
+    const uint32_t step_merge = at_s ? 7u : nt & 4 ? 8u : 10u;        // without s to load; with a word first, and without
     uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? step_merge : 0u;
     if (xa && op == OP_STEP_MERGE) {         // replicas that only step or only merge load less: the mean over the waves
         const uint32_t both = (uint32_t)__builtin_popcountll(xa->step_mask & xa->merge_mask);
@@ -278,10 +283,12 @@ uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, ui
     return bytes < kMaxLds ? bytes : (uint32_t)kMaxLds;
 }
 
+bool all_at_s(const ApplyArgs &a) { return a.at_s == (a.K == 64u ? ~0ull : (1ull << a.K) - 1ull); }
+
 template <int VEC, int OP, bool BF16>
 hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, hipStream_t st, int nt)
 {
-    const uint32_t lds = pace_lds(OP, BF16, xa, nt, VEC, bs.x / 64u);
+    const uint32_t lds = pace_lds(OP, BF16, xa, nt, VEC, bs.x / 64u, all_at_s(a));
     if (xa) {      // extended variants: hints all on or all off
         if constexpr (VEC == 1 && OP == OP_STEP_MERGE) {
             if (nt == 7) {
@@ -455,7 +462,7 @@ lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
     p.a.also_x = c->both_places ? 1 : 0;
     const int vec = c->tune.vec;
     int nt = hint_of(c, p.op == OP_STEP && c->fused_cycle ? USE_FUSED : USE_CYCLE);
-    if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad)) nt |= 4;
+    if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad, all_at_s(p.a))) nt |= 4;
     const ExtArgs *xa = p.has_ext ? &p.ext : nullptr;
     hipError_t e = hipSuccess;
     switch (p.op) {
@@ -485,7 +492,11 @@ lasgd_status enqueue_apply(lasgd_ctx *c, int op, float lr, int resnap, const Ext
 
 constexpr uint64_t kWavesOnChip = 256u * 32u;     // 256 CUs hold at most 32 waves each
 // Streaming, lasgd_step_merge_average holds up to this many replicas in one workgroup; beyond, it takes two kernels.
-constexpr uint32_t kOneKernelMaxK = 12;
+// Where the update writes s alone (bf16, place_models) it loses less to the shape: two kernels / one, an update every
+// step, ResNet-18 list K = 14 1261 / 1137, 18 1612 / 1517, 22 1946 / 1880, 24 2131 / 2076, MobileNetV2 K = 13 359 / 335, 22 595 / 586,
+// 24 648 / 639; every second step, ResNet-18 K = 13 2321 / 2201, 20 3586 / 3494; beyond 24, every step, K = 28 2501 / 2465, 32 2844 / 2846,
+// MobileNetV2 K = 32 848 / 881, 40 1056 / 1136.
+uint32_t one_kernel_max(const lasgd_ctx *c) { return c->both_places ? 12u : 24u; }
 
 // The replica-group kernels: one workgroup per tile, W waves, R replicas per wave.
 struct GroupShape {
@@ -498,6 +509,7 @@ struct GroupShape {
 // kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
 GroupShape group_shape(const lasgd_ctx *c, int kind)
 {
+    const bool at_s = c->at_s == c->all;
     GroupShape g{};
     const uint32_t K = (uint32_t)c->K;
     const bool streaming = (hint_of(c, kind == 0 ? USE_SGD_AR : USE_FUSED) & 3) != 0;
@@ -511,9 +523,11 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
     // else two from K = 4 on (2^20 elements bf16 K = 4 16.8 / 15.0, MobileNetV2 bf16 K = 6 82 / 69, fp32 K = 3 32.9 / 32.9).
     // Fused update (its sum is the last thing a workgroup does): one a wave up to K = 9, streaming see below; in the
     // memory-side cache one / two at 2^20 elements K = 8 44.1 / 43.3, K = 16 100 / 92; 300,000 elements K = 16 27.1 / 25.6.
-    const bool paced = streaming && kind == 1 && K <= kOneKernelMaxK && c->tune.group_r <= 0;
+    const bool paced = streaming && kind == 1 && K <= one_kernel_max(c) && c->tune.group_r <= 0;
+    const bool once = !c->both_places;
     const bool at_once = (uint64_t)c->tables->ntiles * K <= kWavesOnChip;
-    if (kind == 1) g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
+    if (paced && once) g.R = K <= 6u ? 1u : 2u;
+    else if (kind == 1) g.R = K <= 9u || (paced && K >= 12u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     else if (streaming) g.R = K <= 12u || (2u * K >= 30u && K <= kGroupWaves) ? 1u : K <= 24u ? 2u : 4u;
     else g.R = K <= (at_once ? kGroupWaves : 3u) ? 1u : K <= 2u * kGroupWaves ? 2u : 4u;
     if (c->tune.group_r > 0) g.R = (uint32_t)c->tune.group_r;
@@ -535,10 +549,22 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
         // replicas a wave, unless two workgroups of one-replica waves fill three quarters of the CU's 32 slots (K = 12).  us, means
         // over eight placements in memory, one replica and everything at once / one, staged / two, staged: ResNet-18 list bf16
         // K = 9 527 / 555 / 528, 10 586 / 607 / 579, 11 643 / 657 / 638, 12 717 / 687 / 699, fp32 K = 12 710 / 688 / 688;
-        // ResNet-50 bf16 K = 12 1540 / 1520 / 1530; MobileNetV2 bf16 K = 12 218 / 214 / 219.  The SGD-AR kernel waits for
-        // its gradients in the middle, and holding its waves back costs it.
+        // ResNet-50 bf16 K = 12 1540 / 1520 / 1530; MobileNetV2 bf16 K = 12 218 / 214 / 219 (bf16 with
+        // the model in both places).  The SGD-AR kernel waits for its gradients in the middle, and holding its waves back costs it.
         g.staged = K > 9u;
-        const size_t pace = g.staged ? 43u * kLdsGranule : (size_t)6u * kLdsGranule * g.W;      // 43 granules: two a CU
+        size_t pace = g.staged ? 43u * kLdsGranule : (size_t)6u * kLdsGranule * g.W;      // 43 granules: two a CU
+        if (once && K > 6u) {
+            // 2.5 KiB of loads a replica where every model is in s, 3.5 where a step came between: two replicas a wave, everything
+            // at once, and whole workgroups that come to about 16 waves a CU, or 13.  From 19 replicas on two groups are too much,
+            // and the gradients wait again.  us, two updates: the rule of fp32 / this, every model in s: ResNet-18 list K = 7 575 / 571,
+            // 8 675 / 648, 9 761 / 725, 10 890 / 802, 12 984 / 981, ResNet-50 K = 7 1265 / 1230, 8 1466 / 1404, 10 1934 / 1759, 12 2212 /
+            // 2172; at two, three, four, five groups a CU K = 7 - / 592 / 571 / 576, K = 9 737 (four) / 725 (three); a step between: ResNet-18
+            // K = 8 1370 / 1340, 10 1741 / 1692, 12 2027 / 2012, MobileNetV2 K = 12 632 / 629.  At once / staged: K = 17 1442 / 1450,
+            // 18 1517 / 1525, 20 1706 / 1705, 22 1886 / 1880, 24 2109 / 2076.
+            g.staged = K > 18u;
+            const uint32_t groups = ((at_s ? 16u : 13u) + g.W / 2u) / g.W;
+            pace = kCuLds / (groups > 2u ? groups : 2u) / kLdsGranule * kLdsGranule;
+        }
         g.lds = pace > g.lds ? (pace < kMaxLds ? pace : kMaxLds) : g.lds;
     }
     return g;
@@ -553,7 +579,7 @@ hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t s
         else if (BF16 && at_s) hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, BF16>), g.grid, g.bs, g.lds, st, a, g.passes); \
         else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, false>), g.grid, g.bs, g.lds, st, a, g.passes);  \
     } while (0)
-    const bool at_s = a.at_s == (a.K == 64u ? ~0ull : (1ull << a.K) - 1ull);
+    const bool at_s = all_at_s(a);
     if (g.R == 1) LASGD_GROUP(1);
     else if (g.R == 2) LASGD_GROUP(2);
     else LASGD_GROUP(4);
@@ -1060,8 +1086,8 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     ApplyArgs a{};
     fill_common(c, a);
     a.neg_lr = -lr;
-    const GroupShape g = group_shape(c, 0);
     if ((st = place_models(c)) != LASGD_OK) return st;
+    const GroupShape g = group_shape(c, 0);
     a.at_s = c->at_s;
     hipError_t e = launch_group(0, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_SGD_AR));
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -1080,11 +1106,12 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
     if (c->alpha != 1.f || c->beta != 1.f)
         return fail(c, LASGD_ERR_STATE, "elastic coefficients are set: use lasgd_step_merge and lasgd_average");
     const bool captured = is_capturing(c->main);
-    if (c->K > (int32_t)kOneKernelMaxK && (hint_of(c, USE_FUSED) & 3) && c->tune.group_r <= 0) {
-        // Streaming from 13 replicas on, workgroups that hold all replicas of a tile lose more to their shape than the
-        // second pass over s costs: update, then the in-order mean.  us, one kernel / two: K = 12 ResNet-18
-        // 667 / 706, bf16 697 / 716, ResNet-50 bf16 1542 / 1563, MobileNetV2 bf16 217 / 216; K = 13 737 / 765, 768 / 776,
-        // 1709 / 1700, 236 / 233; K = 16 MobileNetV2 286 / 282, bf16 293 / 285, ResNet-50 bf16 2102 / 2077.
+    if ((st = place_models(c)) != LASGD_OK) return st;
+    if (c->K > (int32_t)one_kernel_max(c) && (hint_of(c, USE_FUSED) & 3) && c->tune.group_r <= 0) {
+        // Streaming from 13 replicas on (25 where the update writes s alone), workgroups that hold all replicas of a tile lose more
+        // to their shape than the second pass over s costs: update, then the in-order mean.  us, one kernel / two: K = 12 ResNet-18
+        // 667 / 706, bf16 with the model in both places 697 / 716, ResNet-50 bf16 1542 / 1563, MobileNetV2 bf16 217 / 216; K = 13
+        // 737 / 765, 768 / 776, 1709 / 1700, 236 / 233; K = 16 MobileNetV2 286 / 282, bf16 293 / 285, ResNet-50 bf16 2102 / 2077.
         ApplyPlan p;
         if ((st = plan_apply(c, p, OP_STEP_MERGE, lr, 1)) != LASGD_OK) return st;
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
@@ -1097,9 +1124,8 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         fill_common(c, a);
         a.neg_lr = -lr;
         a.resnap = 1;
-        const GroupShape g = group_shape(c, 1);
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
-        if ((st = place_models(c)) != LASGD_OK) return st;
+        const GroupShape g = group_shape(c, 1);
         a.at_s = c->at_s;
         a.also_x = c->both_places ? 1 : 0;
         hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_FUSED));

@@ -6,7 +6,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from paper_2203_13085_amd import workloads as W            # noqa: E402
-from tests.parity_util import compare_state                # noqa: E402
+from tests.parity_util import compare_state, run_parity    # noqa: E402
 from tests.test_gpu_ext import _pair                       # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -75,15 +75,15 @@ def test_sequences_of_calls(K, numels, hint, sequence):
 
 @pytest.mark.parametrize("first", ["replay", "call"])
 @pytest.mark.parametrize("sent", ["all", "some"])
-@pytest.mark.parametrize("fused", [False, True])
-def test_graphs_recorded_while_the_models_are_in_s(fused, sent, first):
+@pytest.mark.parametrize("fused,K,hint", [(False, 5, 4), (True, 5, 4), (True, 13, 3)])
+def test_graphs_recorded_while_the_models_are_in_s(fused, K, hint, sent, first):
     """Two graphs, a cycle and a lone local step, recorded when all or some of the models are in s only, then replayed and
     mixed with ordinary calls in either order: a replay has to find the model wherever the last call left it."""
-    w = W.small(K=5, numels=(700, 3, 256, 420_001), storage="bf16")
+    w = W.small(K=K, numels=(700, 3, 256, 2_100_001 // K), storage="bf16")
     orc, dev, grads = _pair(w)
     full = (1 << w.K) - 1
     try:
-        dev.ctx.set_tuning(avg_split=1)
+        dev.ctx.set_tuning(avg_split=1, nontemporal=hint)
         g = grads(0)
         dev.load_grads(g)
         calls = _calls(orc, dev.ctx, g, w)
@@ -147,3 +147,12 @@ def test_a_model_in_s_is_read_after_recording_before_any_replay():
             compare_state(dev, orc, rep + 1)
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("m", [1, 2])
+@pytest.mark.parametrize("K", [6, 7, 9, 12, 13, 18, 19, 24, 25])
+def test_streaming_fused_update_at_the_rules_edges(K, m):
+    """One replica a wave, two, the gradients at once or later, and two kernels from K = 25 on; with every model in s (m = 1) and
+    with a step between.  z is the in-order mean to the bit."""
+    w = W.small(K=K, numels=(1030, 1, 257, 2_097_152 // K + 77), storage="bf16", m=m, T=2 * m + 1)
+    assert run_parity(w, tuning=dict(nontemporal=3), fused_mean=True) == 0
