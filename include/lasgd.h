@@ -33,7 +33,7 @@
  *   the fp32 master copy of the parameters when storage is bf16 (from 8 MiB of it
  *   on a global update that re-sends leaves the model in s alone until the next
  *   step; once a call has been recorded into a graph, in both), and the lookup
- *   tables.
+ *   tables; with many replicas one more array for lasgd_sgd_ar_step.
  *
  * Paper <-> calls.  Prologue (steps 1-5): lasgd_local_step(eta_0),
  *   lasgd_snapshot, lasgd_average.  Loop iteration without global update
@@ -118,8 +118,8 @@ typedef struct {
                               as NaN in the parameters.  Results are unchanged when the ordering holds.  */
     int32_t group_r;       /* replicas one wave takes at a time in the one-workgroup-per-tile kernels
                               (lasgd_step_merge_average, lasgd_sgd_ar_step): 1, 2 or 4; the workgroup has
-                              ceil(K / group_r) waves, at most 16; a value > 0 also keeps
-                              lasgd_step_merge_average in one kernel.  <0 = default (from K and the size)   */
+                              ceil(K / group_r) waves, at most 16; a value > 0 also keeps both calls
+                              in one kernel.  <0 = default (from K and the size)   */
 } lasgd_tuning;
 
 /*
@@ -288,7 +288,10 @@ lasgd_status lasgd_set_elastic(lasgd_ctx *ctx, float alpha, float beta);
 /*
  * The SGD All-Reduce comparator (Sec. 2; "SGD-AR" in Table 1): average the K
  * gradients (fp64 accumulate, one rounding) and let every replica take the local
- * update with the mean gradient, in one pass.  Main stream; touches x, v only.
+ * update with the mean gradient.  Main stream; touches x, v only.  One pass, or, for
+ * a state beyond the memory-side cache and 16 replicas or more (12 from 56 MiB an
+ * array on, 8 from 112), two, with the mean gradient in an array that lasgd_create
+ * has set aside; where there was no memory for it, one.
  * Errors: as lasgd_local_step.
  */
 lasgd_status lasgd_sgd_ar_step(lasgd_ctx *ctx, float lr);

@@ -53,6 +53,7 @@ struct lasgd_ctx {
     // device memory (one allocation, carved up)
     char *arena = nullptr;
     float *v = nullptr, *s = nullptr, *z = nullptr, *x32 = nullptr;
+    float *gbar = nullptr;           // mean gradient [npad] of an SGD All-Reduce step in two kernels; NULL: always one
     // one set of lookup tables per tile size ever used (vec = 1, 2, 4), kept until destroy: a graph captured
     // under one tile size still points at its tables after the tile size has been changed
     struct Tables {
@@ -250,6 +251,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 //   step + update (4 KiB, and z), with the mean                 1088 1087 1070 1039 1030 1021
 //   global update (2 KiB, and z), with the mean                  672  660  653  657  683  754
 //   snapshot (1 KiB)                                             251  276  279  299  331  396
+//   step with the mean gradient (2 KiB, and it), with its mean     -   656  652  656  682    -       bf16   -  667  661  655  662    -
 // fp32 local steps take 6 and not 8: beside the mean on a second stream 21 waves were the better count.
 // Nothing is gained where the state stays in the memory-side cache (no streaming hint).
 // A caller's kernel on another stream does not wait longer for a CU: a bf16 product of 4096^3 beside local steps took
@@ -272,7 +274,7 @@ uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, ui
 {
     if (!(nt & 3)) return 0;
     const uint32_t step_merge = at_s ? 7u : nt & 4 ? 8u : 10u;        // without s to load; with a word first, and without
-    uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? step_merge : 0u;
+    uint32_t granules = op == OP_STEP ? (bf16 ? 7u : 6u) : op == OP_MERGE ? 6u : op == OP_STEP_MERGE ? step_merge : op == OP_STEP_MEAN ? (bf16 ? 7u : 6u) : 0u;
     if (xa && op == OP_STEP_MERGE) {         // replicas that only step or only merge load less: the mean over the waves
         const uint32_t both = (uint32_t)__builtin_popcountll(xa->step_mask & xa->merge_mask);
         const uint32_t step = (uint32_t)__builtin_popcountll(xa->step_mask & ~xa->merge_mask);
@@ -312,6 +314,14 @@ hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, 
     case 2: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 2>), grid, bs, lds, st, a); break;
     default: hipLaunchKernelGGL((apply_kernel<VEC, OP, BF16, 3>), grid, bs, lds, st, a); break;
     }
+    return hipGetLastError();
+}
+
+// Streaming and in tiles of 256 elements only.
+template <int OP, bool BF16>
+hipError_t launch_one(const ApplyArgs &a, dim3 grid, dim3 bs, hipStream_t st)
+{
+    hipLaunchKernelGGL((apply_kernel<1, OP, BF16, 3>), grid, bs, pace_lds(OP, BF16, nullptr, 3, 1, bs.x / 64u, false), st, a);
     return hipGetLastError();
 }
 
@@ -366,10 +376,10 @@ struct ApplyPlan {
 // xa == nullptr: every replica takes part, one step size, alpha = 1 (the plain kernels).
 lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap, const ExtArgs *xa = nullptr)
 {
-    if (op < OP_STEP || op > OP_INIT) return fail(c, LASGD_ERR_INVALID, "unknown op %d", op);
+    if (op < OP_STEP || op > OP_STEP_MEAN) return fail(c, LASGD_ERR_INVALID, "unknown op %d", op);
     ApplyArgs &a = p.a;
     fill_common(c, a);
-    int kper = (op == OP_MERGE || op == OP_STEP_MERGE) ? c->tune.kper_merge : c->tune.kper_step;
+    int kper = (op == OP_MERGE || op == OP_STEP_MERGE || op == OP_STEP_MEAN) ? c->tune.kper_merge : c->tune.kper_step;
     const int taking = xa ? __builtin_popcountll(xa->step_mask | xa->merge_mask) : c->K;
     if (kper < 1) kper = 1;
     if (kper > taking) kper = taking;
@@ -378,7 +388,7 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     a.kgroups = (uint32_t)((taking + kper - 1) / kper);
     a.neg_lr = -lr;
     a.resnap = resnap;
-    const bool merging = op == OP_MERGE || op == OP_STEP_MERGE;
+    const bool merging = op == OP_MERGE || op == OP_STEP_MERGE || op == OP_STEP_MEAN;       // or reads a shared row as they do
     int64_t chunk = merging ? c->tune.chunk_merge : c->tune.chunk_step;
     if (chunk < 1 || chunk > (int64_t)a.ntiles) chunk = merging ? 0 : a.ntiles;   // 0: one chunk, handled as the tail
     a.chunk = chunk ? (uint32_t)chunk : 1u;
@@ -469,6 +479,10 @@ lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
     case OP_STEP: e = launch_op<OP_STEP>(p.a, xa, p.grid, p.bs, c->main, vec, nt, bf16); break;
     case OP_MERGE: e = launch_op<OP_MERGE>(p.a, xa, p.grid, p.bs, c->main, vec, nt, bf16); break;
     case OP_STEP_MERGE: e = launch_op<OP_STEP_MERGE>(p.a, xa, p.grid, p.bs, c->main, vec, nt, bf16); break;
+    case OP_STEP_MEAN:
+        if (bf16) e = launch_one<OP_STEP_MEAN, true>(p.a, p.grid, p.bs, c->main);
+        else e = launch_one<OP_STEP_MEAN, false>(p.a, p.grid, p.bs, c->main);
+        break;
     case OP_SNAPSHOT: e = launch_op<OP_SNAPSHOT>(p.a, xa, p.grid, p.bs, c->main, vec, nt, bf16); break;
     default: e = launch_vec<OP_INIT, true>(p.a, nullptr, p.grid, p.bs, c->main, vec, nt); break;
     }
@@ -505,6 +519,21 @@ struct GroupShape {
     dim3 grid, bs;
     size_t lds;
 };
+
+// Does the SGD All-Reduce step take two kernels (and is there the array for the mean gradient between them)?  Streaming, the
+// workgroups of the one kernel, which hold all replicas of a tile, cost more with every replica; the two move 8 bytes a
+// parameter more and need a second launch.  us, one kernel / two (three states in turn): ResNet-18 list K = 4 150 / 158, 6 233 / 233,
+// 8 310 / 303, 12 465 / 449, 16 622 / 591, bf16 K = 5 199 / 200, 8 312 / 303, 16 666 / 595; ResNet-50 K = 8 673 / 652, bf16 695 / 655;
+// MobileNetV2 K = 24 308 / 269.  In turn | with other work between: 41 MB an array K = 12 40.5 / 39.8    42.4 / 42.7, bf16 42.5 / 41.6    44.0 / 46.3,
+// K = 32 44.0 / 39.2    46.0 / 42.0; 56 MB K = 12 55.3 / 51.0    54.6 / 53.9, bf16 59.9 / 53.9    58.0 / 57.9; 80 MB K = 8 72.5 / 75.1, K = 12 74.2 / 70.9
+//    75.1 / 73.2; 112 MB K = 8 110 / 102    105.6 / 104.3, bf16 K = 6 103 / 103    105 / 105.  In the memory-side cache the second launch costs more
+// than it gives (10 MB, K = 24 12.4 / 14.6).
+bool wants_mean_grad(const lasgd_ctx *c)
+{
+    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
+    return c->K >= (array >= (112ull << 20) ? 8 : array >= (56ull << 20) ? 12 : 16);
+}
+bool mean_grad_first(const lasgd_ctx *c) { return c->gbar && hint_of(c, USE_SGD_AR) == 3 && c->tune.vec == 1 && c->tune.group_r <= 0; }
 
 // kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
 GroupShape group_shape(const lasgd_ctx *c, int kind)
@@ -739,7 +768,15 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     const uint64_t per = c->npad * sizeof(float);
     c->both_places = !bf16 || c->K * per < kOneCopyFrom;
     const uint64_t n_arrays = (uint64_t)c->K * (bf16 ? 3 : 2) + 1;       // v, s (, x32), z
-    CREATE_HIP(hipMalloc((void **)&c->arena, n_arrays * per));
+    // the mean gradient's array is the last, and the first to be done without
+    if (wants_mean_grad(c)) {
+        if (hipMalloc((void **)&c->arena, (n_arrays + 1) * per) == hipSuccess) c->gbar = (float *)(c->arena + n_arrays * per);
+        else {
+            (void)hipGetLastError();
+            c->arena = nullptr;
+        }
+    }
+    if (!c->arena) CREATE_HIP(hipMalloc((void **)&c->arena, n_arrays * per));
     CREATE_HIP(hipMemsetAsync(c->arena, 0, n_arrays * per, c->main));
     c->v = (float *)c->arena;
     c->s = c->v + (uint64_t)c->K * c->npad;
@@ -1083,6 +1120,19 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     if (!c) return LASGD_ERR_INVALID;
     lasgd_status st = check_ready_to_step(c, lr);
     if (st != LASGD_OK) return st;
+    if (mean_grad_first(c)) {
+        ApplyPlan p;
+        if ((st = plan_apply(c, p, OP_STEP_MEAN, lr, 0)) != LASGD_OK) return st;
+        p.a.z = c->gbar;
+        const dim3 grid(c->tune.max_blocks > 0 && p.a.ntiles > (uint32_t)c->tune.max_blocks ? (uint32_t)c->tune.max_blocks : p.a.ntiles);
+        ApplyArgs a = p.a;
+        a.nwaves = grid.x;
+        if (c->storage == LASGD_BF16) hipLaunchKernelGGL((mean_grad_kernel<true, 3>), grid, dim3(64), 0, c->main, a);
+        else hipLaunchKernelGGL((mean_grad_kernel<false, 3>), grid, dim3(64), 0, c->main, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+        return launch_apply(c, p);
+    }
     ApplyArgs a{};
     fill_common(c, a);
     a.neg_lr = -lr;

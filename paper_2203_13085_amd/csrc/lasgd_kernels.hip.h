@@ -50,7 +50,7 @@ struct Record {        // one per (replica, tensor): everything a wave needs, in
 };
 static_assert(sizeof(Record) == 32, "one 32-byte scalar load");
 
-enum Op : int { OP_STEP = 0, OP_MERGE = 1, OP_STEP_MERGE = 2, OP_SNAPSHOT = 3, OP_INIT = 4 };
+enum Op : int { OP_STEP = 0, OP_MERGE = 1, OP_STEP_MERGE = 2, OP_SNAPSHOT = 3, OP_INIT = 4, OP_STEP_MEAN = 5 };
 
 // n / d for n < 2^31 by a multiplication (Granlund and Montgomery, "Division by invariant integers using
 // multiplication", 1994): with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1 (2^31 for a power of two),
@@ -70,7 +70,8 @@ struct ApplyArgs {
     float *x32;             // bf16 storage only: fp32 master, [K][npad]
     float *v;               // momentum,     [K][npad]
     float *s;               // sent models,  [K][npad]
-    float *z;               // mean,         [npad] (written only by the fused step+update+mean kernel)
+    float *z;               // mean,         [npad] (written only by the fused step+update+mean kernel); OP_STEP_MEAN and
+                            // mean_grad_kernel: the mean gradient
     uint64_t npad;          // elements per replica in the arenas
     uint32_t ntiles, K, n_tensors;
     uint32_t kcount;        // replicas that take part (K, or fewer in the extended calls)
@@ -311,7 +312,8 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
                                            uint32_t count, uint32_t lane, float neg_lr, float alpha)
 {
     constexpr bool NEED_G = (OP == OP_STEP || OP == OP_STEP_MERGE);
-    constexpr bool NEED_V = NEED_G;
+    constexpr bool STEPS = NEED_G || OP == OP_STEP_MEAN;       // with a gradient of its own, or the mean of all
+    constexpr bool NEED_V = STEPS;
     constexpr bool NEED_X = (OP != OP_INIT);
     constexpr bool NEED_S = (OP == OP_MERGE || OP == OP_STEP_MERGE);
     constexpr bool WRITE_X = (OP != OP_SNAPSHOT);
@@ -377,7 +379,8 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     for (int j = 0; j < VEC; ++j) {
         const uint32_t e = j * 256u + lane * 4u, n = lane_elems<FULL>(e, count);
         if constexpr (AT_S) ss[j] = x[j];
-        if constexpr (NEED_G)
+        if constexpr (OP == OP_STEP_MEAN) g[j] = zt[j];
+        if constexpr (STEPS)
             LASGD_FOR4(step_elem(comp(x[j], c), comp(vv[j], c), compv(g[j], c), wd, a.mu,
                                  neg_lr, a.nesterov);)
         if constexpr (NEED_S) {
@@ -443,7 +446,7 @@ template <bool EXT> __device__ __forceinline__ uint32_t replica_at(const ApplyAr
 template <int VEC, int OP, bool BF16, int NT, bool EXT>
 __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa)
 {
-    constexpr bool NEED_Z = (OP == OP_MERGE || OP == OP_STEP_MERGE);
+    constexpr bool NEED_Z = (OP == OP_MERGE || OP == OP_STEP_MERGE || OP == OP_STEP_MEAN);
     const uint32_t lane = threadIdx.x & 63u;
     // the shape travels in the arguments: reading it from the dispatch would be a vector load before everything else
     const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.wpb + (threadIdx.x >> 6));
@@ -779,6 +782,8 @@ __device__ __forceinline__ float4 row_mean(float *lds, uint32_t K, uint32_t W, u
     return *reinterpret_cast<const float4 *>(lds + lane * 4u);
 }
 
+template <int N> struct Count { static constexpr int value = N; };
+
 __device__ __forceinline__ float group_mean_of(double acc, const ApplyArgs &a)
 {
     return (float)(a.use_mul ? acc * a.inv_k : acc / a.k_as_double);
@@ -958,6 +963,61 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
             if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
             else sgd_ar_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
         }
+    }
+}
+
+// The same in two kernels: the mean gradient (here) into an arena of its own, then OP_STEP_MEAN, which reads it as an update
+// reads z.  Bound by HBM like the mean of the sent models: one wave a tile, eight replicas' rows in flight, summed in replica
+// order, so the result is that of the one kernel to the bit.  It moves 8 bytes a parameter more than the one kernel and gains
+// from one-wave workgroups; lasgd_sgd_ar_step holds the line and both sides.
+template <bool BF16, int NT, bool FULL>
+__device__ __forceinline__ void mean_grad_tile(const ApplyArgs &a, const Tile &t, uint32_t tensor, uint32_t lane)
+{
+    constexpr uint32_t N = 8;
+    const uint32_t e = lane * 4u, n = lane_elems<FULL>(e, t.count);
+    const LASGD_CONST_AS Record *rec = as_const(a.records) + tensor;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    auto rows = [&](uint32_t k, auto count) {
+        constexpr int M = decltype(count)::value;
+        float4 g[M];
+        const char *p[M];
+#pragma unroll
+        for (int u = 0; u < M; ++u) {
+            p[u] = reinterpret_cast<const char *>(rec[(size_t)(k + u) * a.n_tensors].g) + t.toff * (BF16 ? 2 : 4);
+            if constexpr (!FULL) g[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        if (FULL || n == 4u) {
+#pragma unroll
+            for (int u = 0; u < M; ++u)
+                g[u] = BF16 ? widen4(ld2<NT>(reinterpret_cast<const uint16_t *>(p[u]) + e)) : ld4<NT>(reinterpret_cast<const float *>(p[u]) + e);
+        }
+        if constexpr (!FULL) {         // the one lane that a tensor's odd end leaves with one to three
+            if (n - 1u < 3u) {
+#pragma unroll
+                for (int u = 0; u < M; ++u)
+                    LASGD_FOR4(if (c < 3 && (uint32_t)c < n) comp(g[u], c) = BF16 ? bf16_widen(as_global<uint16_t>(p[u])[e + c]) : as_global<float>(p[u])[e + c];)
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < M; ++u) LASGD_ACC4(g[u]);
+    };
+    uint32_t k = 0;
+    for (; k + N <= a.K; k += N) rows(k, Count<N>{});
+    if (k + 4u <= a.K) { rows(k, Count<4>{}); k += 4u; }
+    if (k + 2u <= a.K) { rows(k, Count<2>{}); k += 2u; }
+    if (k < a.K) rows(k, Count<1>{});
+    // a whole row: the arena is padded, and the step that reads it takes whole rows too
+    st4<0>(a.z + t.aoff + e, make_float4(group_mean_of(a0, a), group_mean_of(a1, a), group_mean_of(a2, a), group_mean_of(a3, a)));
+}
+
+template <bool BF16, int NT>
+__global__ __launch_bounds__(64) void mean_grad_kernel(const ApplyArgs a)          // tiles of 256 elements
+{
+    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
+        const uint32_t tensor = tensor_of(a, tile);
+        const Tile t = locate(a, load_record(a, 0, tensor), tile, tensor, 256u);
+        if (t.count == 256u) mean_grad_tile<BF16, NT, true>(a, t, tensor, threadIdx.x);
+        else mean_grad_tile<BF16, NT, false>(a, t, tensor, threadIdx.x);
     }
 }
 
