@@ -46,6 +46,7 @@ struct lasgd_ctx {
     uint64_t npad = 0, ntotal = 0;
     hipStream_t main = nullptr, side = nullptr;
     hipEvent_t evA = nullptr, evZ = nullptr;
+    bool back = false;               // the last launch ran from its last item to its first, see backwards
     bool clearing = false;           // a clear of the gradients may be queued on a stream of the caller's
     bool clear_in_graph = false;     // one was recorded: from then on a replay of it may be queued at any time
     int device = 0;
@@ -390,7 +391,12 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     a.resnap = resnap;
     const bool merging = op == OP_MERGE || op == OP_STEP_MERGE || op == OP_STEP_MEAN;       // or reads a shared row as they do
     int64_t chunk = merging ? c->tune.chunk_merge : c->tune.chunk_step;
-    if (chunk < 1 || chunk > (int64_t)a.ntiles) chunk = merging ? 0 : a.ntiles;   // 0: one chunk, handled as the tail
+    // Steps between two fused updates, which go tile by tile, leave the same tiles of all replicas in the L2s if they go by short
+    // chunks.  bf16 only: an fp32 model is the caller's, and where its replicas lie a round number apart the rows of a tile get in
+    // each other's way.  Two fused updates and two steps, us without / with: bf16 K = 4, 2^20 elements 67.7 / 65.7, K = 8, 2^19 68.3 / 65.3, K = 6,
+    // 2^21 189.6 / 187.7; fp32 K = 4, 1,000,003 elements 67.2 / 64.6, but 2^20 73.7 / 75.8 and with four steps 92.0 / 93.9.
+    if (chunk < 1 && op == OP_STEP && c->fused_cycle && c->storage == LASGD_BF16 && !(hint_of(c, USE_FUSED) & 3)) chunk = 64;
+    if (chunk < 1 || chunk > (int64_t)a.ntiles) chunk = 0;                        // one chunk, handled as the tail
     a.chunk = chunk ? (uint32_t)chunk : 1u;
     const uint32_t nfull = chunk ? a.ntiles / a.chunk : 0u;
     a.full_items = nfull * a.chunk * a.kgroups;
@@ -398,8 +404,9 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     const uint32_t tail = a.ntiles - a.tail_first;
     a.tail_chunk = tail ? tail : 1u;
     // passes over the shared z should start on the same XCD for every replica group: 8 XCDs x up to 4 waves
-    // per workgroup.  A local step or snapshot reads no z and keeps its items dense.
-    a.tail_stride = merging ? (uint32_t)round_up(a.tail_chunk, 32) : a.tail_chunk;
+    // per workgroup.  A local step or snapshot reads no z, but its tiles belong on the XCDs that the other kernels have them
+    // on (see backwards).
+    a.tail_stride = (uint32_t)round_up(a.tail_chunk, merging ? 32u : 8u * (uint32_t)c->tune.waves_per_block);
     const uint64_t nitems = (uint64_t)a.full_items + (tail ? (uint64_t)a.tail_stride * a.kgroups : 0u);
     if (nitems == 0 || nitems > 0x7fffffffull) return fail(c, LASGD_ERR_UNSUPPORTED, "work-item count %llu out of range", (unsigned long long)nitems);
     a.nitems = (uint32_t)nitems;
@@ -462,12 +469,29 @@ lasgd_status place_models(lasgd_ctx *c)
     return LASGD_OK;
 }
 
+// The L2s of the eight XCDs hold 32 MiB between them and keep it from launch to launch.  A tile meets the same L2 in every kernel
+// (workgroup i runs on XCD i mod 8, and rows of items are padded to that), so what a launch touched last is there for the next
+// one to start with: every other launch takes its items from the last to the first.  A cycle's us, three states in turn, as before / on one XCD /
+// and backwards in turn: K = 4, 2^20 elements m = 2 43.0 / 43.0 / 40.0, m = 4 70.1 / 70.1 / 60.5; 700,003 elements 30.5 / 30.3 / 28.7; 300,001
+// 20.0 / 19.3 / 19.2; K = 8, 250,007 24.4 / 22.0 / 21.9, 100,003 18.8 / 17.0 / 16.9.  With the hint (K = 8, m = 4): 30 MB an array 125.7 / 125.7 /
+// 123.9, 53 MB 206.1 / 206.3 / 204.7; K = 4, m = 2: 30 MB 74.9 / 74.9 / 74.8, 80 MB 176.6 / 176.7 / 177.9, 112 MB 243 / 243 / 245.5.  So up to 64 MiB.
+constexpr uint64_t kBackFrom = 8ull << 20, kBackBelow = 64ull << 20;
+void backwards(lasgd_ctx *c, ApplyArgs &a, uint32_t waves_per_group)
+{
+    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
+    if (waves_per_group != 1u || a.nitems % 8u != 0u || array < kBackFrom || array >= kBackBelow) return;
+    c->back = !c->back;
+    a.back = c->back ? a.nitems - 8u : 0u;
+    a.back_mask = c->back ? ~7u : 0u;
+}
+
 // Plans before it launches: after the last check of a call, and just before its launch.
 lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
 {
     const bool bf16 = c->storage == LASGD_BF16;
     const lasgd_status st = place_models(c);
     if (st != LASGD_OK) return st;
+    backwards(c, p.a, p.a.wpb);
     p.a.at_s = c->at_s;
     p.a.also_x = c->both_places ? 1 : 0;
     const int vec = c->tune.vec;
@@ -617,11 +641,14 @@ hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t s
 }
 
 // kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
-hipError_t launch_group(int kind, ApplyArgs &a, const GroupShape &g, hipStream_t st, bool bf16, int nt)
+hipError_t launch_group(lasgd_ctx *c, int kind, ApplyArgs &a, const GroupShape &g, int nt)
 {
-    const bool hint = (nt & 3) != 0;
+    const bool hint = (nt & 3) != 0, bf16 = c->storage == LASGD_BF16;
+    const hipStream_t st = c->main;
     a.wpb = g.W;
     a.nwaves = g.grid.x;
+    a.nitems = a.ntiles & ~7u;
+    if (!hint) backwards(c, a, 1u);              // a tile a workgroup
 #define LASGD_KIND(KIND, BF)                                                                              \
     (!hint ? launch_group_r<KIND, BF, 0, false>(a, g, st)                                                 \
            : g.staged ? launch_group_r<KIND, BF, 3, true>(a, g, st) : launch_group_r<KIND, BF, 3, false>(a, g, st))
@@ -744,6 +771,10 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
         off += round_up((uint64_t)cfg->numel[i], kArenaAlign);
         if (off > kMaxNpad) { delete c; return fail(nullptr, LASGD_ERR_UNSUPPORTED, "more than %llu elements per replica", (unsigned long long)kMaxNpad); }
     }
+    // A replica's arrays must not lie a round number apart: the rows of a tile would meet in a few sets of the caches and channels.  us
+    // without / with one row more, 2^20 elements: two fused updates K = 4 54.0 / 46.1, a cycle K = 8, m = 2 79.4 / 76.9, SGD-AR K = 4 18.0 / 16.8;
+    // 2^19 elements, two fused updates K = 4 30.4 / 29.0, a cycle K = 8 39.5 / 38.3 (3, 8 or 33 rows are no better).
+    if (off * sizeof(float) % 65536u == 0u) off += kArenaAlign;
     c->npad = off;
     c->all = c->K == 64 ? ~0ull : ((1ull << c->K) - 1ull);
     c->ntotal = total;
@@ -1139,7 +1170,7 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     if ((st = place_models(c)) != LASGD_OK) return st;
     const GroupShape g = group_shape(c, 0);
     a.at_s = c->at_s;
-    hipError_t e = launch_group(0, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_SGD_AR));
+    hipError_t e = launch_group(c, 0, a, g, hint_of(c, USE_SGD_AR));
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     c->at_s = 0;
     return LASGD_OK;
@@ -1178,7 +1209,7 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         const GroupShape g = group_shape(c, 1);
         a.at_s = c->at_s;
         a.also_x = c->both_places ? 1 : 0;
-        hipError_t e = launch_group(1, a, g, c->main, c->storage == LASGD_BF16, hint_of(c, USE_FUSED));
+        hipError_t e = launch_group(c, 1, a, g, hint_of(c, USE_FUSED));
         if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
         if (!c->both_places) c->at_s = c->all;
     }

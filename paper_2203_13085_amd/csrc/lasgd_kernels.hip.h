@@ -77,7 +77,10 @@ struct ApplyArgs {
     uint32_t kcount;        // replicas that take part (K, or fewer in the extended calls)
     uint32_t kper;          // replicas a wave handles back to back
     uint32_t kgroups;       // ceil(kcount / kper)
-    uint32_t nitems;        // ntiles * kgroups
+    uint32_t nitems;        // ntiles * kgroups (the replica-group kernels: ntiles rounded down to a multiple of eight)
+    // 0, 0: items in order; nitems (a multiple of eight) - 8, ~7: from the last eight to the first.  They stand here because a wave
+    // needs them as early as its neighbours: at the end of the arguments, another cache line, they cost a short call 0.3 us.
+    uint32_t back, back_mask;
     float neg_lr, mu;
     int32_t nesterov, resnap;
     // bf16 storage: bit k says that replica k's model is s[k], which it has just re-sent, and that its master copy is out of
@@ -179,6 +182,12 @@ __device__ __forceinline__ Tile locate(const ApplyArgs &a, const Record &rec, ui
     r.count = left < tile_elems ? left : tile_elems;
     r.wd = rec.wd;
     return r;
+}
+
+// Which item a workgroup takes when the launch runs backwards.  Eight items at a time, so that each stays on its XCD.
+__device__ __forceinline__ uint32_t in_order(uint32_t item, const ApplyArgs &a)
+{
+    return item + a.back - 2u * (item & a.back_mask);
 }
 
 template <int NT> __device__ __forceinline__ float4 ld4(const float *p)
@@ -450,7 +459,8 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
     const uint32_t lane = threadIdx.x & 63u;
     // the shape travels in the arguments: reading it from the dispatch would be a vector load before everything else
     const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.wpb + (threadIdx.x >> 6));
-    for (uint32_t item = wave0; item < a.nitems; item += a.nwaves) {
+    for (uint32_t i0 = wave0; i0 < a.nitems; i0 += a.nwaves) {
+        const uint32_t item = in_order(i0, a);
         // Item order: tiles are taken in chunks of a.chunk; inside a chunk the items run
         // replica group by replica group, so that each replica's arrays are swept in
         // contiguous runs of a.chunk tiles while the chunk's z tiles are reused K times
@@ -459,7 +469,8 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
         // XCDs round-robin, each with its own L2: when a chunk is a multiple of eight
         // workgroups long, tile j of every replica lands on the same XCD, so only the
         // first replica's request for a z tile misses that L2.  The last, shorter chunk is
-        // padded with idle items to such a multiple for the same reason.
+        // padded with idle items to such a multiple for the same reason, and so are the sweeps of a local step: what one
+        // launch leaves in an XCD's L2, the next finds there, and what it left in another's costs more than the memory-side cache.
         uint32_t tile, kg;
         if (item < a.full_items) {
             const uint32_t ch = fast_div(item, a.by_per);
@@ -952,7 +963,8 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = a.wpb;
     bool again = false;
-    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
+    for (uint32_t i0 = blockIdx.x; i0 < a.ntiles; i0 += a.nwaves) {
+        const uint32_t tile = i0 < a.nitems ? in_order(i0, a) : i0;      // the last, less than eight, keep their places
         const uint32_t tensor = tensor_of(a, tile);
         const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
         const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
@@ -1097,7 +1109,8 @@ __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = a.wpb;
     bool again = false;
-    for (uint32_t tile = blockIdx.x; tile < a.ntiles; tile += a.nwaves) {
+    for (uint32_t i0 = blockIdx.x; i0 < a.ntiles; i0 += a.nwaves) {
+        const uint32_t tile = i0 < a.nitems ? in_order(i0, a) : i0;      // the last, less than eight, keep their places
         const uint32_t tensor = tensor_of(a, tile);
         const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
         const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
