@@ -125,6 +125,10 @@ uint64_t round_up(uint64_t a, uint64_t b) { return (a + b - 1) / b * b; }
 
 bool is_pow2(uint32_t k) { return k && !(k & (k - 1)); }
 
+// One array (x, v, s or the gradients) of all replicas.
+uint64_t array_bytes(const lasgd_ctx *c) { return (uint64_t)c->K * c->npad * sizeof(float); }
+constexpr uint64_t kBackFrom = 8ull << 20, kBackBelow = 64ull << 20;      // see backwards
+
 // What fast_div expects for a divisor d in 1 .. 2^31.
 FastDiv make_div(uint32_t d)
 {
@@ -211,7 +215,7 @@ enum Use { USE_CYCLE, USE_SGD_AR, USE_FUSED, USE_ZERO };
 int hint_of(const lasgd_ctx *c, Use use)
 {
     if (c->tune.nontemporal >= 0) return c->tune.nontemporal & 3;           // 4, no hint, is 0
-    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
+    const uint64_t array = array_bytes(c);
     const uint64_t from = use == USE_CYCLE ? 28ull << 20 : use == USE_SGD_AR ? 40ull << 20 : use == USE_FUSED && !c->both_places ? 96ull << 20 : 128ull << 20;
     return array >= from ? 3 : 0;
 }
@@ -404,9 +408,9 @@ lasgd_status plan_apply(lasgd_ctx *c, ApplyPlan &p, int op, float lr, int resnap
     const uint32_t tail = a.ntiles - a.tail_first;
     a.tail_chunk = tail ? tail : 1u;
     // passes over the shared z should start on the same XCD for every replica group: 8 XCDs x up to 4 waves
-    // per workgroup.  A local step or snapshot reads no z, but its tiles belong on the XCDs that the other kernels have them
-    // on (see backwards).
-    a.tail_stride = (uint32_t)round_up(a.tail_chunk, merging ? 32u : 8u * (uint32_t)c->tune.waves_per_block);
+    // per workgroup.  A local step or snapshot reads no z, but where the L2s hold a good part of the state its tiles belong on the
+    // XCDs that the other kernels have them on (see backwards).
+    a.tail_stride = (uint32_t)round_up(a.tail_chunk, merging ? 32u : array_bytes(c) < kBackBelow ? 8u * (uint32_t)c->tune.waves_per_block : 1u);
     const uint64_t nitems = (uint64_t)a.full_items + (tail ? (uint64_t)a.tail_stride * a.kgroups : 0u);
     if (nitems == 0 || nitems > 0x7fffffffull) return fail(c, LASGD_ERR_UNSUPPORTED, "work-item count %llu out of range", (unsigned long long)nitems);
     a.nitems = (uint32_t)nitems;
@@ -474,12 +478,11 @@ lasgd_status place_models(lasgd_ctx *c)
 // one to start with: every other launch takes its items from the last to the first.  A cycle's us, three states in turn, as before / on one XCD /
 // and backwards in turn: K = 4, 2^20 elements m = 2 43.0 / 43.0 / 40.0, m = 4 70.1 / 70.1 / 60.5; 700,003 elements 30.5 / 30.3 / 28.7; 300,001
 // 20.0 / 19.3 / 19.2; K = 8, 250,007 24.4 / 22.0 / 21.9, 100,003 18.8 / 17.0 / 16.9.  With the hint (K = 8, m = 4): 30 MB an array 125.7 / 125.7 /
-// 123.9, 53 MB 206.1 / 206.3 / 204.7; K = 4, m = 2: 30 MB 74.9 / 74.9 / 74.8, 80 MB 176.6 / 176.7 / 177.9, 112 MB 243 / 243 / 245.5.  So up to 64 MiB.
-constexpr uint64_t kBackFrom = 8ull << 20, kBackBelow = 64ull << 20;
+// 123.9, 53 MB 206.1 / 206.3 / 204.7; K = 4, m = 2: 30 MB 74.9 / 74.9 / 74.8, 80 MB 176.6 / 176.7 / 177.9, 112 MB 243 / 243 / 245.5.  So below 64 MiB
+// (kBackBelow); below 8 MiB an array the L2s hold all of it either way.
 void backwards(lasgd_ctx *c, ApplyArgs &a, uint32_t waves_per_group)
 {
-    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
-    if (waves_per_group != 1u || a.nitems % 8u != 0u || array < kBackFrom || array >= kBackBelow) return;
+    if (waves_per_group != 1u || a.nitems % 8u != 0u || array_bytes(c) < kBackFrom || array_bytes(c) >= kBackBelow) return;
     c->back = !c->back;
     a.back = c->back ? a.nitems - 8u : 0u;
     a.back_mask = c->back ? ~7u : 0u;
@@ -554,7 +557,7 @@ struct GroupShape {
 // than it gives (10 MB, K = 24 12.4 / 14.6).
 bool wants_mean_grad(const lasgd_ctx *c)
 {
-    const uint64_t array = (uint64_t)c->K * c->npad * sizeof(float);
+    const uint64_t array = array_bytes(c);
     return c->K >= (array >= (112ull << 20) ? 8 : array >= (56ull << 20) ? 12 : 16);
 }
 bool mean_grad_first(const lasgd_ctx *c) { return c->gbar && hint_of(c, USE_SGD_AR) == 3 && c->tune.vec == 1 && c->tune.group_r <= 0; }
