@@ -184,6 +184,16 @@ __device__ __forceinline__ Tile locate(const ApplyArgs &a, const Record &rec, ui
     return r;
 }
 
+// The arguments that a wave needs before its first load, asked for together: left to the compiler, they come where each is first
+// used, in three rounds of scalar loads that wait for one another.  us, three rounds / one, three states in turn: a cycle of 2^20 elements
+// K = 4 39.2 / 38.6, 250,007 K = 8 22.1 / 21.6, 100,003 K = 16 20.6 / 20.2, 60 tensors m = 4 32.1 / 31.3.
+__device__ __forceinline__ void load_together(const ApplyArgs &a)
+{
+    asm volatile("" ::"s"(a.blocks), "s"(a.tile0), "s"(a.records), "s"(a.v), "s"(a.npad), "s"(a.n_tensors), "s"(a.kcount), "s"(a.kper),
+                 "s"(a.nitems), "s"(a.back), "s"(a.back_mask), "s"(a.nwaves), "s"(a.nesterov), "s"(a.full_items), "s"(a.tail_first),
+                 "s"(a.tail_chunk), "s"(a.tail_stride), "s"(a.by_stride.m), "s"(a.by_stride.shift));
+}
+
 // Which item a workgroup takes when the launch runs backwards.  Eight items at a time, so that each stays on its XCD.
 __device__ __forceinline__ uint32_t in_order(uint32_t item, const ApplyArgs &a)
 {
@@ -459,6 +469,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
     const uint32_t lane = threadIdx.x & 63u;
     // the shape travels in the arguments: reading it from the dispatch would be a vector load before everything else
     const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.wpb + (threadIdx.x >> 6));
+    load_together(a);
     for (uint32_t i0 = wave0; i0 < a.nitems; i0 += a.nwaves) {
         const uint32_t item = in_order(i0, a);
         // Item order: tiles are taken in chunks of a.chunk; inside a chunk the items run
@@ -610,6 +621,7 @@ template <int NT, bool EXT>
 __global__ __launch_bounds__(256) void average_kernel(const AvgArgs a)
 {
     const uint64_t stride = (uint64_t)a.blocks * a.threads;
+    asm volatile("" ::"s"(a.s), "s"(a.z), "s"(a.npad), "s"(a.K), "s"(a.use_mul));       // in one round, see load_together
     for (uint64_t i = (uint64_t)blockIdx.x * a.threads + threadIdx.x; i < a.nvec; i += stride) {
         const float *p = a.s + i * 4u;
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
