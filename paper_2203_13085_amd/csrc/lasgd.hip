@@ -1358,20 +1358,22 @@ template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hi
     uint32_t R;                 // replicas a wave
     if (NT != 0) {
         // Streaming.  The memory system is fastest with about 24 replicas' rows on a CU (24 KiB of s, then 24 KiB of x), as
-        // whole workgroups: the LDS a workgroup asks for leaves room for 24 / K of them, two at least up to K = 24.  us over three
+        // whole workgroups: the LDS a workgroup asks for leaves room for 24 / K of them, two at least up to K = 19.  us over three
         // states in turn, one replica a wave, everything at once and no bound / staged and bounded with one, two, four a wave:
         // K = 2 131 / 125, 125; K = 3 193 / 188, 189; K = 4 267 / 252, 249, 250; K = 6 397 / 386, 382, 385; K = 8 557 / 536, 529, 529.
         // Two or four a wave from K = 12 on is a matter of 0.5 % either way (150 MB an array, K = 12: 107.8 / 110.2; 1100 MB 707.6 / 705.7).
         // One group more or fewer on a CU costs 1-2 or 3-20 %.  Other work between the calls changes none of this
         // (K = 8 555 / 533, 526).  Vectors of 150 to 1100 MB together, before / staged with this rule: K = 9 -2 to -3 %,
         // K = 10 -1 to -3.5, K = 12 +1 to -4, K = 16 0 to -2, K = 20 -1 to -3.6, K = 24 to 32 -0.3 to -0.8.
-        // K = 25 to 32, two groups a CU / one, 450 MB: K = 25 336 / 323, K = 27 356 / 342, K = 29 337 / 330, K = 32 351 / 345.
+        // K = 20 to 32, two groups a CU / one: 2,000,003 elements K = 18 100.8 / 101.3, 19 106.8 / 106.1, 20 113.6 / 112.0, 22 127.5 / 124.2,
+        // 24 139.1 / 135.3; 12,000,000 K = 18 609.7 / 589.0, 20 689.8 / 655.2, 22 773.2 / 747.1, 24 839.0 / 819.5; 450 MB K = 25 336 / 323,
+        // K = 27 356 / 342, K = 29 337 / 330, K = 32 351 / 345; but K = 17 94.6 / 96.9 and, of 12,000,000 elements, 567.9 / 558.6.
         // Four replicas a wave, K > 32, have enough in flight to wait for s alone at no gain, and are bounded to two groups: at once
         // and no bound / staged / at once and bounded, K = 33, n = 3.5e6 329.0 / 327.3 / 322.8, K = 40, 4e6 423.6 / 426.1 / 422.4,
         // K = 48, 3e6 451.7 / 456.4 / 451.4, K = 64, 3e6 560.3 / 563.4 / 560.3.
         R = a.K <= kFlatOneMaxK ? 1u : a.K <= 2u * kGroupWaves ? 2u : 4u;
         size_t pace = kOneGroupLds;
-        if (a.K <= 24u || R == 4u) {
+        if (a.K < 20u || R == 4u) {
             pace = kCuLds / (a.K <= 12u ? 24u / a.K : 2u) / kLdsGranule * kLdsGranule;
             if (pace > kMaxLds) pace = kMaxLds;
         }

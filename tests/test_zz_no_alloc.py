@@ -225,3 +225,9 @@ def test_static_global_update_streaming_under_capture(K):
         check(f"eager call {rep}")
     del x, s, step, hx, hs
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("K", [18, 19, 20, 24])
+def test_static_global_update_streaming_shapes_at_one_group_a_cu(K):
+    """Two workgroups a CU up to K = 19, one from 20 on."""
+    test_static_global_update_streaming_shapes(K)
