@@ -156,3 +156,10 @@ def test_streaming_fused_update_at_the_rules_edges(K, m):
     with a step between.  z is the in-order mean to the bit."""
     w = W.small(K=K, numels=(1030, 1, 257, 2_097_152 // K + 77), storage="bf16", m=m, T=2 * m + 1)
     assert run_parity(w, tuning=dict(nontemporal=3), fused_mean=True) == 0
+
+
+@pytest.mark.parametrize("K,R,hint", [(40, 1, 3), (40, 2, 4), (64, -1, 4), (33, -1, 3), (17, 4, 3)])
+def test_fused_update_in_several_passes(K, R, hint):
+    """A wave's second and third turn, replicas that do not fill the last one, and four replicas a wave, with every model in s."""
+    w = W.small(K=K, numels=(1030, 1, 257, 2_097_152 // K + 77), storage="bf16", m=1, T=3)
+    assert run_parity(w, tuning=dict(nontemporal=hint, group_r=R), fused_mean=True) == 0
