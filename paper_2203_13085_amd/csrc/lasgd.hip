@@ -43,7 +43,8 @@ struct lasgd_ctx {
     std::vector<int64_t> numel;
     std::vector<float> wd;
     std::vector<uint64_t> aoff;      // arena offset of each tensor (elements)
-    uint64_t npad = 0, ntotal = 0;
+    uint64_t packed = 0;             // elements of one replica's tensors, each rounded up to whole rows
+    uint64_t npad = 0, ntotal = 0;   // npad: the same and, for some lengths, a row more (see padded)
     hipStream_t main = nullptr, side = nullptr;
     hipEvent_t evA = nullptr, evZ = nullptr;
     bool back = false;               // the last launch ran from its last item to its first, see backwards
@@ -224,11 +225,17 @@ int hint_of(const lasgd_ctx *c, Use use)
 // One that moves no more than 16 MiB is done in 3 to 6 us, so it stays on the main stream.  A cycle's us on two streams /
 // on one: K = 3, m = 2, 5000 elements 31 / 11, 10^5 31 / 13, 4e5 (6.4 MB) 38 / 19, 10^6 (16 MB) 40 / 32; K = 8, m = 4, 4e5 (14 MB) 56 / 53;
 // K = 32, m = 4, 10^5 (13 MB) 56 / 53.  Beyond: K = 8, m = 4, 10^6 (36 MB) 123 / 124.  With other work between the calls a longer mean is
-// worth hiding behind it.
-bool mean_on_main(uint32_t participants, uint64_t npad)
+// worth hiding behind it.  Exactly 16 MiB, two streams / one, m = 2: K = 3, 2^20 elements 41.9 / 31.5, K = 7, 2^19 44.8 / 34.3, K = 15, 2^18 47.0 / 36.1,
+// K = 63, 2^16 48.3 / 36.9.  So the line goes by the tensors, not by the row more that just such lengths have in the arenas.
+bool mean_on_main(uint32_t participants, uint64_t packed)
 {
-    return (participants + 1ull) * npad * sizeof(float) <= (16ull << 20);
+    return (participants + 1ull) * packed * sizeof(float) <= (16ull << 20);
 }
+
+// A replica's arrays must not lie a round number apart: the rows of a tile would meet in a few sets of the caches and channels.  us
+// without / with one row more, 2^20 elements: two fused updates K = 4 54.0 / 46.1, a cycle K = 8, m = 2 79.4 / 76.9, SGD-AR K = 4 18.0 / 16.8;
+// 2^19 elements, two fused updates K = 4 30.4 / 29.0, a cycle K = 8 39.5 / 38.3 (3, 8 or 33 rows are no better).
+uint64_t padded(uint64_t packed) { return packed * sizeof(float) % 65536u == 0u ? packed + kArenaAlign : packed; }
 
 lasgd_tuning default_tuning(const lasgd_ctx &c)
 {
@@ -237,7 +244,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
     t.kper_step = 1;
     t.kper_merge = 1;
     t.max_blocks = -1;
-    t.avg_split = c.K >= 12 ? 4 : c.K >= 8 && c.side != c.main && !mean_on_main((uint32_t)c.K, c.npad) ? 2 : 1;
+    t.avg_split = c.K >= 12 ? 4 : c.K >= 8 && c.side != c.main && !mean_on_main((uint32_t)c.K, c.packed) ? 2 : 1;
     t.avg_max_blocks = -1;
     t.nontemporal = -1;
     t.waves_per_block = 1;
@@ -775,11 +782,8 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
         off += round_up((uint64_t)cfg->numel[i], kArenaAlign);
         if (off > kMaxNpad) { delete c; return fail(nullptr, LASGD_ERR_UNSUPPORTED, "more than %llu elements per replica", (unsigned long long)kMaxNpad); }
     }
-    // A replica's arrays must not lie a round number apart: the rows of a tile would meet in a few sets of the caches and channels.  us
-    // without / with one row more, 2^20 elements: two fused updates K = 4 54.0 / 46.1, a cycle K = 8, m = 2 79.4 / 76.9, SGD-AR K = 4 18.0 / 16.8;
-    // 2^19 elements, two fused updates K = 4 30.4 / 29.0, a cycle K = 8 39.5 / 38.3 (3, 8 or 33 rows are no better).
-    if (off * sizeof(float) % 65536u == 0u) off += kArenaAlign;
-    c->npad = off;
+    c->packed = off;
+    c->npad = padded(off);
     c->all = c->K == 64 ? ~0ull : ((1ull << c->K) - 1ull);
     c->ntotal = total;
     c->bound.assign((size_t)c->K, 0);
@@ -975,7 +979,7 @@ static lasgd_status do_average(lasgd_ctx *c, uint64_t mask)
     if (c->pending_mask) return fail(c, LASGD_ERR_STATE, "the previous average has not been merged by all its participants");
     if (mask & ~c->snap_mask) return fail(c, LASGD_ERR_STATE, "no snapshot to average for some of these replicas");
     const bool captured = is_capturing(c->main);
-    const bool on_main = c->side == c->main || mean_on_main((uint32_t)__builtin_popcountll(mask), c->npad);
+    const bool on_main = c->side == c->main || mean_on_main((uint32_t)__builtin_popcountll(mask), c->packed);
     const hipStream_t stream = on_main ? c->main : c->side;
     if (!on_main) {
         LASGD_HIP(c, hipEventRecord(c->evA, c->main));
