@@ -85,3 +85,10 @@ def test_streaming_fp32_local_step_asks_for_one_word_first(asm):
     bf16 = _fast_path(_kernel(asm, "_ZN5lasgd12apply_kernelILi1ELi0ELb1ELi3EEEvNS_9ApplyArgsE"))
     assert re.search(paced, f32)
     assert not re.search(r"global_load_dword v", bf16)
+
+
+@pytest.mark.parametrize("nt", [0, 3])
+def test_mean_of_listed_participants_leaves_room_for_eight_waves(asm, nt):
+    """A partial or elastic mean of few replicas: with more than 64 registers, and so fewer waves, it lost 4 %."""
+    body = _kernel(asm, f"_ZN5lasgd14average_kernelILi{nt}ELb1EEEvNS_7AvgArgsE")
+    assert int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", body).group(1)) <= 64
