@@ -33,7 +33,8 @@
  *   the fp32 master copy of the parameters when storage is bf16 (from 8 MiB of it
  *   on a global update that re-sends leaves the model in s alone until the next
  *   step; once a call has been recorded into a graph, in both), and the lookup
- *   tables; with many replicas one more array for lasgd_sgd_ar_step.
+ *   tables; from the first lasgd_sgd_ar_step on that takes two kernels, the mean
+ *   gradient between them (one array of one replica's length).
  *
  * Paper <-> calls.  Prologue (steps 1-5): lasgd_local_step(eta_0),
  *   lasgd_snapshot, lasgd_average.  Loop iteration without global update
@@ -290,8 +291,9 @@ lasgd_status lasgd_set_elastic(lasgd_ctx *ctx, float alpha, float beta);
  * gradients (fp64 accumulate, one rounding) and let every replica take the local
  * update with the mean gradient.  Main stream; touches x, v only.  One pass, or, for
  * a state beyond the memory-side cache and 16 replicas or more (12 from 56 MiB an
- * array on, 8 from 112), two, with the mean gradient in an array that lasgd_create
- * has set aside; where there was no memory for it, one.
+ * array on, 8 from 112), two, with the mean gradient in an array between them.  The
+ * first call of these, unless it is being recorded into a graph, takes one and then
+ * asks for the array; where there is no memory for it, every call takes one.
  * Errors: as lasgd_local_step.
  */
 lasgd_status lasgd_sgd_ar_step(lasgd_ctx *ctx, float lr);

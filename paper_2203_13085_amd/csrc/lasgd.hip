@@ -52,10 +52,11 @@ struct lasgd_ctx {
     bool clear_in_graph = false;     // one was recorded: from then on a replay of it may be queued at any time
     int device = 0;
 
-    // device memory (one allocation, carved up)
+    // device memory: the state's arrays are one allocation, carved up
     char *arena = nullptr;
     float *v = nullptr, *s = nullptr, *z = nullptr, *x32 = nullptr;
-    float *gbar = nullptr;           // mean gradient [npad] of an SGD All-Reduce step in two kernels; NULL: always one
+    float *gbar = nullptr;           // mean gradient [npad] of an SGD All-Reduce step in two kernels, see reserve_mean_grad
+    bool gbar_tried = false;         // asked for; without it the step always takes one kernel
     // one set of lookup tables per tile size ever used (vec = 1, 2, 4), kept until destroy: a graph captured
     // under one tile size still points at its tables after the tile size has been changed
     struct Tables {
@@ -554,7 +555,7 @@ struct GroupShape {
     size_t lds;
 };
 
-// Does the SGD All-Reduce step take two kernels (and is there the array for the mean gradient between them)?  Streaming, the
+// Does the SGD All-Reduce step take two kernels, given the array for the mean gradient between them?  Streaming, the
 // workgroups of the one kernel, which hold all replicas of a tile, cost more with every replica; the two move 8 bytes a
 // parameter more and need a second launch.  us, one kernel / two (three states in turn): ResNet-18 list K = 4 150 / 158, 6 233 / 233,
 // 8 310 / 303, 12 465 / 449, 16 622 / 591, bf16 K = 5 199 / 200, 8 312 / 303, 16 666 / 595; ResNet-50 K = 8 673 / 652, bf16 695 / 655;
@@ -562,12 +563,28 @@ struct GroupShape {
 // K = 32 44.0 / 39.2    46.0 / 42.0; 56 MB K = 12 55.3 / 51.0    54.6 / 53.9, bf16 59.9 / 53.9    58.0 / 57.9; 80 MB K = 8 72.5 / 75.1, K = 12 74.2 / 70.9
 //    75.1 / 73.2; 112 MB K = 8 110 / 102    105.6 / 104.3, bf16 K = 6 103 / 103    105 / 105.  In the memory-side cache the second launch costs more
 // than it gives (10 MB, K = 24 12.4 / 14.6).
-bool wants_mean_grad(const lasgd_ctx *c)
+bool mean_grad_first(const lasgd_ctx *c)
 {
     const uint64_t array = array_bytes(c);
-    return c->K >= (array >= (112ull << 20) ? 8 : array >= (56ull << 20) ? 12 : 16);
+    return c->K >= (array >= (112ull << 20) ? 8 : array >= (56ull << 20) ? 12 : 16) && hint_of(c, USE_SGD_AR) == 3 && c->tune.vec == 1 &&
+           c->tune.group_r <= 0;
 }
-bool mean_grad_first(const lasgd_ctx *c) { return c->gbar && hint_of(c, USE_SGD_AR) == 3 && c->tune.vec == 1 && c->tune.group_r <= 0; }
+
+// The array for the mean gradient, 1/(2K + 1) of what a context holds already, for those alone that make the call it is for.  The
+// first such call takes one kernel, and the array is asked for while that runs, so no call is longer for it (asked for before
+// the launch it made a first call of the ResNet-50 list, K = 8, 778 us in place of 707).  A call that is being recorded has no
+// kernel to wait beside: there it comes first.  Where there is no memory for it, the step stays in one kernel.
+void reserve_mean_grad(lasgd_ctx *c)
+{
+    c->gbar_tried = true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;        // allowed while a stream of this thread is being recorded, and not recorded
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (hipMalloc((void **)&c->gbar, c->npad * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        c->gbar = nullptr;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
 
 // kind 0: SGD All-Reduce step; kind 1: fused step + global update + next mean
 GroupShape group_shape(const lasgd_ctx *c, int kind)
@@ -822,11 +839,6 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     CREATE_HIP(hipMemset(c->records, 0, tab));
     CREATE_HIP(hipEventCreateWithFlags(&c->evA, hipEventDisableTiming));
     CREATE_HIP(hipEventCreateWithFlags(&c->evZ, hipEventDisableTiming));
-    // Apart from the arena: as its last part it moved the other arrays in memory, and the ResNet-50 list's cycle, K = 8, lost 0.5 %.
-    if (wants_mean_grad(c) && hipMalloc((void **)&c->gbar, per) != hipSuccess) {       // the last, and done without if need be
-        (void)hipGetLastError();
-        c->gbar = nullptr;
-    }
     lasgd_status st = upload_tables(c, c->tune.vec);
     if (st != LASGD_OK) {
         g_create_error = c->err;
@@ -1156,7 +1168,9 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     if (!c) return LASGD_ERR_INVALID;
     lasgd_status st = check_ready_to_step(c, lr);
     if (st != LASGD_OK) return st;
-    if (mean_grad_first(c)) {
+    const bool two = mean_grad_first(c);
+    if (two && !c->gbar_tried && is_capturing(c->main)) reserve_mean_grad(c);
+    if (two && c->gbar) {
         ApplyPlan p;
         if ((st = plan_apply(c, p, OP_STEP_MEAN, lr, 0)) != LASGD_OK) return st;
         p.a.z = c->gbar;
@@ -1178,6 +1192,7 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     hipError_t e = launch_group(c, 0, a, g, hint_of(c, USE_SGD_AR));
     if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     c->at_s = 0;
+    if (two && !c->gbar_tried) reserve_mean_grad(c);
     return LASGD_OK;
 }
 

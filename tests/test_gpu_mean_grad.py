@@ -78,3 +78,58 @@ def test_graph_replays_mix_with_calls():
         _same(dev, orc, "at the end")
     finally:
         dev.close()
+
+
+@pytest.mark.parametrize("K,n,growth", [(16, 1 << 22, 1),        # 256 MiB an array: two kernels
+                                        (7, 1 << 23, 0),         # 224 MiB, too few replicas: always one
+                                        (32, 1 << 17, 0)])       # 16 MiB: below the hint's size
+def test_memory_is_for_callers_of_the_call(K, n, growth):
+    """A context holds v, s and z; the array for the mean gradient comes with the first call that takes two kernels, once."""
+    x, g = (torch.zeros(K, n, device="cuda") for _ in range(2))
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        torch.zeros(8, device="cuda").add_(1.0)              # a stream's first launch creates its queue
+    torch.cuda.synchronize()
+
+    def used():
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free
+
+    def made():
+        return B.Context(K, [n], storage=B.F32, momentum=0.9, nesterov=True, wd_scalar=0.0, main_stream=st.cuda_stream, side_stream=st.cuda_stream)
+
+    made().close()                                           # whatever the runtime sets up with a first context
+    u0 = used()
+    c = made()
+    try:
+        row = (n + 256) * 4
+        assert used() - u0 <= (2 * K + 1) * row + (6 << 20)              # pages and tables: a few MiB
+        for k in range(K):
+            c.bind(k, [x[k].data_ptr()], [g[k].data_ptr()])
+        u1 = used()
+        c.sgd_ar_step(0.1)
+        assert growth * n * 4 <= used() - u1 <= growth * (row + (2 << 20))
+        u2 = used()
+        for _ in range(3):
+            c.sgd_ar_step(0.1)
+        assert used() == u2
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_first_call_and_those_after_it(storage):
+    """The first call takes one kernel, the others two: the same bits."""
+    w = W.small(K=19, numels=(1030, 1, 257, 3), storage=storage)
+    orc, dev, grads = _pair(w)
+    try:
+        dev.ctx.set_tuning(nontemporal=3)
+        for i in range(3):
+            g = grads(i)
+            dev.load_grads(g)
+            orc.sgd_ar_step(g, w.lr)
+            dev.ctx.sgd_ar_step(w.lr)
+            _same(dev, orc, f"call {i}")
+    finally:
+        dev.close()
