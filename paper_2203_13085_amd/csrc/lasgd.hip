@@ -77,8 +77,9 @@ struct lasgd_ctx {
                                      // a call has been recorded into a graph
     bool settled = true;             // both_places: all models are back in the master copies, on the main stream
     uint64_t settle_mask = 0;        // those that were in s when a call was first recorded
-    unsigned long long settle_graph = 0;   // the capture that the copy was last recorded into
-    uint32_t *settle_done = nullptr;       // device word, see settle_kernel
+    bool settle_recorded = false;          // into a graph,
+    unsigned long long settle_graph = 0;   // last into this capture
+    uint32_t *settle = nullptr;            // words behind the master copies, see settle_word
 
     // protocol state (bit k = replica k)
     bool master_ready = false;   // bf16: master copy initialised
@@ -298,7 +299,7 @@ uint32_t pace_lds(int op, bool bf16, const ExtArgs *xa, int nt, uint32_t vec, ui
     return bytes < kMaxLds ? bytes : (uint32_t)kMaxLds;
 }
 
-bool all_at_s(const ApplyArgs &a) { return a.at_s == (a.K == 64u ? ~0ull : (1ull << a.K) - 1ull); }
+bool all_at_s(const ApplyArgs &a) { return !(a.place & LOOK) && a.at_s == (a.K == 64u ? ~0ull : (1ull << a.K) - 1ull); }
 
 template <int VEC, int OP, bool BF16>
 hipError_t launch_nt(const ApplyArgs &a, const ExtArgs *xa, dim3 grid, dim3 bs, hipStream_t st, int nt)
@@ -452,33 +453,63 @@ bool is_capturing(hipStream_t st, unsigned long long *id = nullptr)
 // bf16 storage: before a call that reads or writes the models.  A global update that re-sends leaves the model in s alone
 // (apply_tile), and c->at_s says where each call finds it.  A recorded call cannot go by that: it is replayed whenever the
 // caller likes.  So once a call has been recorded, every update writes the master copy too, recorded or not, and models that
-// are in s at that moment are copied back once (settle_kernel), by the first graph that is replayed or the first call that runs.
+// are in s at that moment are brought back once, by the first graph that is replayed or the first call that runs: in a graph by its first
+// kernel as it goes (settle_word), where that writes all of them, else by a kernel in front (settle_kernel).
 //
 // From 8 MiB an array on.  us, both places / s alone, an update every step, every third step, two fused ones, K = 4:
 // 0.3 MB an array 10 / 10, 21 / 21, 16 / 16; 4 MB 13.7 / 13.1, 25.2 / 23.7, 20.3 / 18.5; 16 MB 27.8 / 22.4, 55.9 / 51.9,
-// 52.6 / 45.3; 32 MB 54.0 / 44.6, 109.9 / 106.6, 98.9 / 79.0.  A graph recorded while models are in s keeps the copy's kernel
-// as its first node, which from the second replay on does nothing in 1.7 us: more than is to be gained below.
+// 52.6 / 45.3; 32 MB 54.0 / 44.6, 109.9 / 106.6, 98.9 / 79.0.
 constexpr uint64_t kOneCopyFrom = 8ull << 20;
 constexpr uint32_t kSettleBlocks = 256;
-lasgd_status place_models(lasgd_ctx *c)
+
+// Is a call on the models being recorded (while that matters)?  With the first one the rule above changes.
+bool note_recording(lasgd_ctx *c, unsigned long long *id = nullptr)
 {
-    if (c->storage != LASGD_BF16) return LASGD_OK;
-    unsigned long long id = 0;
-    const bool capturing = !(c->both_places && c->settled) && is_capturing(c->main, &id);
+    if (c->storage != LASGD_BF16 || (c->both_places && c->settled)) return false;
+    unsigned long long any = 0;
+    if (!is_capturing(c->main, id ? id : &any)) return false;
     if (!c->both_places) {
-        if (!capturing) return LASGD_OK;
         c->both_places = true;
         c->settle_mask = c->at_s;
         c->settled = !c->settle_mask;
         c->at_s = 0;
     }
-    if (c->settled || (capturing && c->settle_graph == id)) return LASGD_OK;
-    hipLaunchKernelGGL(settle_kernel, dim3(kSettleBlocks), dim3(256), 0, c->main, c->x32, c->s, c->npad, c->settle_mask, c->settle_done);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
-    if (capturing) c->settle_graph = id;
-    else c->settled = true;
+    return !c->settled;
+}
+
+// a: the call's arguments, told where the models are.  rewritten: the replicas whose master copies it writes from their models; reads:
+// it only reads the models, and leaves bringing them back to the next call.
+lasgd_status place_models(lasgd_ctx *c, ApplyArgs *a = nullptr, uint64_t rewritten = 0, bool reads = false)
+{
+    if (c->storage != LASGD_BF16) return LASGD_OK;
+    unsigned long long id = 0;
+    const bool recording = note_recording(c, &id);
+    if (a) {
+        a->at_s = c->at_s;
+        a->place = c->both_places ? ALSO_X : 0u;
+    }
+    if (!c->both_places || c->settled || (recording && c->settle_recorded && c->settle_graph == id)) return LASGD_OK;
+    const bool as_it_goes = recording && a && (reads || !(c->settle_mask & ~rewritten));
+    if (as_it_goes) {
+        a->at_s = c->settle_mask;
+        a->place |= reads ? LOOK : LOOK | SETTLES;
+        if (reads) return LASGD_OK;
+    } else {
+        hipLaunchKernelGGL(settle_kernel, dim3(kSettleBlocks), dim3(256), 0, c->main, c->x32, c->s, c->npad, c->settle_mask, c->settle);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    }
+    if (recording) {
+        c->settle_recorded = true;
+        c->settle_graph = id;
+    } else c->settled = true;
     return LASGD_OK;
+}
+
+// The launch that would have brought the models back has failed.
+void not_settled(lasgd_ctx *c, const ApplyArgs &a)
+{
+    if (a.place & SETTLES) c->settle_recorded = false;
 }
 
 // The L2s of the eight XCDs hold 32 MiB between them and keep it from launch to launch.  A tile meets the same L2 in every kernel
@@ -500,11 +531,11 @@ void backwards(lasgd_ctx *c, ApplyArgs &a, uint32_t waves_per_group)
 lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
 {
     const bool bf16 = c->storage == LASGD_BF16;
-    const lasgd_status st = place_models(c);
+    const uint64_t taking = p.has_ext ? p.ext.step_mask | p.ext.merge_mask : c->all;
+    const bool writes = p.op != OP_SNAPSHOT && p.op != OP_INIT;
+    const lasgd_status st = place_models(c, &p.a, writes ? taking : 0, p.op == OP_SNAPSHOT);
     if (st != LASGD_OK) return st;
     backwards(c, p.a, p.a.wpb);
-    p.a.at_s = c->at_s;
-    p.a.also_x = c->both_places ? 1 : 0;
     const int vec = c->tune.vec;
     int nt = hint_of(c, p.op == OP_STEP && c->fused_cycle ? USE_FUSED : USE_CYCLE);
     if (nt == 3 && vec == 1 && word_first(p.op, (uint64_t)c->K * c->npad, all_at_s(p.a))) nt |= 4;
@@ -521,7 +552,10 @@ lasgd_status launch_apply(lasgd_ctx *c, ApplyPlan &p)
     case OP_SNAPSHOT: e = launch_op<OP_SNAPSHOT>(p.a, xa, p.grid, p.bs, c->main, vec, nt, bf16); break;
     default: e = launch_vec<OP_INIT, true>(p.a, nullptr, p.grid, p.bs, c->main, vec, nt); break;
     }
-    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        not_settled(c, p.a);
+        return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    }
     if (bf16 && p.op != OP_SNAPSHOT) {
         const bool merging = p.op == OP_MERGE || p.op == OP_STEP_MERGE;
         const uint64_t stepped = p.op == OP_MERGE ? 0 : xa ? xa->step_mask : c->all, merged = !merging ? 0 : xa ? xa->merge_mask : c->all;
@@ -653,17 +687,22 @@ GroupShape group_shape(const lasgd_ctx *c, int kind)
 template <int KIND, bool BF16, int NT, bool ST>
 hipError_t launch_group_r(const ApplyArgs &a, const GroupShape &g, hipStream_t st)
 {
+#define LASGD_GROUP_AT(RR, P)                                                                            \
+    do {                                                                                                 \
+        if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT, ST, P>), g.grid, g.bs, g.lds, st, a, g.passes); \
+        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, P>), g.grid, g.bs, g.lds, st, a, g.passes); \
+    } while (0)
 #define LASGD_GROUP(RR)                                                                                  \
     do {                                                                                                 \
-        if constexpr (KIND == 0) hipLaunchKernelGGL((sgd_ar_kernel<RR, BF16, NT, ST>), g.grid, g.bs, g.lds, st, a, g.passes); \
-        else if (BF16 && at_s) hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, BF16>), g.grid, g.bs, g.lds, st, a, g.passes); \
-        else hipLaunchKernelGGL((step_merge_mean_kernel<RR, BF16, NT, ST, false>), g.grid, g.bs, g.lds, st, a, g.passes);  \
+        if (BF16 && (a.place & SETTLES)) LASGD_GROUP_AT(RR, BF16 ? PLACE_SETTLE : PLACE_AT_S);                      \
+        else if (BF16 && KIND == 1 && all_at_s(a)) LASGD_GROUP_AT(RR, BF16 && KIND == 1 ? PLACE_ALL_IN_S : PLACE_AT_S); \
+        else LASGD_GROUP_AT(RR, PLACE_AT_S);                                                             \
     } while (0)
-    const bool at_s = all_at_s(a);
     if (g.R == 1) LASGD_GROUP(1);
     else if (g.R == 2) LASGD_GROUP(2);
     else LASGD_GROUP(4);
 #undef LASGD_GROUP
+#undef LASGD_GROUP_AT
     return hipGetLastError();
 }
 
@@ -760,7 +799,6 @@ void release(lasgd_ctx *c)
         if (t.mem) (void)hipFree(t.mem);
     if (c->records) (void)hipFree(c->records);
     if (c->gbar) (void)hipFree(c->gbar);
-    if (c->settle_done) (void)hipFree(c->settle_done);
     if (c->evA) (void)hipEventDestroy(c->evA);
     if (c->evZ) (void)hipEventDestroy(c->evZ);
     delete c;
@@ -824,16 +862,14 @@ static lasgd_status create_impl(const lasgd_config *cfg, lasgd_ctx **out)
     const uint64_t per = c->npad * sizeof(float);
     c->both_places = !bf16 || c->K * per < kOneCopyFrom;
     const uint64_t n_arrays = (uint64_t)c->K * (bf16 ? 3 : 2) + 1;       // v, s (, x32), z
-    CREATE_HIP(hipMalloc((void **)&c->arena, n_arrays * per));
-    CREATE_HIP(hipMemsetAsync(c->arena, 0, n_arrays * per, c->main));
+    const uint64_t bytes = n_arrays * per + (bf16 ? kSettleWords * sizeof(uint32_t) : 0u);
+    CREATE_HIP(hipMalloc((void **)&c->arena, bytes));
+    CREATE_HIP(hipMemsetAsync(c->arena, 0, bytes, c->main));
     c->v = (float *)c->arena;
     c->s = c->v + (uint64_t)c->K * c->npad;
     c->z = c->s + (uint64_t)c->K * c->npad;
     c->x32 = bf16 ? c->z + c->npad : nullptr;
-    if (bf16) {
-        CREATE_HIP(hipMalloc((void **)&c->settle_done, sizeof(uint32_t)));
-        CREATE_HIP(hipMemset(c->settle_done, 0, sizeof(uint32_t)));
-    }
+    c->settle = bf16 ? (uint32_t *)(c->x32 + (uint64_t)c->K * c->npad) : nullptr;
     const size_t tab = (size_t)c->K * c->n_tensors * sizeof(Record);
     CREATE_HIP(hipMalloc((void **)&c->records, tab));
     CREATE_HIP(hipMemset(c->records, 0, tab));
@@ -970,7 +1006,7 @@ static lasgd_status do_snapshot(lasgd_ctx *c, uint64_t mask)
     if ((st = check_mask(c, mask, false, "mask")) != LASGD_OK) return st;
     if (mask & c->pending_mask)
         return fail(c, LASGD_ERR_STATE, "an average over some of these replicas is in flight and not merged: s may still be read");
-    if ((st = place_models(c)) != LASGD_OK) return st;
+    note_recording(c);
     const uint64_t copied = mask & ~c->at_s;           // a model that is in s only has been sent already
     if (copied == c->all) st = enqueue_apply(c, OP_SNAPSHOT, 0.f, 0);
     else if (copied) {
@@ -1186,11 +1222,13 @@ lasgd_status lasgd_sgd_ar_step(lasgd_ctx *c, float lr)
     ApplyArgs a{};
     fill_common(c, a);
     a.neg_lr = -lr;
-    if ((st = place_models(c)) != LASGD_OK) return st;
+    if ((st = place_models(c, &a, c->all)) != LASGD_OK) return st;
     const GroupShape g = group_shape(c, 0);
-    a.at_s = c->at_s;
     hipError_t e = launch_group(c, 0, a, g, hint_of(c, USE_SGD_AR));
-    if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        not_settled(c, a);
+        return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+    }
     c->at_s = 0;
     if (two && !c->gbar_tried) reserve_mean_grad(c);
     return LASGD_OK;
@@ -1207,7 +1245,7 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
     if (c->alpha != 1.f || c->beta != 1.f)
         return fail(c, LASGD_ERR_STATE, "elastic coefficients are set: use lasgd_step_merge and lasgd_average");
     const bool captured = is_capturing(c->main);
-    if ((st = place_models(c)) != LASGD_OK) return st;
+    note_recording(c);
     if (c->K > (int32_t)one_kernel_max(c) && (hint_of(c, USE_FUSED) & 3) && c->tune.group_r <= 0) {
         // Streaming from 13 replicas on (25 where the update writes s alone), workgroups that hold all replicas of a tile lose more
         // to their shape than the second pass over s costs: update, then the in-order mean.  us, one kernel / two: K = 12 ResNet-18
@@ -1226,11 +1264,13 @@ lasgd_status lasgd_step_merge_average(lasgd_ctx *c, float lr)
         a.neg_lr = -lr;
         a.resnap = 1;
         if (!c->z_on_main) LASGD_HIP(c, hipStreamWaitEvent(c->main, c->evZ, 0));
+        if ((st = place_models(c, &a, c->all)) != LASGD_OK) return st;
         const GroupShape g = group_shape(c, 1);
-        a.at_s = c->at_s;
-        a.also_x = c->both_places ? 1 : 0;
         hipError_t e = launch_group(c, 1, a, g, hint_of(c, USE_FUSED));
-        if (e != hipSuccess) return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+        if (e != hipSuccess) {
+            not_settled(c, a);
+            return fail(c, LASGD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+        }
         if (!c->both_places) c->at_s = c->all;
     }
     // every replica has merged and re-sent, and the mean of the sent models is (being) written to z

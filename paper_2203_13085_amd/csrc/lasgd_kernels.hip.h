@@ -52,6 +52,8 @@ static_assert(sizeof(Record) == 32, "one 32-byte scalar load");
 
 enum Op : int { OP_STEP = 0, OP_MERGE = 1, OP_STEP_MERGE = 2, OP_SNAPSHOT = 3, OP_INIT = 4, OP_STEP_MEAN = 5 };
 
+enum : uint32_t { ALSO_X = 1, LOOK = 2, SETTLES = 4 };     // LOOK, and SETTLES with it: early in a recorded graph, see settle_word
+
 // n / d for n < 2^31 by a multiplication (Granlund and Montgomery, "Division by invariant integers using
 // multiplication", 1994): with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1 (2^31 for a power of two),
 // floor(n * m / 2^(31+l)) is exact, and m fits 32 bits.
@@ -67,7 +69,7 @@ struct ApplyArgs {
     const uint32_t *blocks; // [ceil(ntiles / 64)] tensor of each block's first tile, kMoreInBlock if others follow in it
     const uint32_t *tile0;  // [n_tensors + 16] the tensors' first tiles, then 0xffffffff, which no tile reaches
     const Record *records;  // [K * n_tensors]
-    float *x32;             // bf16 storage only: fp32 master, [K][npad]
+    float *x32;             // bf16 storage only: fp32 master, [K][npad], and behind it the words of settle_word
     float *v;               // momentum,     [K][npad]
     float *s;               // sent models,  [K][npad]
     float *z;               // mean,         [npad] (written only by the fused step+update+mean kernel); OP_STEP_MEAN and
@@ -83,10 +85,10 @@ struct ApplyArgs {
     uint32_t back, back_mask;
     float neg_lr, mu;
     int32_t nesterov, resnap;
-    // bf16 storage: bit k says that replica k's model is s[k], which it has just re-sent, and that its master copy is out of
-    // date.  A global update that re-sends leaves it that way unless also_x, and the next step writes the master again.
-    uint64_t at_s;
-    int32_t also_x;
+    // bf16 storage: bit k of at_s says that replica k's model is s[k], which it has just re-sent, and that its master copy is out of
+    // date.  A global update that re-sends leaves it that way unless ALSO_X, and the next step writes the master again.
+    uint32_t place;         // ALSO_X, LOOK, SETTLES
+    uint64_t at_s;          // LOOK: until the words behind the master copies say otherwise
     uint32_t tile_elems;    // 256 * VEC
     uint32_t wpb, nwaves;   // waves per workgroup, and in the grid (the replica-group kernels: workgroups in the grid)
     uint32_t chunk;         // item order, see apply_kernel
@@ -192,6 +194,35 @@ __device__ __forceinline__ void load_together(const ApplyArgs &a)
     asm volatile("" ::"s"(a.blocks), "s"(a.tile0), "s"(a.records), "s"(a.v), "s"(a.npad), "s"(a.n_tensors), "s"(a.kcount), "s"(a.kper),
                  "s"(a.nitems), "s"(a.back), "s"(a.back_mask), "s"(a.nwaves), "s"(a.nesterov), "s"(a.full_items), "s"(a.tail_first),
                  "s"(a.tail_chunk), "s"(a.tail_stride), "s"(a.by_stride.m), "s"(a.by_stride.shift));
+}
+
+// bf16 storage, and a graph recorded while models were in s only.  It is replayed at any time, so nothing in it may depend on where the
+// last call left a model: its first kernel finds the models of at_s in s on the first replay and in the master copies, which it
+// writes, on all later ones, unless a call has run in between (settle_kernel).  A word in memory says which: kSettled, once every wave of
+// the one that comes first has counted itself there.  No wave can find it so before its own share is done, and the next kernel
+// begins when all are.  Waves count in parts that share no cache line, since
+// a million of them on one word would take longer than the kernel; later replays only read the word, beside the replica's record, so that
+// it costs no wait of its own.  us a replay with a kernel in front that does nothing from the second replay on / this / recorded with the models
+// in the master copies, three states in turn: fused update K = 8, 8 MiB an array 21.5 / 17.1 / 17.0, 92 MiB 145.3 / 140.9 / 141.0; K = 4, 16 MiB
+// 29.9 / 25.5 / 25.3; a cycle, m = 1, K = 8, 8 MiB 20.9 / 19.3 / 19.3, 92 MiB 129.2 / 127.9 / 127.7.  The words lie where x32 tells: one pointer more among
+// the arguments cost every call on bf16 models 0.1 us.
+constexpr uint32_t kSettled = 0x80000000u, kSettleParts = 256u, kSettleStride = 16u;       // stride: words
+constexpr uint32_t kSettleWords = kSettleStride * (1u + kSettleParts);
+
+__device__ __forceinline__ uint32_t *settle_words(const ApplyArgs &a) { return reinterpret_cast<uint32_t *>(a.x32 + (uint64_t)a.K * a.npad); }
+__device__ __forceinline__ uint32_t settle_word(const ApplyArgs &a)
+{
+    const uint32_t *p = settle_words(a);
+    asm volatile("" : "+s"(p));               // here, where other loads are under way, and not in front of the loop
+    return *as_const(p);
+}
+__device__ __forceinline__ void count_settled(uint32_t *settle, uint32_t wave, uint32_t waves, uint32_t lane)
+{
+    if (lane != 0u) return;
+    const uint32_t parts = waves < kSettleParts ? waves : kSettleParts, part = wave % kSettleParts;
+    const uint32_t others = (waves - 1u - part) / kSettleParts;                            // in this part
+    if (atomicAdd(settle + kSettleStride * (1u + part), 1u) != others) return;
+    atomicAdd(settle, part == 0u ? kSettled - (parts - 1u) : 1u);                          // the parts' sum is kSettled
 }
 
 // Which item a workgroup takes when the launch runs backwards.  Eight items at a time, so that each stays on its XCD.
@@ -344,7 +375,7 @@ __device__ __forceinline__ void apply_tile(const ApplyArgs &a, void *xu, const v
     const uint16_t *g16 = static_cast<const uint16_t *>(gu);
     constexpr bool LOAD_S = NEED_S && !AT_S;
     const bool write_s = (OP == OP_SNAPSHOT) || (NEED_S && a.resnap);
-    const bool write_x = !BF16 || !NEED_S || !a.resnap || a.also_x;
+    const bool write_x = !BF16 || !NEED_S || !a.resnap || (a.place & ALSO_X);
 
     if constexpr (OP == OP_SNAPSHOT && !FULL) {          // a copy
 #pragma unroll
@@ -470,6 +501,8 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
     // the shape travels in the arguments: reading it from the dispatch would be a vector load before everything else
     const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.wpb + (threadIdx.x >> 6));
     load_together(a);
+    uint32_t word = 0;
+    bool looked = false;
     for (uint32_t i0 = wave0; i0 < a.nitems; i0 += a.nwaves) {
         const uint32_t item = in_order(i0, a);
         // Item order: tiles are taken in chunks of a.chunk; inside a chunk the items run
@@ -498,7 +531,14 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
         const uint32_t k0 = kg * a.kper;
         const uint32_t k1 = (k0 + a.kper < a.kcount) ? k0 + a.kper : a.kcount;
         const uint32_t tensor = tensor_of(a, tile);
+        if constexpr (BF16 && OP != OP_INIT) {
+            if (__builtin_expect((a.place & LOOK) != 0u, 0)) {
+                word = settle_word(a);
+                looked = true;
+            }
+        }
         Record rec = load_record(a, replica_at<EXT>(a, xa, k0), tensor);
+        const uint64_t in_s = !BF16 || word >= kSettled ? 0ull : a.at_s;
         const Tile t = locate(a, rec, tile, tensor, 256u * VEC);
         const bool full = (t.count == 256u * VEC);
         float4 zt[VEC];
@@ -521,7 +561,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
                 gu = reinterpret_cast<const char *>(rec.g) + t.toff * esz;
             const size_t ao = (size_t)k * a.npad + t.aoff;
             float *xm = BF16 ? a.x32 + ao : nullptr;
-            const bool at_s = BF16 && ((a.at_s >> k) & 1ull);
+            const bool at_s = BF16 && ((in_s >> k) & 1ull);
             const float *xr = at_s ? a.s + ao : xm;
 #define LASGD_TILE_AT(OPX, NLR, AL, AT)                                                                      \
     do {                                                                                                     \
@@ -555,6 +595,12 @@ __device__ __forceinline__ void apply_body(const ApplyArgs &a, const ExtArgs *xa
 #undef LASGD_TILE_AT
             if (++j == k1) break;
             rec = load_record(a, replica_at<EXT>(a, xa, j), tensor);
+        }
+    }
+    if constexpr (BF16 && (NEED_Z || OP == OP_STEP)) {         // they write the master copy from the model, wherever that is
+        if (__builtin_expect((a.place & SETTLES) != 0u, 0)) {
+            if (!looked) word = settle_word(a);
+            if (word < kSettled) count_settled(settle_words(a), wave0, a.nwaves, lane);
         }
     }
 }
@@ -823,15 +869,19 @@ template <bool BF16> struct ReplicaTile {
     uint16_t *x16;
     const void *g;
 };
+// Where a replica-group kernel finds the models: each as at_s says; all in s; at_s holds until settled, and it counts (the last two: bf16 only).
+// By kind and not by a test at the start, which was a round of scalar loads more in front of all others: 2-3 % of a fused update
+// (us, K = 8, bf16: 2,000,003 elements 98.8 with, 97.0 without; 3,000,003 144.6 / 141.1).
+enum Place : int { PLACE_AT_S = 0, PLACE_ALL_IN_S = 1, PLACE_SETTLE = 2 };
 template <bool BF16>
-__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, const Record &rec, uint32_t k)
+__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, const Record &rec, uint32_t k, uint64_t in_s)
 {
     constexpr size_t ESZ = BF16 ? 2 : 4;
     const size_t ao = (size_t)k * a.npad + t.aoff;
     char *xu = reinterpret_cast<char *>(rec.x) + t.toff * ESZ;
     ReplicaTile<BF16> r;
     r.xw = BF16 ? a.x32 + ao : reinterpret_cast<float *>(xu);
-    r.xf = BF16 && ((a.at_s >> k) & 1ull) ? a.s + ao : r.xw;
+    r.xf = BF16 && ((in_s >> k) & 1ull) ? a.s + ao : r.xw;
     r.x16 = reinterpret_cast<uint16_t *>(xu);
     r.v = a.v + ao;
     r.s = a.s + ao;
@@ -839,9 +889,9 @@ __device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, co
     return r;
 }
 template <bool BF16>
-__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, uint32_t k, uint32_t tensor)
+__device__ __forceinline__ ReplicaTile<BF16> replica_tile(const ApplyArgs &a, const Tile &t, uint32_t k, uint32_t tensor, uint64_t in_s)
 {
-    return replica_tile<BF16>(a, t, load_record(a, k, tensor), k);
+    return replica_tile<BF16>(a, t, load_record(a, k, tensor), k, in_s);
 }
 // The loads of R replicas' gradients (G) and models (X) from the caller's buffers.  The last row of a tensor takes the
 // same 128-bit accesses in the lanes that have four elements; only the one lane with one to three goes element by
@@ -893,7 +943,7 @@ __device__ __forceinline__ void ld_caller(const ReplicaTile<BF16> (&q)[R], uint3
 // STAGED: the models are asked for when the gradients have arrived, and fly while these go round through LDS.
 template <int R, bool BF16, int NT, bool FULL, bool STAGED>
 __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
-                                           uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
+                                           uint32_t w, uint32_t W, uint32_t passes, uint32_t lane, uint64_t in_s)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= t.count) ? 0u : (t.count - e0 < 4u) ? t.count - e0 : 4u;
@@ -907,7 +957,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
         for (int r = 0; r < R; ++r) {
             const uint32_t kw = w + (uint32_t)r * W;
             mine[r] = kw < a.K;
-            rt[r] = r == 0 ? replica_tile<BF16>(a, t, rec0, kw) : replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u, tensor);
+            rt[r] = r == 0 ? replica_tile<BF16>(a, t, rec0, kw, in_s) : replica_tile<BF16>(a, t, mine[r] ? kw : a.K - 1u, tensor, in_s);
         }
         ld_caller<R, BF16, NT, FULL, true, !STAGED>(rt, e0, n, g, x);
         if constexpr (STAGED) {
@@ -927,7 +977,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
-            q[r] = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
+            q[r] = replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor, in_s);
         }
         ld_caller<R, BF16, NT, FULL, true, false>(q, e0, n, g, g);
 #pragma unroll
@@ -953,7 +1003,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
         for (int r = 0; r < R; ++r) {
             const uint32_t kw = w + (p * R + (uint32_t)r) * W;
             ok[r] = kw < a.K;
-            q[r] = replica_tile<BF16>(a, t, ok[r] ? kw : a.K - 1u, tensor);
+            q[r] = replica_tile<BF16>(a, t, ok[r] ? kw : a.K - 1u, tensor, in_s);
         }
         ld_caller<R, BF16, NT, FULL, false, true>(q, e0, n, xx, xx);
 #pragma unroll
@@ -970,7 +1020,7 @@ __device__ __forceinline__ void sgd_ar_row(const ApplyArgs &a, const Tile &t, co
     }
 }
 
-template <int R, bool BF16, int NT, bool STAGED>
+template <int R, bool BF16, int NT, bool STAGED, int PLACE>
 __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const uint32_t passes)
 {
     extern __shared__ float lds[];                        // [K][256]
@@ -978,18 +1028,24 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = a.wpb;
     bool again = false;
+    uint32_t word = 0;
     for (uint32_t i0 = blockIdx.x; i0 < a.ntiles; i0 += a.nwaves) {
         const uint32_t tile = i0 < a.nitems ? in_order(i0, a) : i0;      // the last, less than eight, keep their places
+        if constexpr (PLACE == PLACE_SETTLE) word = settle_word(a);
         const uint32_t tensor = tensor_of(a, tile);
         const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
+        const uint64_t in_s = !BF16 || word >= kSettled ? 0ull : a.at_s;
         const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
         const uint32_t rows = (t.count + 255u) >> 8;
         for (uint32_t row = 0; row < rows; ++row) {
             if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
             again = true;
-            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
-            else sgd_ar_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            if (t.count - row * 256u >= 256u) sgd_ar_row<R, BF16, NT, true, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane, in_s);
+            else sgd_ar_row<R, BF16, NT, false, STAGED>(a, t, rec0, tensor, lds, row, w, W, passes, lane, in_s);
         }
+    }
+    if constexpr (PLACE == PLACE_SETTLE) {
+        if (word < kSettled) count_settled(settle_words(a), blockIdx.x * W + w, a.nwaves * W, lane);       // every workgroup has a tile
     }
 }
 
@@ -1059,7 +1115,7 @@ __global__ __launch_bounds__(64) void mean_grad_kernel(const ApplyArgs a)       
 // AT_S: every replica's model is the one it sent last (see apply_tile), read once for both.
 template <int R, bool BF16, int NT, bool FULL, bool STAGED, bool AT_S>
 __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Tile &t, const Record &rec0, uint32_t tensor, float *lds, uint32_t row,
-                                                    uint32_t w, uint32_t W, uint32_t passes, uint32_t lane)
+                                                    uint32_t w, uint32_t W, uint32_t passes, uint32_t lane, uint64_t in_s)
 {
     const uint32_t e0 = row * 256u + lane * 4u;
     const uint32_t n = FULL ? 4u : (e0 >= t.count) ? 0u : (t.count - e0 < 4u) ? t.count - e0 : 4u;
@@ -1072,7 +1128,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             kw[r] = w + (p * R + (uint32_t)r) * W;
-            q[r] = r == 0 && p == 0u ? replica_tile<BF16>(a, t, rec0, kw[r]) : replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor);
+            q[r] = r == 0 && p == 0u ? replica_tile<BF16>(a, t, rec0, kw[r], in_s) : replica_tile<BF16>(a, t, kw[r] < a.K ? kw[r] : a.K - 1u, tensor, in_s);
         }
         ld_caller<R, BF16, NT, FULL, !STAGED, true>(q, e0, n, g, x);
 #pragma unroll
@@ -1094,7 +1150,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
             LASGD_FOR4(comp(x[r], c) = merge_elem(compv(x[r], c), compv(ss[r], c), compv(z, c));)
             if (kw[r] < a.K) {
                 row_st<NT, FULL>(q[r].v, e0, n, v[r]);
-                if (!BF16 || a.also_x) row_st<NT, FULL>(q[r].xw, e0, n, x[r]);
+                if (!BF16 || (a.place & ALSO_X)) row_st<NT, FULL>(q[r].xw, e0, n, x[r]);
                 if constexpr (BF16) row_st16<NT, FULL>(q[r].x16, e0, n, x[r]);
                 row_st<NT, FULL>(q[r].s, e0, n, x[r]);
                 *reinterpret_cast<float4 *>(lds + (size_t)kw[r] * 256u + lane * 4u) = x[r];
@@ -1116,7 +1172,7 @@ __device__ __forceinline__ void step_merge_mean_row(const ApplyArgs &a, const Ti
     }
 }
 
-template <int R, bool BF16, int NT, bool STAGED, bool AT_S>
+template <int R, bool BF16, int NT, bool STAGED, int PLACE>
 __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a, const uint32_t passes)
 {
     extern __shared__ float lds[];                        // [K][256]
@@ -1124,18 +1180,24 @@ __global__ __launch_bounds__(1024) void step_merge_mean_kernel(const ApplyArgs a
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = a.wpb;
     bool again = false;
+    uint32_t word = 0;
     for (uint32_t i0 = blockIdx.x; i0 < a.ntiles; i0 += a.nwaves) {
         const uint32_t tile = i0 < a.nitems ? in_order(i0, a) : i0;      // the last, less than eight, keep their places
+        if constexpr (PLACE == PLACE_SETTLE) word = settle_word(a);
         const uint32_t tensor = tensor_of(a, tile);
         const Record rec0 = load_record(a, w, tensor);       // of this wave's first replica: W <= K
+        const uint64_t in_s = !BF16 || word >= kSettled ? 0ull : a.at_s;
         const Tile t = locate(a, rec0, tile, tensor, a.tile_elems);
         const uint32_t rows = (t.count + 255u) >> 8;
         for (uint32_t row = 0; row < rows; ++row) {
             if (again) __syncthreads();     // a further row reuses the LDS buffer; after the last one waves leave as they finish
             again = true;
-            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true, STAGED, AT_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
-            else step_merge_mean_row<R, BF16, NT, false, STAGED, AT_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane);
+            if (t.count - row * 256u >= 256u) step_merge_mean_row<R, BF16, NT, true, STAGED, PLACE == PLACE_ALL_IN_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane, in_s);
+            else step_merge_mean_row<R, BF16, NT, false, STAGED, PLACE == PLACE_ALL_IN_S>(a, t, rec0, tensor, lds, row, w, W, passes, lane, in_s);
         }
+    }
+    if constexpr (PLACE == PLACE_SETTLE) {
+        if (word < kSettled) count_settled(settle_words(a), blockIdx.x * W + w, a.nwaves * W, lane);       // every workgroup has a tile
     }
 }
 
@@ -1170,20 +1232,18 @@ __global__ __launch_bounds__(64) void zero_grads_kernel(const ApplyArgs a)
     }
 }
 
-// bf16 storage, once, before the first work that a recorded graph may hold: the models of `mask` from s back to the master copies.
-// Graphs are replayed at any time, so with one about nothing may depend on where the last call left a model.  Whichever comes
-// first on the main stream, a replay or another call, does the copy; `done` counts the workgroups that have (gridDim.x of them
-// in every launch), and no workgroup can find it full before its own share is done.
-__global__ __launch_bounds__(256) void settle_kernel(float *x32, const float *s, uint64_t npad, uint64_t mask, uint32_t *done)
+// The same as a kernel of its own: the models of `mask` from s back to the master copies, once.  For a call that runs before the
+// first replay, and in a graph whose first kernel does not write all of them.
+__global__ __launch_bounds__(256) void settle_kernel(float *x32, const float *s, uint64_t npad, uint64_t mask, uint32_t *settle)
 {
-    if (*as_global<uint32_t>(done) >= gridDim.x) return;
+    if (*as_global<uint32_t>(settle) >= kSettled) return;
     const uint64_t stride = (uint64_t)gridDim.x * 256u;
     for (; mask; mask &= mask - 1ull) {
         const uint64_t k = (uint64_t)__builtin_ctzll(mask);
         for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < npad / 4u; i += stride) st4<3>(x32 + k * npad + i * 4u, ld4<3>(s + k * npad + i * 4u));
     }
     __syncthreads();
-    if (threadIdx.x == 0u) atomicAdd(done, 1u);
+    count_settled(settle, blockIdx.x, gridDim.x, threadIdx.x);
 }
 
 // Debugging aid for the two-stream protocol: fill z with NaN.

@@ -1,6 +1,8 @@
 """bf16 storage, from 8 MiB an array on: after a global update that re-sends, the fp32 model is kept once, in s, and the next
 call that needs it reads it there.  Whatever calls follow one another, and whatever graphs are recorded and replayed between them, the state has to be
 the oracle's, to the bit."""
+import ctypes
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -163,3 +165,110 @@ def test_fused_update_in_several_passes(K, R, hint):
     """A wave's second and third turn, replicas that do not fill the last one, and four replicas a wave, with every model in s."""
     w = W.small(K=K, numels=(1030, 1, 257, 2_097_152 // K + 77), storage="bf16", m=1, T=3)
     assert run_parity(w, tuning=dict(nontemporal=hint, group_r=R), fused_mean=True) == 0
+
+
+class _Graph:
+    """A recorded graph by the runtime's own calls, which tell how many nodes it has."""
+
+    hip = ctypes.CDLL("libamdhip64.so")
+
+    def __init__(self, stream, record):
+        self.stream, self.graph, self.run, n = stream, ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_size_t()
+        torch.cuda.synchronize()
+        self._do("hipStreamBeginCapture", ctypes.c_void_p(stream.cuda_stream), 2)          # relaxed
+        try:
+            record()
+        finally:
+            self._do("hipStreamEndCapture", ctypes.c_void_p(stream.cuda_stream), ctypes.byref(self.graph))
+        self._do("hipGraphGetNodes", self.graph, None, ctypes.byref(n))
+        self.nodes = n.value
+        self._do("hipGraphInstantiate", ctypes.byref(self.run), self.graph, None, None, ctypes.c_size_t(0))
+
+    def _do(self, name, *args):
+        st = getattr(self.hip, name)(*args)
+        assert st == 0, (name, st)
+
+    def replay(self):
+        self._do("hipGraphLaunch", self.run, ctypes.c_void_p(self.stream.cuda_stream))
+
+    def close(self):
+        torch.cuda.synchronize()
+        self._do("hipGraphExecDestroy", self.run)
+        self._do("hipGraphDestroy", self.graph)
+
+
+class _Nobody:
+    def __getattr__(self, name):
+        return lambda *a, **k: None
+
+
+# what is recorded -> how many kernels that is, and how many with one that copies the models back in front
+RECORDED = {"plain_step": (1, 0), "step:odd": (1, 1), "step": (1, 0), "sgd_ar": (1, 0), "mean update": (2, 0), "mean merge plain_step": (3, 0),
+            "send mean merge": (3, 0), "send:even mean:even update:even": (3, 0), "step:odd plain_step": (2, 1), "fused": (1, 0)}
+
+
+@pytest.mark.parametrize("shape", [dict(), dict(waves_per_block=4, max_blocks=37, kper_step=3, kper_merge=5), dict(vec=4), dict(vec=2, group_r=2)])
+@pytest.mark.parametrize("what", list(RECORDED))
+def test_a_recorded_graph_holds_its_own_kernels_alone(what, shape):
+    """Recorded while the models are in s, and the same once more; replayed second one first, then with calls between.  The first kernel
+    of the first replay brings the models back, without a kernel of its own, wherever that first kernel writes all of them."""
+    K = 5
+    w = W.small(K=K, numels=(700, 3, 256, 420_001), storage="bf16")
+    orc, dev, grads = _pair(w)
+    full = (1 << K) - 1
+    masks = {"odd": 0b01010, "even": 0b10101}
+    graphs = []
+    try:
+        dev.ctx.set_tuning(avg_split=1, **shape)
+        g = grads(0)
+        dev.load_grads(g)
+        both, oracle, device = _calls(orc, dev.ctx, g, w), _calls(orc, _Nobody(), g, w), _calls(_Nobody(), dev.ctx, g, w)
+
+        def do(calls, words):
+            for word in words.split():
+                name, _, mask = word.partition(":")
+                calls[name](masks.get(mask, full))
+        do(both, "plain_step send mean update" + (" mean" if what == "fused" else ""))
+        graphs = [_Graph(dev.main, lambda: do(device, what)) for _ in range(2)]
+        kernels, copies = RECORDED[what]
+        assert [x.nodes for x in graphs] == [kernels + copies, kernels + copies]
+        for i, which in enumerate([1, 0, 0, 1]):
+            graphs[which].replay()
+            do(oracle, what)
+            compare_state(dev, orc, i)
+        for i in range(2):
+            do(both, "plain_step " + what)
+            graphs[i].replay()
+            do(oracle, what)
+            compare_state(dev, orc, 10 + i)
+    finally:
+        for x in graphs:
+            x.close()
+        dev.close()
+
+
+@pytest.mark.parametrize("what", ["plain_step", "fused", "mean update"])
+def test_a_call_before_the_first_replay_of_such_a_graph(what):
+    """The call brings the models back; the graph's first kernel finds them in the master copies then, whatever was in s."""
+    w = W.small(K=4, numels=(700, 3, 523_000), storage="bf16")
+    orc, dev, grads = _pair(w)
+    graph = None
+    try:
+        dev.ctx.set_tuning(avg_split=1)
+        g = grads(0)
+        dev.load_grads(g)
+        both, oracle, device = _calls(orc, dev.ctx, g, w), _calls(orc, _Nobody(), g, w), _calls(_Nobody(), dev.ctx, g, w)
+        for name in ("plain_step", "send", "mean", "update") + (("mean",) if what == "fused" else ()):
+            both[name]()
+        graph = _Graph(dev.main, lambda: [device[n]() for n in what.split()])
+        both["plain_step"]()
+        both["plain_step"]()
+        for i in range(3):
+            graph.replay()
+            for n in what.split():
+                oracle[n]()
+            compare_state(dev, orc, i)
+    finally:
+        if graph:
+            graph.close()
+        dev.close()
