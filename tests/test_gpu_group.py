@@ -200,7 +200,8 @@ def test_sgd_ar_every_group_shape(storage, K):
 @pytest.mark.parametrize("K", [4, 9, 11, 12, 13, 25])
 def test_streaming_shapes_of_the_group_calls(K, storage):
     """The shapes taken once the state no longer fits the memory-side cache (here asked for by the streaming hint):
-    one or two replicas a wave, paced workgroups, and from K = 13 on update + in-order mean.  z stays bit-exact."""
+    one or two replicas a wave, paced workgroups, and from K = 13 on update + in-order mean.  z stays bit-exact.
+    From K = 16 on the first of the two SGD-AR steps is one kernel and the second two."""
     w = W.small(K=K, numels=(1030, 1, 4, 257, 768, 2051), storage=storage, m=1, T=4)
     assert run_parity(w, tuning=dict(nontemporal=3), fused_mean=True) == 0
     from oracle import lasgd_oracle as O32
@@ -229,6 +230,32 @@ def test_streaming_shapes_of_the_group_calls(K, storage):
 def test_streaming_shapes_at_the_rules_edges(K, storage):
     """Both sides of each line of the shape rules that the test above leaves out."""
     test_streaming_shapes_of_the_group_calls(K, storage)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("K", [16, 17, 24, 25, 33])
+def test_streaming_sgd_ar_in_one_kernel_with_many_replicas(K, storage):
+    """What every call takes where there is no memory for the mean gradient's array: one replica a wave at K = 16, two up to 24,
+    then four, and several passes.  Tiles of 512 elements take it too, and go by the same rule."""
+    from oracle import lasgd_oracle as O32
+    from paper_2203_13085_amd.driver import DeviceReplicas
+    w = W.small(K=K, numels=(1030, 1, 4, 257, 768, 2051), storage=storage)
+    x0, grads = packed_inputs(w)
+    orc = O32.Oracle(K, w.numels, w.momentum, w.nesterov, [w.weight_decay] * len(w.numels), storage=storage)
+    dev = DeviceReplicas(w, weight_decay=[w.weight_decay] * len(w.numels))
+    try:
+        dev.ctx.set_tuning(nontemporal=3, vec=2)
+        orc.set_model(x0); dev.load_model(x0)
+        for i in range(3):
+            g = grads(i)
+            dev.load_grads(g)
+            orc.sgd_ar_step(g, w.lr)
+            dev.ctx.sgd_ar_step(w.lr)
+        for k in range(K):
+            assert_close(dev.ctx.read_state(B.STATE_X, k), orc.x[k], f"x replica {k}")
+            assert_close(dev.ctx.read_state(B.STATE_V, k), orc.v[k], f"v replica {k}")
+    finally:
+        dev.close()
 
 
 @pytest.mark.parametrize("storage,K,R,hint", [("bf16", 40, 1, 3), ("f32", 40, 2, 3), ("bf16", 33, 1, 4), ("f32", 64, 2, 4),

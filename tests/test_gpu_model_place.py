@@ -47,11 +47,13 @@ SEQUENCES = [
     "mean fused fused plain_step fused update mean fused merge plain_step",      # one pass after another, and out again
     "mean:odd update:odd step:odd mean:odd merge:odd step:even mean:odd update:odd send:even mean update",   # some in s, some not
     "mean merge:even step:odd merge:odd step:low mean fused step:odd update step:even send",
+    "sgd_ar mean:odd update:odd sgd_ar step:low send:even mean merge:even sgd_ar merge:odd sgd_ar sgd_ar",      # the same with some of the models in s
 ]
 
 
 SHAPES = [(1, (2_097_001, 3), 4), (5, (700, 3, 256, 420_001), 4), (5, (700, 3, 256, 420_001), 3), (12, (175_003, 64), 3),
-          (13, (161_515, 64), 3), (13, (161_515, 64), 4), (4, (523_265, 500), 4)]        # the last: one row short of 8 MiB
+          (13, (161_515, 64), 3), (13, (161_515, 64), 4), (4, (523_265, 500), 4),        # the last: one row short of 8 MiB
+          (17, (125_003, 64), 3)]        # sgd_ar in two kernels, from a sequence's second one on
 
 
 @pytest.mark.parametrize("K,numels,hint,sequence", [s + (q,) for s in SHAPES for q in SEQUENCES if s[0] > 1 or ":" not in q])
@@ -129,10 +131,12 @@ def test_graphs_recorded_while_the_models_are_in_s(fused, K, hint, sent, first):
         dev.close()
 
 
-def test_a_model_in_s_is_read_after_recording_before_any_replay():
-    w = W.small(K=3, numels=(700_001, 3), storage="bf16")
+@pytest.mark.parametrize("K,n,hint", [(3, 700_001, -1), (17, 125_003, 3)])          # 17: recorded as two kernels
+def test_a_model_in_s_is_read_after_recording_before_any_replay(K, n, hint):
+    w = W.small(K=K, numels=(n, 3), storage="bf16")
     orc, dev, grads = _pair(w)
     try:
+        dev.ctx.set_tuning(nontemporal=hint, avg_split=1)
         g = grads(0)
         dev.load_grads(g)
         calls = _calls(orc, dev.ctx, g, w)
@@ -241,6 +245,34 @@ def test_a_recorded_graph_holds_its_own_kernels_alone(what, shape):
             graphs[i].replay()
             do(oracle, what)
             compare_state(dev, orc, 10 + i)
+    finally:
+        for x in graphs:
+            x.close()
+        dev.close()
+
+
+def test_a_recorded_mean_gradient_and_its_step_bring_the_models_back():
+    """Two kernels are recorded, the second of which reads the models in s: no third that copies them.  The graph recorded last is
+    replayed first."""
+    w = W.small(K=17, numels=(125_003, 64), storage="bf16")
+    orc, dev, grads = _pair(w)
+    graphs = []
+    try:
+        dev.ctx.set_tuning(nontemporal=3, avg_split=1)
+        g = grads(0)
+        dev.load_grads(g)
+        calls = _calls(orc, dev.ctx, g, w)
+        for name in ("plain_step", "send", "mean", "update"):
+            calls[name]()
+        calls["step"](0b10010)
+        graphs = [_Graph(dev.main, lambda: dev.ctx.sgd_ar_step(w.lr)) for _ in range(2)]
+        assert [x.nodes for x in graphs] == [2, 2]
+        for i, which in enumerate([1, 0, 1]):
+            graphs[which].replay()
+            orc.sgd_ar_step(g, w.lr)
+            compare_state(dev, orc, i)
+            calls["sgd_ar"]()
+        compare_state(dev, orc, 99)
     finally:
         for x in graphs:
             x.close()

@@ -87,6 +87,35 @@ def test_streaming_fp32_local_step_asks_for_one_word_first(asm):
     assert not re.search(r"global_load_dword v", bf16)
 
 
+HOT = {
+    # streaming kernels of 256-element tiles: registers at most
+    "_ZN5lasgd12apply_kernelILi1ELi5ELb0ELi3EEEvNS_9ApplyArgsE": 64,      # a step with the mean gradient
+    "_ZN5lasgd12apply_kernelILi1ELi5ELb1ELi3EEEvNS_9ApplyArgsE": 64,
+    "_ZN5lasgd12apply_kernelILi1ELi0ELb1ELi3EEEvNS_9ApplyArgsE": 64,      # bf16 step, update and step + update, whose models may be in s
+    "_ZN5lasgd12apply_kernelILi1ELi1ELb1ELi3EEEvNS_9ApplyArgsE": 64,
+    "_ZN5lasgd12apply_kernelILi1ELi2ELb1ELi3EEEvNS_9ApplyArgsE": 64,
+    # the mean gradient holds eight rows and their addresses: seven waves a SIMD, and bounding its waves changed nothing
+    "_ZN5lasgd16mean_grad_kernelILb0ELi3EEEvNS_9ApplyArgsE": 72,
+    "_ZN5lasgd16mean_grad_kernelILb1ELi3EEEvNS_9ApplyArgsE": 72,
+}
+
+
+@pytest.mark.parametrize("name", list(HOT))
+def test_streaming_kernels_stay_in_registers(asm, name):
+    body = _kernel(asm, name)
+    assert re.search(r"\.amdhsa_private_segment_fixed_size 0\b", body)
+    assert not re.search(r"\bscratch_(load|store)|flat_(load|store)", body)
+    assert re.search(r"global_load_dwordx2 .* nt" if "mean_grad_kernelILb1" in name else r"global_load_dwordx4 .* nt", body)
+    assert int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", body).group(1)) <= HOT[name]
+
+
+def test_models_in_s_are_read_once(asm):
+    """bf16 step + update: one full-tile path loads x, v and s, the other, for a model that is in s, v and s."""
+    body = _kernel(asm, "_ZN5lasgd12apply_kernelILi1ELi2ELb1ELi3EEEvNS_9ApplyArgsE")
+    paths = [b for b in re.split(r"\n\.LBB\d+_\d+:", body) if re.search(r"global_load_dwordx2 .* nt", b)]
+    assert {len(re.findall(r"global_load_dwordx4 .* nt", b)) for b in paths} >= {2, 3}
+
+
 @pytest.mark.parametrize("nt", [0, 3])
 def test_mean_of_listed_participants_leaves_room_for_eight_waves(asm, nt):
     """A partial or elastic mean of few replicas: with more than 64 registers, and so fewer waves, it lost 4 %."""
