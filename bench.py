@@ -32,15 +32,24 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 
 
-def algorithmic_bytes(K: int, N: int, bf16: bool) -> dict:
-    """Bytes each kernel must move per launch (what the method needs, not what caches do)."""
+def update_bytes(K: int, N: int, bf16: bool, after_update: bool) -> int:
+    """What a global update that re-sends moves beyond a local step, per replica-parameter: s in and out.  bf16 storage from
+    8 MiB an array on keeps the model once, in s: it is not written to the master copy too, and right after another update
+    model and s are read once.  (In a recorded graph both are written; no rate is given for those legs.)"""
+    if not bf16 or 4 * K * N < 8 << 20:
+        return 8
+    return 0 if after_update else 4
+
+
+def algorithmic_bytes(K: int, N: int, bf16: bool, update: int = 8) -> dict:
+    """Bytes each kernel must move per launch (what the method needs, not what caches do).  update: see update_bytes."""
     # local step: read g, x, v; write x, v (bf16: g and the bf16 copy are 2 bytes each)
     step = (2 + 4 + 4 + 4 + 4 + 2 if bf16 else 20) * K * N
     # fused step + global update + re-send: also read s and z (once per parameter), write s
-    step_merge = step + 8 * K * N + 4 * N
+    step_merge = step + update * K * N + 4 * N
     average = 4 * (K + 1) * N
     # the same with the next mean computed in the pass: z is read once and written once per parameter
-    step_merge_average = step + 8 * K * N + 8 * N
+    step_merge_average = step + update * K * N + 8 * N
     return {"local_step": step, "step_merge": step_merge, "average": average, "step_merge_average": step_merge_average}
 
 
@@ -96,8 +105,8 @@ def cpu_baseline(w, seconds: float = 10.0) -> dict:
 
 def run_variant(args, w, make, alg) -> dict:
     """Timed loops over the extended entry points; one JSON line in the same format.
-    Bytes are algorithmic: 20 B per replica-parameter that steps, +8 B (+4/K for z) per
-    replica-parameter that merges and re-sends, 4(P+1) B per parameter for a mean over P."""
+    Bytes are algorithmic: 20 B per replica-parameter that steps, +8 B (bf16 see update_bytes; +4/K for z)
+    per replica-parameter that merges and re-sends, 4(P+1) B per parameter for a mean over P."""
     import numpy as np
     import torch
     K, N = w.K, w.N
@@ -136,7 +145,8 @@ def run_variant(args, w, make, alg) -> dict:
                     if j == max(counts) - 1:
                         c.step_merge_ex(lrs, mask, full, True)
                         c.average()
-                        nbytes += act * N * per_rp_step + 8 * K * N + 4 * N + alg["average"]
+                        update = update_bytes(K, N, w.storage == "bf16", after_update=j == 0)
+                        nbytes += act * N * per_rp_step + update * K * N + 4 * N + alg["average"]
                     else:
                         c.local_step_ex(lrs, mask)
                         nbytes += act * N * per_rp_step
@@ -155,7 +165,8 @@ def run_variant(args, w, make, alg) -> dict:
                 c.average_ex(part)
                 one.prev = part
                 steps_done += K * w.m
-                nbytes += w.m * alg["local_step"] + bin(one.prev).count("1") * N * 8 + 4 * N + 4 * (P + 1) * N \
+                update = update_bytes(K, N, w.storage == "bf16", after_update=False)
+                nbytes += w.m * alg["local_step"] + bin(one.prev).count("1") * N * update + 4 * N + 4 * (P + 1) * N \
                     + bin(late).count("1") * N * 8
             else:   # elastic: the headline cycle with alpha = beta = 0.5
                 for _ in range(w.m - 1):
@@ -254,7 +265,8 @@ def main() -> int:
         del src, dst
         torch.cuda.empty_cache()
 
-    alg = algorithmic_bytes(w.K, w.N, bf16)
+    alg = algorithmic_bytes(w.K, w.N, bf16, update_bytes(w.K, w.N, bf16, after_update=w.m == 1))
+    alg_alone = algorithmic_bytes(w.K, w.N, bf16, update_bytes(w.K, w.N, bf16, after_update=True))      # one launch after the other
     cycle_bytes = (w.m - 1) * alg["local_step"] + alg["step_merge"] + alg["average"]
     if args.mode != "lasgd":
         print(json.dumps(run_variant(args, w, make, alg)), flush=True)
@@ -432,9 +444,9 @@ def main() -> int:
         fused_bytes = (w.m - 1) * alg["local_step"] + alg["step_merge_average"]
         detail = {
             "alone_ms": {"local_step": t_step, "step_merge": t_sm, "average": t_av, "step_merge_average": t_sma},
-            "alone_GBps": {"local_step": alg["local_step"] / t_step / 1e6, "step_merge": alg["step_merge"] / t_sm / 1e6,
+            "alone_GBps": {"local_step": alg["local_step"] / t_step / 1e6, "step_merge": alg_alone["step_merge"] / t_sm / 1e6,
                            "average": alg["average"] / t_av / 1e6,
-                           "step_merge_average": alg["step_merge_average"] / t_sma / 1e6},
+                           "step_merge_average": alg_alone["step_merge_average"] / t_sma / 1e6},
             "ms_per_cycle_one_stream": ms_serial,
             "ms_per_cycle_two_streams": ms_two,
             "ms_per_cycle_hip_graph": ms_graph,

@@ -195,6 +195,21 @@ def test_algorithmic_bytes_match_the_per_unit_figures():
     assert round(((w.m - 1) * a["local_step"] + a["step_merge"] + a["average"]) / 1e9, 2) == 19.01
 
 
+def test_algorithmic_bytes_of_an_update_that_keeps_the_model_once():
+    """bf16 from 8 MiB an array on: 24 B per replica-parameter, 20 right after another update; all else as above."""
+    import bench
+    w = W.config(4)
+    KN, z = w.K * w.N, 4 * w.N
+    after = {False: 24 * KN, True: 20 * KN}
+    for after_update, bytes_ in after.items():
+        a = bench.algorithmic_bytes(w.K, w.N, True, bench.update_bytes(w.K, w.N, True, after_update))
+        assert (a["local_step"], a["step_merge"], a["step_merge_average"]) == (20 * KN, bytes_ + z, bytes_ + 2 * z)
+        assert bench.update_bytes(w.K, w.N, False, after_update) == 8
+        assert bench.update_bytes(4, 500_000, True, after_update) == 8
+    # ResNet-50 list, K = 32, m = 8: 137.6 GB a cycle
+    assert round((7 * 20 * KN + after[False] + z + 4 * (w.K + 1) * w.N) / 1e9, 1) == 137.6
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
