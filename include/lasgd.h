@@ -32,8 +32,8 @@
  * Memory owned by the library:  momentum v[k], sent models s[k], the mean z,
  *   the fp32 master copy of the parameters when storage is bf16 (from 8 MiB of it
  *   on a global update that re-sends leaves the model in s alone until the next
- *   step; once a call has been recorded into a graph, in both), and the lookup
- *   tables; from the first lasgd_sgd_ar_step on that takes two kernels, the mean
+ *   step, "kept once" below; once a call that reads or writes the models has been
+ *   recorded into a graph, in both for good), and the lookup tables; from the first lasgd_sgd_ar_step on that takes two kernels, the mean
  *   gradient between them (one array of one replica's length).
  *
  * Paper <-> calls.  Prologue (steps 1-5): lasgd_local_step(eta_0),
@@ -93,7 +93,8 @@ typedef struct {
 typedef struct {
     int32_t vec;           /* 128-bit vectors per lane per tile: 1, 2 or 4 (tile = 256*vec elements) */
     int32_t kper_step;     /* replicas one wave handles back to back in local_step (1..K)            */
-    int32_t kper_merge;    /* same for merge / step_merge; K keeps each z tile in registers          */
+    int32_t kper_merge;    /* same for merge / step_merge, and the step of an sgd_ar_step in two kernels;
+                              K keeps each z tile in registers                                        */
     int32_t max_blocks;    /* cap on workgroups per launch (grid-stride beyond it); <0 = no cap      */
     int32_t avg_split;     /* waves of a workgroup that share one tile's K replicas in average (1,2,4) */
     int32_t avg_max_blocks;/* cap on workgroups of the average kernel; <0 = no cap                   */
@@ -101,18 +102,20 @@ typedef struct {
                               kernels also take their streaming shapes: the step and merge kernels bound
                               their waves per CU through LDS that they ask for and do not use (up to a CU's
                               160 KiB among the waves of a local step), and lasgd_step_merge_average takes
-                              two kernels beyond 12 replicas (bf16 24).  4 switches that off too.
+                              two kernels beyond 12 replicas (24 where the model is kept once).  4 switches that off too.
                               Once set, it holds for every call.  <0 = default: each call decides by the size of one array of all
                               replicas, from 28 MiB on for steps, updates and the mean, 40 MiB for
-                              lasgd_sgd_ar_step, 128 MiB (bf16 96) for lasgd_step_merge_average.  These sizes are right
+                              lasgd_sgd_ar_step, 128 MiB (96 where the model is kept once, see above) for lasgd_step_merge_average.  These sizes are right
                               for a program that has other memory to move between the calls; one that calls
                               nothing else, on a single state that fits the 256 MB memory-side cache, gains
                               1-3 % with 4 up to 64 MB an array (lasgd_sgd_ar_step 5-13 % up to 112 MB)    */
     int32_t chunk_step;    /* work-item order of local_step / snapshot: tiles are taken in chunks of this
                               many; inside a chunk replica after replica.  1 = the replicas of a tile are
-                              adjacent; <0 = whole replica after whole replica                       */
-    int32_t chunk_merge;   /* same for merge / step_merge (a chunk's z tiles are reused K times within
-                              a short window; multiples of 32 keep a tile on one XCD's L2)           */
+                              adjacent; <0 = whole replica after whole replica, but bf16 steps without the
+                              streaming hint between two lasgd_step_merge_average calls in chunks of 64 */
+    int32_t chunk_merge;   /* same for merge / step_merge and the step of an sgd_ar_step in two kernels (a
+                              chunk's z tiles are reused K times within a short window; multiples of 32
+                              keep a tile on one XCD's L2)                                           */
     int32_t waves_per_block; /* independent waves per workgroup in the multi-tensor kernels: 1, 2 or 4  */
     int32_t race_probe;    /* debugging aid, 1 = on, <0 = off (default): lasgd_average first fills z with NaN
                               on the stream the mean runs on, so a global update that did not wait for the mean shows
@@ -224,8 +227,8 @@ lasgd_status lasgd_step_merge(lasgd_ctx *ctx, float lr, int32_t resnapshot);
  * (Algorithm 1 steps 7 and 9a-c, then Sec. 3 Eq. 8 on the models just re-sent):
  * exactly lasgd_step_merge(lr, 1) followed by lasgd_average, same roundings, but
  * the K replicas of each tile meet in on-chip memory, so the sent models are not
- * read back for the mean (more than 12 replicas, bf16 24, of a model beyond the memory-side
- * cache take two kernels, which is faster there).  Everything runs on the main
+ * read back for the mean (more than 12 replicas, 24 where the model is kept once, of a state
+ * beyond the memory-side cache take two kernels, which is faster there).  Everything runs on the main
  * stream (after the pending average), nothing on the side stream; afterwards the new mean counts as
  * launched, exactly as after lasgd_average.  Meant for cadences with nothing to
  * overlap the All-Reduce with (a global update every step, tau_max = 1 in Sec. 5.2).

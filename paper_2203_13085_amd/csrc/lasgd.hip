@@ -52,7 +52,7 @@ struct lasgd_ctx {
     bool clear_in_graph = false;     // one was recorded: from then on a replay of it may be queued at any time
     int device = 0;
 
-    // device memory: the state's arrays are one allocation, carved up
+    // device memory: v, s, z and x32 are one allocation, carved up
     char *arena = nullptr;
     float *v = nullptr, *s = nullptr, *z = nullptr, *x32 = nullptr;
     float *gbar = nullptr;           // mean gradient [npad] of an SGD All-Reduce step in two kernels, see reserve_mean_grad
@@ -273,7 +273,7 @@ lasgd_tuning default_tuning(const lasgd_ctx &c)
 constexpr uint32_t kLdsGranule = 1280;
 constexpr size_t kCuLds = 163840;
 constexpr size_t kOneGroupLds = (kCuLds / 2 / kLdsGranule + 1) * kLdsGranule;      // two workgroups with this do not fit a CU
-constexpr size_t kMaxLds = 65536;      // never more for pacing: what a workgroup may ask for without further ado
+constexpr size_t kMaxLds = 65536;      // what a workgroup may ask for without further ado: pacing stops there, but for kOneGroupLds (launch_flat_update)
 // Step + update asks for a word of its model before its loads, as the fp32 local step always does, and then runs 16 waves a CU in
 // place of 12, up to 1e8 replica-parameters.  A pass's us without / with, over three states in turn (and with other work between
 // the passes): MobileNetV2 list K = 16, every step 285 / 280 (287 / 290), with m = 2 456 / 449 (460 / 455), partial rounds 411 / 402 (422 / 416);
@@ -1425,6 +1425,7 @@ template <int NT> hipError_t launch_flat_update(FlatArgs &a, uint32_t blocks, hi
         // K = 20 to 32, two groups a CU / one: 2,000,003 elements K = 18 100.8 / 101.3, 19 106.8 / 106.1, 20 113.6 / 112.0, 22 127.5 / 124.2,
         // 24 139.1 / 135.3; 12,000,000 K = 18 609.7 / 589.0, 20 689.8 / 655.2, 22 773.2 / 747.1, 24 839.0 / 819.5; 450 MB K = 25 336 / 323,
         // K = 27 356 / 342, K = 29 337 / 330, K = 32 351 / 345; but K = 17 94.6 / 96.9 and, of 12,000,000 elements, 567.9 / 558.6.
+        // So from 20 on one group is better at every length; at 17 and 18 it is for long vectors only, and they keep two.
         // Four replicas a wave, K > 32, have enough in flight to wait for s alone at no gain, and are bounded to two groups: at once
         // and no bound / staged / at once and bounded, K = 33, n = 3.5e6 329.0 / 327.3 / 322.8, K = 40, 4e6 423.6 / 426.1 / 422.4,
         // K = 48, 3e6 451.7 / 456.4 / 451.4, K = 64, 3e6 560.3 / 563.4 / 560.3.

@@ -79,7 +79,8 @@ struct ApplyArgs {
     uint32_t kcount;        // replicas that take part (K, or fewer in the extended calls)
     uint32_t kper;          // replicas a wave handles back to back
     uint32_t kgroups;       // ceil(kcount / kper)
-    uint32_t nitems;        // ntiles * kgroups (the replica-group kernels: ntiles rounded down to a multiple of eight)
+    uint32_t nitems;        // full_items + tail_stride * kgroups if there is a tail: padding items among them (the replica-group
+                            // kernels: ntiles rounded down to a multiple of eight)
     // 0, 0: items in order; nitems (a multiple of eight) - 8, ~7: from the last eight to the first.  They stand here because a wave
     // needs them as early as its neighbours: at the end of the arguments, another cache line, they cost a short call 0.3 us.
     uint32_t back, back_mask;
@@ -1052,7 +1053,7 @@ __global__ __launch_bounds__(1024) void sgd_ar_kernel(const ApplyArgs a, const u
 // The same in two kernels: the mean gradient (here) into an arena of its own, then OP_STEP_MEAN, which reads it as an update
 // reads z.  Bound by HBM like the mean of the sent models: one wave a tile, eight replicas' rows in flight, summed in replica
 // order, so the result is that of the one kernel to the bit.  It moves 8 bytes a parameter more than the one kernel and gains
-// from one-wave workgroups; lasgd_sgd_ar_step holds the line and both sides.
+// from one-wave workgroups; mean_grad_first in the host code holds the line and both sides.
 template <bool BF16, int NT, bool FULL>
 __device__ __forceinline__ void mean_grad_tile(const ApplyArgs &a, const Tile &t, uint32_t tensor, uint32_t lane)
 {
