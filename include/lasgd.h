@@ -189,7 +189,7 @@ lasgd_status lasgd_snapshot(lasgd_ctx *ctx);
  * The All-Reduce itself (Sec. 3, Eq. 8): z = (1/K) sum_k s[k], accumulated in
  * fp64 and rounded once.  Runs on the side stream after everything enqueued so
  * far on the main stream; the main stream does not wait for it.  A mean that moves
- * no more than 16 MiB (participants + 1 padded models) runs on the main stream, where
+ * no more than 16 MiB (participants + 1 models, tensors in whole rows of 256) runs on the main stream, where
  * it takes less than the events around it would: lasgd_average_done, and not the side
  * stream, says when a mean is over.
  * Errors: STATE (no snapshot since the last merge that did not re-snapshot;
